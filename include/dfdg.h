@@ -95,7 +95,13 @@ typedef struct {
                         aggregation multigrid V-cycle (Chebyshev(2) smoothing on the
                         finest level, one Chebyshev(1) step before and after the
                         correction on the coarser levels; coarse space spanned by the
-                        constant multiplier; built on the host at context creation) */
+                        constant multiplier; built on the host at context creation).  Small
+                        meshes (up to 32768 multipliers on triangles, 65536 on tetrahedra if
+                        the matrices fit) with mg_fp32 = 1 or the Krylov refinement and
+                        facet_blocks = 0 take an exact solve in FP32 in the cycle's place: the
+                        interiors of cells of elements eliminated, the interface between the
+                        cells inverted densely (factored on the GPU when the workspace is
+                        bound) */
   double ir_rtol;    /* MIXED: outer FP64 refinement target (relative residual) */
   double inner_rtol; /* MIXED, mixed_solver = 0: FP32 inner PCG reduction per refinement step */
   int extrapolate;   /* rk3_step: 0 = warm start from the last same-stage multiplier,

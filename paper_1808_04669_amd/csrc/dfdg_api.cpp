@@ -13,6 +13,7 @@
 
 #include "dfdg.h"
 #include "dfdg_amg.h"
+#include "dfdg_elim.h"
 #include "dfdg_kernels.h"
 #include "dfdg_setup.h"
 
@@ -64,6 +65,11 @@ struct dfdg_ctx {
   // multigrid preconditioner
   AmgHierarchy H;
   MgDev mg;
+  // block elimination in the multigrid cycle's place on small meshes
+  ElimHost eh;
+  ElimDev el{};
+  bool el_on = false;
+  double* elST = nullptr;
   // PCG iterations captured as HIP graphs (kernel arguments fixed: the solve runs in lamx)
   double* lamx = nullptr;
   hipStream_t cap_stream = nullptr;
@@ -295,6 +301,12 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
     return DFDG_E_UNSUPPORTED;
   }
   ctx->hs.fe4 = ctx->dim == 2 && prm->local_space == DFDG_LOCAL_FE4;
+  // small meshes precondition with the block elimination in the FP32 cycle's place, unless the
+  // caller asked for a launch shape of the facet kernels (see kElimUnknowns)
+  const bool krylov = prm->precision == DFDG_FP64 ? prm->mg_fp32 != 0 : prm->mixed_solver == 1;
+  if (prm->precond == DFDG_AMG && krylov && prm->facet_blocks == 0)
+    ctx->el_on = build_elim(mesh->m, ctx->dim == 3 ? nF3(prm->k) : nF(prm->k), ctx->eh);
+  ctx->hs.keep_ST = ctx->el_on;
   if ((ctx->dim == 3 ? build_setup3(mesh->m, prm->k, prm->alpha, ctx->hs, e)
                      : build_setup(mesh->m, prm->k, prm->alpha, ctx->hs, e))) {
     g_mesh_err = e;
@@ -325,6 +337,8 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
   ctx->E = mesh->m.E;
   ctx->nU = (long)ctx->dim * ctx->P * ctx->T;
   ctx->nL = (long)ctx->NF * ctx->E;
+  // a hierarchy of one level is solved densely as it is
+  if (ctx->H.lv.size() < 2) ctx->el_on = false;
   *out = ctx;
   return DFDG_OK;
 }
@@ -578,6 +592,41 @@ static void carve(dfdg_ctx* ctx, char* base) {
     mg.coarse_inv = c.take<double>(H.coarse_inv.size());
     mg.coarse_inv32 = f32 ? c.take<float>(H.coarse_inv.size()) : nullptr;
   }
+  if (ctx->el_on) {
+    const ElimHost& h2 = ctx->eh;
+    ElimDev& D = ctx->el;
+    D = ElimDev{};
+    D.nc = h2.nc;
+    D.ng = h2.ng;
+    D.NF = (int)NF;
+    D.maxB = h2.maxB;
+    D.maxV = h2.maxV;
+    for (int i = 0; i < h2.nc; ++i) D.maxN = std::max(D.maxN, (h2.noff[i + 1] - h2.noff[i]) * (int)NF);
+    D.boff = c.take<int>(h2.boff.size());
+    D.bfac = c.take<int>(h2.bfac.size());
+    D.noff = c.take<int>(h2.noff.size());
+    D.ngam = c.take<int>(h2.ngam.size());
+    D.nfac = c.take<int>(h2.nfac.size());
+    D.gfac = c.take<int>(h2.gfac.size());
+    D.gpos = c.take<int>(h2.gpos.size());
+    D.gcell = c.take<int>(h2.gpos.size());
+    D.eoff = c.take<int>(h2.eoff.size());
+    D.elem = c.take<int>(h2.elem.size());
+    D.elp = c.take<int>(h2.elp.size());
+    D.moff = c.take<long>(h2.moff.size());
+    D.foff = c.take<long>(h2.foff.size());
+    D.zhat = c.take<double>(h2.ng);
+    const size_t n = (size_t)h2.ng * NF, ld = (n + 3) & ~size_t(3);
+    D.mat = c.take<float>(h2.mvals);
+    D.tmat = c.take<float>(n * ld);
+    D.contrib = c.take<float>(h2.ngam.size() * NF);
+    D.front = c.take<double>(h2.fvals);
+    D.top = c.take<double>(n * n);
+    const size_t pan = 32 * std::max((size_t)h2.nc * h2.maxV, n);
+    D.panW = c.take<double>(pan);
+    D.panR = c.take<double>(pan);
+    ctx->elST = c.take<double>(h.ST.size());
+  }
   ctx->ws_need = c.off + 256;
 }
 
@@ -738,6 +787,40 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
     }
     HIPC(hipStreamSynchronize(s));
   }
+  if (ctx->el_on) {
+    const ElimHost& e = ctx->eh;
+    ElimDev& D = ctx->el;
+    std::vector<int> gcell(e.gpos.size(), -1), cellof(e.ngam.size());
+    for (int c = 0; c < e.nc; ++c)
+      for (int i = e.noff[c]; i < e.noff[c + 1]; ++i) cellof[i] = c;
+    for (size_t i = 0; i < e.gpos.size(); ++i)
+      if (e.gpos[i] >= 0) gcell[i] = cellof[e.gpos[i]];
+    // kernel vector on the interface, and the mean diagonal as the size of the shift along it
+    std::vector<double> zhat(e.ng, 0.0);
+    double zz = 0, diag = 0;
+    for (int i = 0; i < e.ng; ++i) zz += h.zdef[e.gfac[i]] * h.zdef[e.gfac[i]];
+    for (double d : h.dinv) diag += 1.0 / d;
+    if (h.singular)
+      for (int i = 0; i < e.ng; ++i) zhat[i] = h.zdef[e.gfac[i]] / std::sqrt(zz);
+    const double shift = h.singular ? diag / h.dinv.size() : 0.0;
+    HIPC(up(const_cast<int*>(D.boff), e.boff, s));
+    HIPC(up(const_cast<int*>(D.bfac), e.bfac, s));
+    HIPC(up(const_cast<int*>(D.noff), e.noff, s));
+    HIPC(up(const_cast<int*>(D.ngam), e.ngam, s));
+    HIPC(up(const_cast<int*>(D.nfac), e.nfac, s));
+    HIPC(up(const_cast<int*>(D.gfac), e.gfac, s));
+    HIPC(up(const_cast<int*>(D.gpos), e.gpos, s));
+    HIPC(up(const_cast<int*>(D.gcell), gcell, s));
+    HIPC(up(const_cast<int*>(D.eoff), e.eoff, s));
+    HIPC(up(const_cast<int*>(D.elem), e.elem, s));
+    HIPC(up(const_cast<int*>(D.elp), e.elp, s));
+    HIPC(up(const_cast<long*>(D.moff), e.moff, s));
+    HIPC(up(const_cast<long*>(D.foff), e.foff, s));
+    HIPC(up(const_cast<double*>(D.zhat), zhat, s));
+    HIPC(up(ctx->elST, h.ST, s));
+    HIPC(launch_elim_factor(D, ctx->dim + 1, ctx->elST, shift, s));
+    HIPC(hipStreamSynchronize(s));  // the host lists end with this block
+  }
   HIPC(hipStreamSynchronize(s));
   if (!ctx->pinned) HIPC(hipHostMalloc((void**)&ctx->pinned, 4 * sizeof(PcgScalars), hipHostMallocDefault));
   // the device address of the allocation-free diagnostics' scratch on this (current) device
@@ -850,7 +933,7 @@ static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGrap
   // With the multigrid cycle (two levels or more) the last kernel of an iteration applies
   // the stopping test, so a run of n iterations takes n launches; otherwise the next
   // iteration's first kernel applies it and a run takes n + 1
-  const int extra = (amg && ctx->mg.nlev >= 2) ? 0 : 1;
+  const int extra = (amg && ctx->mg.nlev >= 2) ? 0 : 1;  // (the elimination likewise)
   // the first chunk: the fewest iterations among the last kHintRuns runs.  With start
   // values that vary in quality the count varies from solve to solve; a chunk that falls
   // short costs one host round trip, while each iteration enqueued past the end still runs
@@ -858,7 +941,7 @@ static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGrap
   int h = hint[0];
   for (int j = 1; j < kHintRuns; ++j)
     if (hint[j] > 0) h = std::min(h, hint[j]);
-  int chunk = h > 0 ? h + extra : (amg ? 16 : 64);
+  int chunk = h > 0 ? h + extra : (ctx->el_on ? 4 : amg ? 16 : 64);
   fin.done = PCG_RUNNING;
   int launched = 0;
   while (fin.done == PCG_RUNNING) {
@@ -994,8 +1077,11 @@ static int solve_facets(dfdg_ctx* ctx, double* lam, dfdg_solve_info* info, const
     }
     HIPC(launch_pcg_init(NF, bj, g, A, ctx->gv, x, ctx->r, ctx->z, ctx->p[0], pb, s, !proj));
     const bool c32 = mixed || ctx->prm.mg_fp32 != 0;
-    const bool fused = amg && ctx->mg.nlev >= 2;
-    if (amg) {
+    const bool elim = ctx->el_on;
+    const bool fused = amg && ctx->mg.nlev >= 2 && !elim;
+    if (elim) {
+      HIPC(launch_elim_apply(ctx->el, g, ctx->r, ctx->z, pb.rz[0], pb.sc, s));
+    } else if (amg) {
       if (c32) HIPC((launch_vcycle<float, double>(NF, g, A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
       else HIPC((launch_vcycle<double, double>(NF, g, A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
     }
@@ -1015,6 +1101,7 @@ static int solve_facets(dfdg_ctx* ctx, double* lam, dfdg_solve_info* info, const
       if (e != hipSuccess) return e;
       e = launch_pcg_update(NF, pc, g, A, pout, ctx->Sp, x, ctx->r, ctx->z, pb, it, st);
       if (e != hipSuccess || !amg) return e;
+      if (elim) return launch_elim_apply(ctx->el, g, ctx->r, ctx->z, pb.rz[it & 1], pb.sc, st);
       if (c32) return launch_vcycle<float, double>(NF, g, A, ctx->mg, ctx->r, ctx->z, pb.rz[it & 1], pb.sc, st);
       return launch_vcycle<double, double>(NF, g, A, ctx->mg, ctx->r, ctx->z, pb.rz[it & 1], pb.sc, st);
     };

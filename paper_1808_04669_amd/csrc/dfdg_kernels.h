@@ -91,6 +91,24 @@ hipError_t launch_pcg_iteration_mg(int NF, const DevGeo& g, const DevBsr& A, con
                                    int it, const VB* z_in, const VB* p_old, VB* p_new, VB* Sp, VB* x,
                                    const VB* r_old, VB* r_new, VB* z, hipStream_t s);
 
+// Block elimination of the facet system on small meshes (dfdg_elim.hip): index lists as in
+// ElimHost, solve matrices in FP32, fronts and panels of the set-up in FP64.
+constexpr int kElimMaxVec_ = 12288;
+struct ElimDev {
+  int nc, ng, NF, maxB, maxN, maxV;
+  const int *boff, *bfac, *noff, *ngam, *nfac, *gfac, *gpos, *gcell, *eoff, *elem, *elp;
+  const long *moff, *foff;
+  const double* zhat;   // [ng] kernel vector of the interface matrix (mode 0), normalised
+  float *mat, *tmat, *contrib;
+  double *front, *top, *panW, *panR;
+};
+// ST [T][nr][nr]: the elements' facet matrices; shift > 0 for a system with a kernel.
+hipError_t launch_elim_factor(const ElimDev& D, int nfac, const double* ST, double shift, hipStream_t s);
+// z = S^+ r up to FP32 rounding, (r, z) partials into rz[2*block] and the stopping test of the
+// iteration; all kernels return at once when the PCG has stopped.
+hipError_t launch_elim_apply(const ElimDev& D, const DevGeo& g, const double* r, double* z, double* rz,
+                             PcgScalars* sc, hipStream_t s);
+
 // g[E][NF] = facet sums of q, then (one block) the deflated (g,g) and the stopping
 // threshold tol2 = rtol^2 (g,g) into pb.sc (done = RUNNING, or CONVERGED for g = 0).
 // Start/stop events for the dispatch packet of the next SpMV or residual launch (kernel

@@ -638,6 +638,7 @@ int condense_elements(HostSetup& h, int nfac, int NP, int NU, int NF, const Cond
   std::vector<double> diagR((size_t)E * NF * NF, 0.0);
   std::atomic<int> bad(-1);
   const int ND = h.fe4 ? NU - NP : 0;
+  if (h.keep_ST) h.ST.assign((size_t)T * NR * NR, 0.0);
   auto work = [&](int t0, int t1) {
     std::vector<double> D((size_t)NP * NU), DDt((size_t)NP * NP), C((size_t)NR * NU), CDt((size_t)NR * NP),
         X((size_t)NR * NP), ST((size_t)NR * NR), Z((size_t)NU * ND), ZZ((size_t)ND * ND), CZ((size_t)NR * ND),
@@ -714,6 +715,13 @@ int condense_elements(HostSetup& h, int nfac, int NP, int NU, int NF, const Cond
           for (int j = 0; j < NP; ++j) s -= X[(size_t)r * NP + j] * CDt[(size_t)c2 * NP + j];
           ST[(size_t)r * NR + c2] = ST[(size_t)c2 * NR + r] = s;
         }
+      if (h.keep_ST) {
+        double* keep = &h.ST[(size_t)t * NR * NR];
+        std::copy(ST.begin(), ST.end(), keep);
+        for (int f = 0; f < nfac; ++f)
+          if (h.sF[(size_t)f * T + t] == 0.0)  // outflow facet: no face rows, an identity block
+            for (int a = f * NF; a < (f + 1) * NF; ++a) keep[(size_t)a * NR + a] = 1.0;
+      }
       for (int f = 0; f < nfac; ++f) {
         const int F = h.efacet[(size_t)f * T + t];
         const bool isR = el.isR(t, f);

@@ -39,6 +39,10 @@ struct HostSetup {
   bool fe4 = false;
   std::vector<double> G4;
   std::vector<int> nbr, code, efacet, qL, qR, cols;
+  // the elements' facet matrices S_T [T][nfac*NF][nfac*NF], kept when keep_ST is set before
+  // build_setup (an outflow facet's identity block included)
+  bool keep_ST = false;
+  std::vector<double> ST;
 };
 
 int build_mesh(int T, const double* xyz, const double* period, MeshHost& m, std::string& err);
