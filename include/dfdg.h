@@ -134,7 +134,9 @@ typedef struct {
                         results are the same up to the order of the partial sums. */
   int matrix_free;   /* tetrahedral meshes, FP64 PCG: 1 = form S p element by element as
                         sum_T C_T W_T C_T^T p from the element data (two passes, no matrix
-                        read) instead of reading the assembled S; 0 = assembled S (default).
+                        read) instead of reading the assembled S; 0 = assembled S (default)
+                        below 32768 elements, element by element above, where S no longer
+                        fits the cache.
                         The multigrid smoothing still reads S.  Triangle meshes: must be 0. */
   int mixed_solver;  /* MIXED facet solves (the residual is FP32 in both):
                         1 = Krylov refinement (default): FP64 PCG iterations (FP64 S, vectors,

@@ -383,6 +383,15 @@ struct Carver {
 
 static int d3slots(const dfdg_ctx* ctx) { return ctx->dim == 3 ? kSlots3 : kSlots; }
 
+// Whether the FP64 PCG forms its products element by element instead of reading S: when the
+// caller asks for it, and on tetrahedral meshes from 32768 elements on.  Measured, Jacobi
+// iteration with and without: BDM_2 16^3 (24576 elements) 35 / 36 us, 20^3 41 / 53, 24^3 50 /
+// 133, 32^3 87 / 240 (S no longer fits the Infinity Cache from 21^3 on); BDM_1 16^3 19 / 20,
+// 24^3 33 / 37, 32^3 54 / 86.
+static bool mf_products(const dfdg_ctx* ctx) {
+  return ctx->prm.matrix_free != 0 || (ctx->dim == 3 && ctx->T >= 32768);
+}
+
 static void carve(dfdg_ctx* ctx, char* base) {
   Carver c{base};
   const HostSetup& h = ctx->hs;
@@ -425,6 +434,7 @@ static void carve(dfdg_ctx* ctx, char* base) {
   d.Zh = tb.Zh.empty() ? nullptr : c.take<double>(tb.Zh.size());
   d.fpidx = tb.fpidx.empty() ? nullptr : c.take<int>(tb.fpidx.size());
   d.Qf = tb.Qf.empty() ? nullptr : c.take<double>(tb.Qf.size());
+  d.cond = tb.cond.empty() ? nullptr : c.take<double>(tb.cond.size());
   DevBsr& A = ctx->A;
   A.ns = d3slots(ctx);
   A.cols = c.take<int>(h.cols.size());
@@ -445,11 +455,8 @@ static void carve(dfdg_ctx* ctx, char* base) {
   // work
   ctx->Lbuf = c.take<double>(nU);
   ctx->q = c.take<double>(nfac * NF * T);
-  // the matrix-free products use q for the face contributions: the condensation right-hand
-  // side in it has been gathered into g before the PCG runs, and nothing reads it after
-  A.mfq = ctx->prm.matrix_free ? ctx->q : nullptr;
-  A.mfCh = d.Ch;
-  A.mfDh = d.Dh;
+  A.mfq = mf_products(ctx) ? c.take<double>(2 * nL) : nullptr;
+  A.mfcond = d.cond;
   A.mfQf = d.Qf;
   A.mfK = ctx->K;
   ctx->gv = c.take<double>(nL);
@@ -691,6 +698,7 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
   if (ctx->tb.Zh) HIPC(up(const_cast<double*>(ctx->tb.Zh), tb.Zh, s));
   if (ctx->tb.fpidx) HIPC(up(const_cast<int*>(ctx->tb.fpidx), tb.fpidx, s));
   if (ctx->tb.Qf) HIPC(up(const_cast<double*>(ctx->tb.Qf), tb.Qf, s));
+  if (ctx->tb.cond) HIPC(up(const_cast<double*>(ctx->tb.cond), tb.cond, s));
   HIPC(up(const_cast<int*>(ctx->A.cols), h.cols, s));
   HIPC(up(const_cast<double*>(ctx->A.vals), h.vals, s));
   HIPC(up(const_cast<double*>(ctx->A.dinv), h.dinv, s));
@@ -1097,7 +1105,7 @@ static int solve_facets(dfdg_ctx* ctx, double* lam, dfdg_solve_info* info, const
         return launch_pcg_iteration_mg<double, double>(NF, g, A, ctx->mg, pb, it, ctx->z, pin, pout, ctx->Sp, x, rin,
                                                        rout, ctx->z, st);
       }
-      hipError_t e = launch_pcg_spmv(NF, g, A, ctx->z, pin, pout, ctx->Sp, pb, it, st);
+      hipError_t e = launch_pcg_spmv(NF, g, A, ctx->z, pin, pout, ctx->Sp, pb, it, st, amg);
       if (e != hipSuccess) return e;
       e = launch_pcg_update(NF, pc, g, A, pout, ctx->Sp, x, ctx->r, ctx->z, pb, it, st);
       if (e != hipSuccess || !amg) return e;
@@ -1749,9 +1757,10 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
     double b = 0;
     switch (which) {
       case 0:
-        if (ctx->A.mfq)  // element pass: Jinv, (D D^T)^{-1}, per face id, code, sqrt(|F|/det), normal,
-                         // z and p_old gathered, contributions out; face pass: 2 offsets, both
-                         // contributions, z, p_old in, p_new, Sp out
+        if (ctx->A.mfq)  // two passes that each read z and p_old: per element Jinv, (D D^T)^{-1}, per
+                         // face id, code, sqrt(|F|/det), normal, z and p_old gathered,
+                         // contributions out; per face 2 offsets, both contributions, z, p_old
+                         // in, p_new, Sp out (the element pass now writes p_new itself)
           b = T * (9 * 8.0 + nGpk3(ctx->K) * 8.0 + 4 * (2 * 4.0 + 4 * 8.0) + 4 * NF * 2 * 8.0 + 4 * NF * 8.0) +
               E * (2 * 4.0 + 6.0 * NF * 8.0);
         else

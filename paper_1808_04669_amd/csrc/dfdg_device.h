@@ -23,11 +23,12 @@ __device__ inline double wave_max(double x) {
 // Block index remapped so that each of the 8 XCDs (which take the launched blocks round
 // robin, each with its own L2) works on one contiguous range of rows: neighbouring
 // elements and facets, whose data a block gathers, then mostly sit in the same L2.
-// A bijection of [0, gridDim.x) for every grid size.
-__device__ inline int xcd_block() {
-  const int G = gridDim.x, b = blockIdx.x, x = b & 7;
+// A bijection of [0, gridDim.x) for every grid size, or of [0, G) on the first G blocks.
+__device__ inline int xcd_block(int G) {
+  const int b = blockIdx.x, x = b & 7;
   return x * (G >> 3) + min(x, G & 7) + (b >> 3);
 }
+__device__ inline int xcd_block() { return xcd_block(gridDim.x); }
 
 // A read-only table (reference-element matrices) seen through the constant address
 // space: reads at wave-uniform indices then compile to scalar loads into SGPRs.  Through

@@ -76,6 +76,7 @@ struct RefTables {
   // permutation p maps the own one to (orthogonal change of the face basis)
   std::vector<int> fpidx;            // [6][nqf]
   std::vector<double> Qf;            // [6][NF][NF]
+  std::vector<double> cond;          // Ch as [4][P][NF], then Dh as [P][NP][3]
 };
 void gauss_legendre01(int n, std::vector<double>& x, std::vector<double>& w);
 void triangle_rule(int degree, std::vector<double>& pts, std::vector<double>& w);
@@ -130,14 +131,15 @@ struct DevTabs {
   const double* Dh; const double* Ch;
   const double* Zh;                    // triangles: RefTables::Zh
   const int* fpidx; const double* Qf;  // tetrahedra: face point and face basis permutations
+  const double* cond;                  // tetrahedra: RefTables::cond
 };
 struct DevBsr {
   int ns;               // blocks per row: 5 (triangles) or 7 (tetrahedra)
-  // matrix-free products of the FP64 PCG (tetrahedra, dfdg_params.matrix_free): S p is formed
-  // element by element as sum_T C_T W_T C_T^T p from the element data and the reference
-  // tables below, through the per-element face contributions mfq [4][NF][T]; null = BSR
+  // matrix-free products of the FP64 PCG (tetrahedra, see mf_products): S p is formed element
+  // by element as sum_T C_T W_T C_T^T p from the element data and the reference tables below,
+  // through the face contributions mfq [E][2][NF] of the faces' L and R sides; null = BSR
   double* mfq;
-  const double* mfCh; const double* mfDh; const double* mfQf;
+  const double* mfcond; const double* mfQf;
   int mfK;
   const int* cols;      // [5][E]
   const double* vals;   // [5][NF][NF][E]

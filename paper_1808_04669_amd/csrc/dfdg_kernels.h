@@ -133,10 +133,13 @@ hipError_t launch_eval3(int K, int npts, const DevGeo& g, const double* tab, con
                         hipStream_t s);
 hipError_t launch_diagnostics3(int K, const DevGeo& g, const DevTabs& tb, const double* U, double* partials,
                                double* res, hipStream_t s);
-// The PCG product p_new = z + beta p_old, Sp = S p_new and its (p, Sp) partials, matrix free
-// (A.mfq set): an element pass and a face pass (same role and arguments as launch_pcg_spmv).
+// The PCG product p_new = z + beta p_old, S p_new and its partials, matrix free (A.mfq set):
+// an element pass, and with form_Sp a face pass that writes Sp (same role and arguments as
+// launch_pcg_spmv); launch_mf_update3 is the Jacobi update that reads the sides of S p.
 hipError_t launch_mf_spmv3(int NF, const DevGeo& g, const DevBsr& A, const double* z, const double* p_old,
-                           double* p_new, double* Sp, const PcgBufs& pb, int it, hipStream_t s);
+                           double* p_new, double* Sp, const PcgBufs& pb, int it, bool form_Sp, hipStream_t s);
+hipError_t launch_mf_update3(int NF, bool bj, const DevGeo& g, const DevBsr& A, const double* p, double* x, double* r,
+                             double* z, const PcgBufs& pb, int it, hipStream_t s);
 // x_{.,0} -= (zdef, x_{.,0}) zdef (part: scratch for one partial per facet block).
 hipError_t launch_deflate(int NF, const DevGeo& g, double* x, double* part, hipStream_t s);
 hipError_t launch_gather_g(int NF, const DevGeo& g, const double* q, double* gv, const PcgBufs& pb, double rtol,
@@ -147,8 +150,10 @@ hipError_t launch_pcg_init(int NF, bool block_jacobi, const DevGeo& g, const Dev
 // Iteration it >= 1: stopping test on iteration it-1, beta, p_new = z + beta p_old, Sp = S p_new.
 // `it` selects the parity of the partial buffers (the kernels read the iteration count
 // itself from pb.sc, so a captured launch sequence can be replayed).
+// form_Sp = false: a matrix-free product leaves S p as its two sides, for launch_pcg_update's
+// Jacobi forms.
 hipError_t launch_pcg_spmv(int NF, const DevGeo& g, const DevBsr& A, const double* z, const double* p_old,
-                           double* p_new, double* Sp, const PcgBufs& pb, int it, hipStream_t s);
+                           double* p_new, double* Sp, const PcgBufs& pb, int it, hipStream_t s, bool form_Sp = true);
 // x += alpha p, r -= alpha Sp, z = M^{-1} r (pc: 0 Jacobi, 1 block Jacobi, 2 none).
 hipError_t launch_pcg_update(int NF, int pc, const DevGeo& g, const DevBsr& A, const double* p,
                              const double* Sp, double* x, double* r, double* z, const PcgBufs& pb, int it,

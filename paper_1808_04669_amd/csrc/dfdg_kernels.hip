@@ -2255,13 +2255,13 @@ hipError_t launch_pcg_init(int NF, bool bj, const DevGeo& g, const DevBsr& A, co
 
 template <typename V>
 static hipError_t spmv_any(int NF, const DevGeo& g, const DevBsr& A, const V* z, const V* p_old, V* p_new, V* Sp,
-                           const PcgBufs& pb, int it, hipStream_t s) {
+                           const PcgBufs& pb, int it, hipStream_t s, bool form_Sp = true) {
   const int G = g.fgrid;
   const double* prev = pb.rz[(it - 1) & 1];
   const double* prev2 = pb.rz[it & 1];
   if constexpr (sizeof(V) == 8) {
     if (A.mfq) return launch_mf_spmv3(NF, g, A, (const double*)z, (const double*)p_old, (double*)p_new, (double*)Sp, pb,
-                                      it, s);
+                                      it, form_Sp, s);
   }
   if (sizeof(V) == 4 && A.ns != kSlots) return hipErrorInvalidValue;  // FP32 copies: triangles only
   DFDG_DISPATCH_NFS(NF, A.ns, DFDG_LAUNCH_TIMED((k_pcg_spmv<NN, SS, V, V>), dim3(G), dim3(kBlk), 0, s, g, A, z, p_old,
@@ -2289,11 +2289,12 @@ static hipError_t update_any(int NF, int pc, const DevGeo& g, const DevBsr& A, c
 }
 
 hipError_t launch_pcg_spmv(int NF, const DevGeo& g, const DevBsr& A, const double* z, const double* p_old,
-                           double* p_new, double* Sp, const PcgBufs& pb, int it, hipStream_t s) {
-  return spmv_any<double>(NF, g, A, z, p_old, p_new, Sp, pb, it, s);
+                           double* p_new, double* Sp, const PcgBufs& pb, int it, hipStream_t s, bool form_Sp) {
+  return spmv_any<double>(NF, g, A, z, p_old, p_new, Sp, pb, it, s, form_Sp);
 }
 hipError_t launch_pcg_update(int NF, int pc, const DevGeo& g, const DevBsr& A, const double* p, const double* Sp,
                              double* x, double* r, double* z, const PcgBufs& pb, int it, hipStream_t s) {
+  if (A.mfq && pc != 2) return launch_mf_update3(NF, pc == 1, g, A, p, x, r, z, pb, it, s);
   return update_any<double>(NF, pc, g, A, p, Sp, x, r, z, pb, it, s);
 }
 hipError_t launch_pcg32_spmv(int NF, const DevGeo& g, const DevBsr& A, const float* z, const float* p_old,

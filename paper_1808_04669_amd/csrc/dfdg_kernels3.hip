@@ -407,48 +407,125 @@ __global__ __launch_bounds__(kEBlk) void k_residual_vjp3(DevGeo g, DevTabs tb, c
 // ---------------------------------------------------------------------------------------
 // a4 / a6: element condensation and recovery (eq. (FE3), orthonormal basis: M_T = I)
 // ---------------------------------------------------------------------------------------
+// The reference matrices of the condensation, DevTabs::cond: the face moments [4][P][NF] and
+// the divergence moments [P][NP][3], so that what one basis function i needs lies together.
+// They are read as scalars, a group of a few i at a time.  Left to itself the compiler loads
+// all 720 SGPRs' worth once (K = 2) and keeps them in the lanes of vector registers: 4200
+// v_readlane of 6600 instructions and 50 KB of code in k_mf_apply3, which every launch fetches
+// again.  From LDS the same values took as long, in more registers.  The face basis
+// permutations Qf differ from lane to lane: LDS (as loads from memory they were 288 a thread).
+template <int K>
+struct CondTabs3 {
+  static constexpr int P = nP3(K), NF = nF3(K), NP = nPp3(K);
+  double Qf[6][NF][NF];
+};
+template <int K>
+__device__ inline void stage_cond3(CondTabs3<K>& s, const double* __restrict__ Qf) {  // (the caller synchronises)
+  double* d = &s.Qf[0][0][0];
+  for (int i = threadIdx.x; i < 6 * nF3(K) * nF3(K); i += blockDim.x) d[i] = Qf[i];
+}
+// A new scalar pointer to the same table: what is read through it is loaded again.
+__device__ inline const double* again(const double* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+// Ends a group of table reads, after N basis functions.
+template <int N>
+__device__ inline void table_group(int i) {
+  if (i % N == N - 1) __builtin_amdgcn_sched_barrier(0);
+}
+
 // y <- W_T y = y - D_T^T (D_T D_T^T)^{-1} D_T y, D_T = sum_a Jinv[a][c] Dh[a]
 template <int K>
 __device__ inline void apply_W3(double (&y)[3][nP3(K)], const double (&Ji)[3][3], const double* __restrict__ G, int T,
-                                int t, const double* __restrict__ Dh) {
-  constexpr int P = nP3(K), NP = nPp3(K);
-  const auto Dc = cst(Dh);
+                                int t, const double* cond) {
+  constexpr int P = nP3(K), NP = nPp3(K), kD = 4 * P * nF3(K);
+  auto D = cst(again(cond) + kD);
   double d[NP];
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    double s = 0;
+  for (int j = 0; j < NP; ++j) d[j] = 0;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double a[3] = {0, 0, 0};
+  for (int i = 0; i < P; ++i) {  // the reference components w = Jinv y serve every j
+    double w[3];
 #pragma unroll
-      for (int i = 0; i < P; ++i)
+    for (int e = 0; e < 3; ++e) w[e] = Ji[e][0] * y[0][i] + Ji[e][1] * y[1][i] + Ji[e][2] * y[2][i];
 #pragma unroll
-        for (int e = 0; e < 3; ++e) a[e] += Dc[(e * NP + j) * P + i] * y[c][i];
-      s += Ji[0][c] * a[0] + Ji[1][c] * a[1] + Ji[2][c] * a[2];
-    }
-    d[j] = s;
+    for (int j = 0; j < NP; ++j)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) d[j] += D[(i * NP + j) * 3 + e] * w[e];
+    table_group<3>(i);
   }
-  double e[NP];
+  D = cst(again(cond) + kD);
+  double x[NP];
 #pragma unroll
-  for (int j = 0; j < NP; ++j) e[j] = 0;
+  for (int j = 0; j < NP; ++j) x[j] = 0;
 #pragma unroll
   for (int j = 0, p = 0; j < NP; ++j)
 #pragma unroll
     for (int l = 0; l <= j; ++l, ++p) {
       const double gv = G[(size_t)p * T + t];
-      e[j] += gv * d[l];
-      if (l != j) e[l] += gv * d[j];
+      x[j] += gv * d[l];
+      if (l != j) x[l] += gv * d[j];
     }
 #pragma unroll
-  for (int c = 0; c < 3; ++c)
+  for (int i = 0; i < P; ++i) {
+    double w[3];
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
-      double s = 0;
+    for (int e = 0; e < 3; ++e) {
+      w[e] = 0;
 #pragma unroll
-      for (int j = 0; j < NP; ++j)
-        s += (Ji[0][c] * Dc[(0 * NP + j) * P + i] + Ji[1][c] * Dc[(1 * NP + j) * P + i] + Ji[2][c] * Dc[(2 * NP + j) * P + i]) * e[j];
-      y[c][i] -= s;
+      for (int j = 0; j < NP; ++j) w[e] += D[(i * NP + j) * 3 + e] * x[j];
     }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) y[c][i] -= Ji[0][c] * w[0] + Ji[1][c] * w[1] + Ji[2][c] * w[2];
+    table_group<3>(i);
+  }
+}
+
+// m = the face moments of y (n: the normal times sqrt(2|F| / det J)), and y += their transpose.
+template <int K>
+__device__ inline void face_rows3(const double (&y)[3][nP3(K)], const double (&n)[3], const double* cond, int f,
+                                  double (&m)[nF3(K)]) {
+  constexpr int P = nP3(K), NF = nF3(K);
+  const auto Ch = cst(again(cond) + f * P * NF);
+#pragma unroll
+  for (int a = 0; a < NF; ++a) m[a] = 0;
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const double yn = n[0] * y[0][i] + n[1] * y[1][i] + n[2] * y[2][i];
+#pragma unroll
+    for (int a = 0; a < NF; ++a) m[a] += Ch[i * NF + a] * yn;
+    table_group<3>(i);
+  }
+}
+template <int K>
+__device__ inline void face_add3(double (&y)[3][nP3(K)], const double (&n)[3], const double* cond, int f,
+                                 const double (&m)[nF3(K)]) {
+  constexpr int P = nP3(K), NF = nF3(K);
+  const auto Ch = cst(again(cond) + f * P * NF);
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    double s = 0;
+#pragma unroll
+    for (int a = 0; a < NF; ++a) s += m[a] * Ch[i * NF + a];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) y[c][i] += n[c] * s;
+    table_group<3>(i);
+  }
+}
+// m <- Q m (R side to L side) or Q^T m.
+template <int K, bool TR>
+__device__ inline void face_map3(const double (&Q)[nF3(K)][nF3(K)], double (&m)[nF3(K)]) {
+  constexpr int NF = nF3(K);
+  double w[NF];
+#pragma unroll
+  for (int a = 0; a < NF; ++a) {
+    w[a] = 0;
+#pragma unroll
+    for (int b = 0; b < NF; ++b) w[a] += (TR ? Q[b][a] : Q[a][b]) * m[b];
+  }
+#pragma unroll
+  for (int a = 0; a < NF; ++a) m[a] = w[a];
 }
 
 // q[4][NF][T] = C_T W_T F_T per element and local face, in the L side's face basis (the
@@ -457,6 +534,9 @@ template <int K>
 __global__ __launch_bounds__(kEBlk) void k_cond_rhs3(DevGeo g, DevTabs tb, const double* __restrict__ F,
                                                      double* __restrict__ q) {
   constexpr int P = nP3(K), NF = nF3(K);
+  __shared__ __align__(16) CondTabs3<K> s;
+  stage_cond3<K>(s, tb.Qf);
+  __syncthreads();
   const int T = g.T;
   const int t = xcd_block() * blockDim.x + threadIdx.x;
   if (t >= T) return;
@@ -467,34 +547,16 @@ __global__ __launch_bounds__(kEBlk) void k_cond_rhs3(DevGeo g, DevTabs tb, const
     for (int i = 0; i < P; ++i) y[c][i] = F[(size_t)(c * P + i) * T + t];
   double Ji[3][3];
   load_Jinv3(g, t, Ji);
-  apply_W3<K>(y, Ji, g.G, T, t, tb.Dh);
+  apply_W3<K>(y, Ji, g.G, T, t, tb.cond);
 #pragma unroll 1
   for (int f = 0; f < 4; ++f) {
     const size_t idx = (size_t)f * T + t;
     const double sc = g.sF[idx];
-    const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
+    const double n[3] = {sc * g.nx[idx], sc * g.ny[idx], sc * g.nz[idx]};
     const int code = g.code[idx];
     double m[NF];
-#pragma unroll
-    for (int mm = 0; mm < NF; ++mm) {
-      double s = 0;
-#pragma unroll
-      for (int i = 0; i < P; ++i) s += cst(tb.Ch)[(f * NF + mm) * P + i] * (n[0] * y[0][i] + n[1] * y[1][i] + n[2] * y[2][i]);
-      m[mm] = sc * s;
-    }
-    if ((code >> 5) & 1) {
-      const double* Q = tb.Qf + ((code >> 2) & 7) * NF * NF;
-      double o[NF];
-#pragma unroll
-      for (int a = 0; a < NF; ++a) {
-        double s = 0;
-#pragma unroll
-        for (int b = 0; b < NF; ++b) s += Q[a * NF + b] * m[b];
-        o[a] = s;
-      }
-#pragma unroll
-      for (int a = 0; a < NF; ++a) m[a] = o[a];
-    }
+    face_rows3<K>(y, n, tb.cond, f, m);
+    if ((code >> 5) & 1) face_map3<K, false>(s.Qf[(code >> 2) & 7], m);
 #pragma unroll
     for (int mm = 0; mm < NF; ++mm) q[(size_t)(f * NF + mm) * T + t] = m[mm];
   }
@@ -507,6 +569,9 @@ __global__ __launch_bounds__(kEBlk) void k_recover3(DevGeo g, DevTabs tb, const 
                                                     double ca, const double* __restrict__ Un, double cb,
                                                     const double* __restrict__ Us, double dt) {
   constexpr int P = nP3(K), NF = nF3(K);
+  __shared__ __align__(16) CondTabs3<K> s;
+  stage_cond3<K>(s, tb.Qf);
+  __syncthreads();
   const int T = g.T;
   const int t = xcd_block() * blockDim.x + threadIdx.x;
   if (t >= T) return;
@@ -523,34 +588,14 @@ __global__ __launch_bounds__(kEBlk) void k_recover3(DevGeo g, DevTabs tb, const 
     double lm[NF];
 #pragma unroll
     for (int a = 0; a < NF; ++a) lm[a] = lam[(size_t)Fc * NF + a];
-    if ((code >> 5) & 1) {  // own face coefficients: Qf^T times the L side's
-      const double* Q = tb.Qf + ((code >> 2) & 7) * NF * NF;
-      double o[NF];
-#pragma unroll
-      for (int b = 0; b < NF; ++b) {
-        double s = 0;
-#pragma unroll
-        for (int a = 0; a < NF; ++a) s += Q[a * NF + b] * lm[a];
-        o[b] = s;
-      }
-#pragma unroll
-      for (int b = 0; b < NF; ++b) lm[b] = o[b];
-    }
-    const double sc = g.sF[idx];
-    const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      double s = 0;
-#pragma unroll
-      for (int mm = 0; mm < NF; ++mm) s += lm[mm] * cst(tb.Ch)[(f * NF + mm) * P + i];
-      s *= sc;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) y[c][i] -= n[c] * s;
-    }
+    if ((code >> 5) & 1) face_map3<K, true>(s.Qf[(code >> 2) & 7], lm);  // own face coefficients
+    const double sc = -g.sF[idx];
+    const double n[3] = {sc * g.nx[idx], sc * g.ny[idx], sc * g.nz[idx]};
+    face_add3<K>(y, n, tb.cond, f, lm);
   }
   double Ji[3][3];
   load_Jinv3(g, t, Ji);
-  apply_W3<K>(y, Ji, g.G, T, t, tb.Dh);
+  apply_W3<K>(y, Ji, g.G, T, t, tb.cond);
 #pragma unroll
   for (int c = 0; c < 3; ++c)
 #pragma unroll
@@ -566,185 +611,270 @@ __global__ __launch_bounds__(kEBlk) void k_recover3(DevGeo g, DevTabs tb, const 
 // condensed), in the PCG iteration it (read from the scalars): beta and the stopping test
 // from the partials of the previous updates, exactly as the BSR kernel forms them.
 // ---------------------------------------------------------------------------------------
-// beta of iteration it from the (r, z) partials of iterations it-1 and it-2 (every block of
-// every kernel that calls this sums them in the same order: the same bits); false when the
-// run has stopped (block 0 records the stopping test for the host and later kernels)
-__device__ inline bool pcg_beta(PcgScalars* sc, const double* __restrict__ rz_prev,
-                                const double* __restrict__ rz_prev2, int G, bool test, double& beta) {
-  if (sc->done != PCG_RUNNING) return false;
-  const int it = sc->it;
-  double t1[2];
-  block_sum_partials<2>(rz_prev, G, t1);
-  beta = 0;
-  if (it >= 2) {
-    double t2[2];
-    block_sum_partials<2>(rz_prev2, G, t2);
-    beta = t1[0] / t2[0];
-  }
+// Element pass: p = z + beta p_old at the element's four faces (the L side's face basis,
+// mapped to the own one on R faces), y = W_T C_T^T p, and the face contributions C_T y
+// (mapped back) into A.mfq [E][side][NF], where the two sides of a face lie together for the
+// next kernel.  The L side writes p.  The element's share of (p, S p) is |y|^2 (W_T is an
+// orthogonal projector), that of (z, S p) comes from its contributions; one partial of each
+// per block, over a grid-stride loop on the facet kernels' grid.
+//
+// All indices, normals and face values are loaded ahead of the arithmetic, at two waves per
+// SIMD (rolled over the faces, three waves: 70 us against 67 at 32^3, and 44 against 36 at
+// K = 1).  Bound by the latency of that chain and by the 312 B of geometry and 576 B of face
+// values an element; 1500 FP64 instructions are 8 us of it.  With the face pass 136 -> 67 us
+// at 32^3 BDM_2 (16^3: 43 -> 26, 24^3: 41).
+template <int K>
+__global__ __launch_bounds__(kBlk) void k_mf_apply3(DevGeo g, DevBsr A, const double* __restrict__ z,
+                                                    const double* __restrict__ p_old, double* __restrict__ p_new,
+                                                    PcgScalars* sc, const double* __restrict__ rz_prev,
+                                                    const double* __restrict__ rz_prev2, double* __restrict__ pq) {
+  constexpr int P = nP3(K), NF = nF3(K);
+  if (sc->done != PCG_RUNNING) return;
+  __shared__ __align__(16) CondTabs3<K> s;
+  const int G = gridDim.x, it = sc->it, T = g.T;
+  PartLoad<2> q1, q2;
+  partials_load<2>(rz_prev, G, true, q1);
+  partials_load<2>(rz_prev2, G, it >= 2, q2);
+  stage_cond3<K>(s, A.mfQf);  // visible after the sums' synchronisation
+  // the grid is the facet kernels'; the blocks with elements are spread over all XCDs
+  const int nb = min(G, (T + kBlk - 1) / kBlk);
+  const int t0 = (int)blockIdx.x < nb ? xcd_block(nb) * kBlk + threadIdx.x : T;
+  double t1[2], t2[2], beta = 0;
+  partials_sum<2>(q1, G, t1);
+  partials_sum<2>(q2, G, t2);
+  if (it >= 2) beta = t1[0] / t2[0];
   int status = PCG_RUNNING;
   if (!isfinite(t1[0]) || !isfinite(t1[1]) || !isfinite(beta)) status = PCG_NONFINITE;
   else if (t1[1] <= sc->tol2) status = PCG_CONVERGED;
   else if (it - 1 >= sc->maxit) status = PCG_MAXIT;
-  if (test && blockIdx.x == 0 && threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     sc->iters = it - 1;
     sc->rr = t1[1];
     sc->rz = t1[0];
     if (it == 1) sc->rr0 = t1[1];
     if (status != PCG_RUNNING) sc->done = status;
   }
-  return status == PCG_RUNNING;
-}
-
-// Element pass: p = z + beta p_old at the element's four faces (the L side's face basis,
-// mapped to the own one on R faces), y = W_T C_T^T p, and the face contributions C_T y
-// (mapped back) into A.mfq.
-template <int K>
-__global__ __launch_bounds__(kBlk) void k_mf_apply3(DevGeo g, DevBsr A, const double* __restrict__ z,
-                                                    const double* __restrict__ p_old, PcgScalars* sc,
-                                                    const double* __restrict__ rz_prev,
-                                                    const double* __restrict__ rz_prev2, int G) {
-  constexpr int P = nP3(K), NF = nF3(K);
-  double beta;
-  if (!pcg_beta(sc, rz_prev, rz_prev2, G, true, beta)) return;
-  const int T = g.T;
-  const int t = xcd_block() * blockDim.x + threadIdx.x;
-  if (t >= T) return;
-  const auto Ch = cst(A.mfCh);
-  double y[3][P];
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-#pragma unroll
-    for (int i = 0; i < P; ++i) y[c][i] = 0;
-#pragma unroll 1
-  for (int f = 0; f < 4; ++f) {
-    const size_t idx = (size_t)f * T + t;
-    const int Fc = g.efacet[idx];
-    const int code = g.code[idx];
-    double lm[NF];
-#pragma unroll
-    for (int a = 0; a < NF; ++a) lm[a] = z[(size_t)Fc * NF + a] + beta * p_old[(size_t)Fc * NF + a];
-    if ((code >> 5) & 1) {
-      const double* Q = A.mfQf + ((code >> 2) & 7) * NF * NF;
-      double o[NF];
-#pragma unroll
-      for (int b = 0; b < NF; ++b) {
-        double s = 0;
-#pragma unroll
-        for (int a = 0; a < NF; ++a) s += Q[a * NF + b] * lm[a];
-        o[b] = s;
-      }
-#pragma unroll
-      for (int b = 0; b < NF; ++b) lm[b] = o[b];
-    }
-    const double sc2 = g.sF[idx];
-    const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      double s = 0;
-#pragma unroll
-      for (int mm = 0; mm < NF; ++mm) s += lm[mm] * Ch[(f * NF + mm) * P + i];
-      s *= sc2;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) y[c][i] += n[c] * s;
-    }
-  }
-  double Ji[3][3];
-  load_Jinv3(g, t, Ji);
-  apply_W3<K>(y, Ji, g.G, T, t, A.mfDh);
-#pragma unroll 1
-  for (int f = 0; f < 4; ++f) {
-    const size_t idx = (size_t)f * T + t;
-    const double sc2 = g.sF[idx];
-    const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
-    const int code = g.code[idx];
-    double m[NF];
-#pragma unroll
-    for (int mm = 0; mm < NF; ++mm) {
-      double s = 0;
-#pragma unroll
-      for (int i = 0; i < P; ++i) s += Ch[(f * NF + mm) * P + i] * (n[0] * y[0][i] + n[1] * y[1][i] + n[2] * y[2][i]);
-      m[mm] = sc2 * s;
-    }
-    if ((code >> 5) & 1) {
-      const double* Q = A.mfQf + ((code >> 2) & 7) * NF * NF;
-      double o[NF];
-#pragma unroll
-      for (int a = 0; a < NF; ++a) {
-        double s = 0;
-#pragma unroll
-        for (int b = 0; b < NF; ++b) s += Q[a * NF + b] * m[b];
-        o[a] = s;
-      }
-#pragma unroll
-      for (int a = 0; a < NF; ++a) m[a] = o[a];
-    }
-#pragma unroll
-    for (int mm = 0; mm < NF; ++mm) A.mfq[(size_t)(f * NF + mm) * T + t] = m[mm];
-  }
-}
-
-// Face pass: S p = the two sides' contributions, p_new = z + beta p_old, (p_new, S p) and
-// (z, S p) partials (z the kernel vector; grid-stride over the face rows, one partial per
-// block).
-template <int NF>
-__global__ __launch_bounds__(kBlk) void k_mf_gather(DevGeo g, DevBsr A, const double* __restrict__ z,
-                                                    const double* __restrict__ p_old, double* __restrict__ p_new,
-                                                    double* __restrict__ Sp, PcgScalars* sc,
-                                                    const double* __restrict__ rz_prev,
-                                                    const double* __restrict__ rz_prev2, double* __restrict__ pq) {
-  double beta;
-  if (!pcg_beta(sc, rz_prev, rz_prev2, gridDim.x, false, beta)) return;
-  const int T = g.T;
+  if (status != PCG_RUNNING) return;
   double v[2] = {0, 0};
-  for (int F = xcd_block() * blockDim.x + threadIdx.x; F < g.E; F += gridDim.x * blockDim.x) {
-    const int a = g.qL[F], b = g.qR[F];
+  for (int t = t0; t < T; t += nb * kBlk) {
+    // indices, normals and the kernel vector's values of all faces first: the face values
+    // are one round trip behind them
+    int code[4], Fc[4];
+    double zd[4], n[4][3];
 #pragma unroll
-    for (int m = 0; m < NF; ++m) {
-      const size_t o = (size_t)F * NF + m;
-      // b = -1: a closed boundary face, one side; b = -2: an outflow face, whose row of S
-      // is the identity (no multiplier) and whose element contributions vanish
-      const double y = b == -2 ? z[o] + beta * p_old[o]
-                               : A.mfq[a + (size_t)m * T] + (b >= 0 ? A.mfq[b + (size_t)m * T] : 0.0);
-      const double pn = z[o] + beta * p_old[o];
-      p_new[o] = pn;
-      Sp[o] = y;
-      v[0] += pn * y;
-      if (m == 0) v[1] += g.zdef[F] * y;
+    for (int f = 0; f < 4; ++f) {
+      const size_t idx = (size_t)f * T + t;
+      code[f] = g.code[idx];
+      Fc[f] = g.efacet[idx];
+    }
+    double lz[4][NF];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const size_t idx = (size_t)f * T + t;
+      const double sc2 = g.sF[idx];
+      n[f][0] = sc2 * g.nx[idx];
+      n[f][1] = sc2 * g.ny[idx];
+      n[f][2] = sc2 * g.nz[idx];
+      zd[f] = g.zdef[Fc[f]];
+    }
+    double y[3][P];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int i = 0; i < P; ++i) y[c][i] = 0;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const size_t o = (size_t)Fc[f] * NF;
+#pragma unroll
+      for (int a = 0; a < NF; ++a) lz[f][a] = z[o + a] + beta * p_old[o + a];
+    }
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const size_t o = (size_t)Fc[f] * NF;
+      double (&lm)[NF] = lz[f];
+      if ((code[f] >> 5) & 1) {
+        face_map3<K, true>(s.Qf[(code[f] >> 2) & 7], lm);
+      } else {
+#pragma unroll
+        for (int a = 0; a < NF; ++a) p_new[o + a] = lm[a];
+        if ((code[f] >> 6) & 1)  // an outflow face: its row of S is the identity
+#pragma unroll
+          for (int a = 0; a < NF; ++a) v[0] += lm[a] * lm[a];
+      }
+      face_add3<K>(y, n[f], A.mfcond, f, lm);
+    }
+    double Ji[3][3];
+    load_Jinv3(g, t, Ji);
+    apply_W3<K>(y, Ji, g.G, T, t, A.mfcond);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int i = 0; i < P; ++i) v[0] += y[c][i] * y[c][i];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const bool R = (code[f] >> 5) & 1;
+      double m[NF];
+      face_rows3<K>(y, n[f], A.mfcond, f, m);
+      if (R) {
+        face_map3<K, false>(s.Qf[(code[f] >> 2) & 7], m);
+      } else if ((code[f] >> 6) & 1) {
+        const size_t o = (size_t)Fc[f] * NF;
+#pragma unroll
+        for (int a = 0; a < NF; ++a) m[a] = z[o + a] + beta * p_old[o + a];
+      }
+      double* q = A.mfq + ((size_t)Fc[f] * 2 + (R ? 1 : 0)) * NF;
+#pragma unroll
+      for (int mm = 0; mm < NF; ++mm) q[mm] = m[mm];
+      v[1] += zd[f] * m[0];
     }
   }
   block_write_partial<2>(v, pq);
 }
 
+// Sums of the two sides' contributions of entry i (mode i % NF of face i / NF), and of entries
+// i and i + 1 (NF even, i even); a boundary face has one side, its other half stays zero.
+template <int NF>
+__device__ inline double mf_sp(const double* __restrict__ q, long i) {
+  const long o = i + (i / NF) * NF;
+  return q[o] + q[o + NF];
+}
+template <int NF>
+__device__ inline double2 mf_sp2(const double* __restrict__ q, long i) {
+  const long o = i + (i / NF) * NF;
+  const double2 a = *(const double2*)(q + o), b = *(const double2*)(q + o + NF);
+  return {a.x + b.x, a.y + b.y};
+}
+
+// Sp = S p for the multigrid iterations, whose next kernel gathers it.
+template <int NF>
+__global__ __launch_bounds__(kBlk) void k_mf_sum(long n, const double* __restrict__ q, double* __restrict__ Sp,
+                                                 const PcgScalars* sc) {
+  if (sc->done != PCG_RUNNING) return;
+  for (long u = (long)xcd_block() * kBlk + threadIdx.x; NF * u < n; u += (long)gridDim.x * kBlk) {
+    const long i = NF * u;
+    if constexpr (NF % 2 == 0) {
+#pragma unroll
+      for (int a = 0; a < NF; a += 2) *(double2*)(Sp + i + a) = mf_sp2<NF>(q, i + a);
+    } else {
+#pragma unroll
+      for (int a = 0; a < NF; ++a) Sp[i + a] = mf_sp<NF>(q, i + a);
+    }
+  }
+}
+
+// The PCG update of point- and facet-block-Jacobi iterations (k_pcg_update) with S p summed
+// from the two sides on the way: it is neither written nor read as a vector.
+template <int NF, bool BJ>
+__global__ __launch_bounds__(kBlk) void k_mf_update(DevGeo g, DevBsr A, const double* __restrict__ p,
+                                                    double* __restrict__ x, double* __restrict__ r,
+                                                    double* __restrict__ z, PcgScalars* sc,
+                                                    const double* __restrict__ rz_prev,
+                                                    const double* __restrict__ pq, double* __restrict__ rz_out) {
+  if (sc->done != PCG_RUNNING) return;
+  const int G = gridDim.x;
+  double t1[2], t2[2];
+  block_sum_partials<2>(rz_prev, G, t1);
+  block_sum_partials<2>(pq, G, t2);
+  int status = PCG_RUNNING;
+  if (!isfinite(t2[0])) status = PCG_NONFINITE;
+  else if (!(t2[0] > 0)) status = PCG_BREAKDOWN;
+  if (status != PCG_RUNNING) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->done = status;
+    return;
+  }
+  const double alpha = t1[0] / t2[0], dz = t2[1];
+  const double* __restrict__ q = A.mfq;
+  double v[2] = {0, 0};
+  if constexpr (!BJ && NF % 2 == 0) {
+    const long n2 = (long)g.E * NF / 2;
+    for (long u = (long)xcd_block() * kBlk + threadIdx.x; u < n2; u += (long)G * kBlk) {
+      const long i = 2 * u;
+      const double2 s = mf_sp2<NF>(q, i), pv = ((const double2*)p)[u], dv = ((const double2*)A.dinv)[u];
+      double2 xv = ((double2*)x)[u], rv = ((double2*)r)[u], zv;
+      xv.x += alpha * pv.x;
+      xv.y += alpha * pv.y;
+      const double s0 = i % NF == 0 ? s.x - dz * g.zdef[i / NF] : s.x;
+      rv.x -= alpha * s0;
+      rv.y -= alpha * s.y;
+      zv.x = dv.x * rv.x;
+      zv.y = dv.y * rv.y;
+      ((double2*)x)[u] = xv;
+      ((double2*)r)[u] = rv;
+      ((double2*)z)[u] = zv;
+      v[0] += rv.x * zv.x + rv.y * zv.y;
+      v[1] += rv.x * rv.x + rv.y * rv.y;
+    }
+  } else {
+    for (int F = xcd_block() * kBlk + threadIdx.x; F < g.E; F += G * kBlk) {
+      double rr[NF], zz[NF];
+#pragma unroll
+      for (int a = 0; a < NF; ++a) {
+        const long o = (long)F * NF + a;
+        double s = mf_sp<NF>(q, o);
+        if (a == 0) s -= dz * g.zdef[F];
+        x[o] += alpha * p[o];
+        rr[a] = r[o] - alpha * s;
+        r[o] = rr[a];
+      }
+#pragma unroll
+      for (int a = 0; a < NF; ++a) {
+        if constexpr (BJ) {
+          zz[a] = 0;
+#pragma unroll
+          for (int b = 0; b < NF; ++b) zz[a] += A.binv[((size_t)F * NF + a) * NF + b] * rr[b];
+        } else {
+          zz[a] = A.dinv[(size_t)F * NF + a] * rr[a];
+        }
+        z[(size_t)F * NF + a] = zz[a];
+        v[0] += rr[a] * zz[a];
+        v[1] += rr[a] * rr[a];
+      }
+    }
+  }
+  block_write_partial<2>(v, rz_out);
+  if (blockIdx.x == 0 && threadIdx.x == 0) sc->it = sc->it + 1;
+}
+
+// A launch that carries the start / stop events of the timing entry point where they are set.
+#define DFDG_LAUNCH_EV(E0, E1, KER, GRID, S, ...)                                          \
+  do {                                                                                    \
+    if ((E0) || (E1)) hipExtLaunchKernelGGL(KER, GRID, dim3(kBlk), 0, S, E0, E1, 0, __VA_ARGS__); \
+    else hipLaunchKernelGGL(KER, GRID, dim3(kBlk), 0, S, __VA_ARGS__);                    \
+  } while (0)
+
 hipError_t launch_mf_spmv3(int NF, const DevGeo& g, const DevBsr& A, const double* z, const double* p_old,
-                           double* p_new, double* Sp, const PcgBufs& pb, int it, hipStream_t s) {
-  const int G = g.fgrid;
+                           double* p_new, double* Sp, const PcgBufs& pb, int it, bool form_Sp, hipStream_t s) {
   const double* prev = pb.rz[(it - 1) & 1];
   const double* prev2 = pb.rz[it & 1];
   hipEvent_t e0, e1;  // kernel timing: start of the element pass to the end of the face pass
   get_dispatch_events(&e0, &e1);
-  const dim3 eg(nblk(g.T, kBlk)), blk(kBlk);
-  switch (A.mfK) {
-    case 1:
-      if (e0) hipExtLaunchKernelGGL((k_mf_apply3<1>), eg, blk, 0, s, e0, nullptr, 0, g, A, z, p_old, pb.sc, prev, prev2, G);
-      else hipLaunchKernelGGL((k_mf_apply3<1>), eg, blk, 0, s, g, A, z, p_old, pb.sc, prev, prev2, G);
-      break;
-    case 2:
-      if (e0) hipExtLaunchKernelGGL((k_mf_apply3<2>), eg, blk, 0, s, e0, nullptr, 0, g, A, z, p_old, pb.sc, prev, prev2, G);
-      else hipLaunchKernelGGL((k_mf_apply3<2>), eg, blk, 0, s, g, A, z, p_old, pb.sc, prev, prev2, G);
-      break;
-    default: return hipErrorInvalidValue;
+  const dim3 gr(g.fgrid);
+  const hipEvent_t last = form_Sp ? nullptr : e1;
+  const long n = (long)g.E * NF;
+  const double* q = A.mfq;
+  const PcgScalars* csc = pb.sc;
+  if (A.mfK == 1 && NF == 3) {
+    DFDG_LAUNCH_EV(e0, last, (k_mf_apply3<1>), gr, s, g, A, z, p_old, p_new, pb.sc, prev, prev2, pb.pq);
+    if (form_Sp) DFDG_LAUNCH_EV((hipEvent_t)nullptr, e1, (k_mf_sum<3>), gr, s, n, q, Sp, csc);
+  } else if (A.mfK == 2 && NF == 6) {
+    DFDG_LAUNCH_EV(e0, last, (k_mf_apply3<2>), gr, s, g, A, z, p_old, p_new, pb.sc, prev, prev2, pb.pq);
+    if (form_Sp) DFDG_LAUNCH_EV((hipEvent_t)nullptr, e1, (k_mf_sum<6>), gr, s, n, q, Sp, csc);
+  } else {
+    return hipErrorInvalidValue;
   }
-  switch (NF) {
-    case 3:
-      if (e1) hipExtLaunchKernelGGL((k_mf_gather<3>), dim3(G), blk, 0, s, nullptr, e1, 0, g, A, z, p_old, p_new, Sp, pb.sc, prev, prev2, pb.pq);
-      else hipLaunchKernelGGL((k_mf_gather<3>), dim3(G), blk, 0, s, g, A, z, p_old, p_new, Sp, pb.sc, prev, prev2, pb.pq);
-      break;
-    case 6:
-      if (e1) hipExtLaunchKernelGGL((k_mf_gather<6>), dim3(G), blk, 0, s, nullptr, e1, 0, g, A, z, p_old, p_new, Sp, pb.sc, prev, prev2, pb.pq);
-      else hipLaunchKernelGGL((k_mf_gather<6>), dim3(G), blk, 0, s, g, A, z, p_old, p_new, Sp, pb.sc, prev, prev2, pb.pq);
-      break;
-    default: return hipErrorInvalidValue;
-  }
+  return hipGetLastError();
+}
+
+hipError_t launch_mf_update3(int NF, bool bj, const DevGeo& g, const DevBsr& A, const double* p, double* x, double* r,
+                             double* z, const PcgBufs& pb, int it, hipStream_t s) {
+  const dim3 gr(g.fgrid), bl(kBlk);
+  const double *prev = pb.rz[(it - 1) & 1], *pq = pb.pq;
+  double* out = pb.rz[it & 1];
+  if (NF == 3 && bj) hipLaunchKernelGGL((k_mf_update<3, true>), gr, bl, 0, s, g, A, p, x, r, z, pb.sc, prev, pq, out);
+  else if (NF == 3) hipLaunchKernelGGL((k_mf_update<3, false>), gr, bl, 0, s, g, A, p, x, r, z, pb.sc, prev, pq, out);
+  else if (NF == 6 && bj) hipLaunchKernelGGL((k_mf_update<6, true>), gr, bl, 0, s, g, A, p, x, r, z, pb.sc, prev, pq, out);
+  else if (NF == 6) hipLaunchKernelGGL((k_mf_update<6, false>), gr, bl, 0, s, g, A, p, x, r, z, pb.sc, prev, pq, out);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

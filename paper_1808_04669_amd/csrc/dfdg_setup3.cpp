@@ -354,6 +354,7 @@ void build_ref_tables3(int K, RefTables& t) {
   t.NP = nPp3(K);
   t.NF = nF3(K);
   const int P = t.P, NF = t.NF;
+  t.cond.clear();
   tet_rule(3 * K - 1, t.vq, t.vw);
   std::vector<double> fpts;
   sym_face_rule(K == 1 ? 4 : 6, fpts, t.fw);
@@ -441,6 +442,12 @@ void build_ref_tables3(int K, RefTables& t) {
       for (int m = 0; m < NF; ++m)
         for (int n = 0; n < NF; ++n) t.Qf[((size_t)pid * NF + m) * NF + n] += cw[r] * mu2[m] * mu[n];
     }
+  for (int f = 0; f < 4; ++f)
+    for (int i = 0; i < P; ++i)
+      for (int m = 0; m < NF; ++m) t.cond.push_back(t.Ch[((size_t)f * NF + m) * P + i]);
+  for (int i = 0; i < P; ++i)
+    for (int j = 0; j < t.NP; ++j)
+      for (int a = 0; a < 3; ++a) t.cond.push_back(t.Dh[((size_t)a * t.NP + j) * P + i]);
 }
 
 // ---------------------------------------------------------------------------------------
