@@ -435,6 +435,7 @@ static void carve(dfdg_ctx* ctx, char* base) {
   d.fpidx = tb.fpidx.empty() ? nullptr : c.take<int>(tb.fpidx.size());
   d.Qf = tb.Qf.empty() ? nullptr : c.take<double>(tb.Qf.size());
   d.cond = tb.cond.empty() ? nullptr : c.take<double>(tb.cond.size());
+  d.res = tb.res.empty() ? nullptr : c.take<double>(tb.res.size());
   DevBsr& A = ctx->A;
   A.ns = d3slots(ctx);
   A.cols = c.take<int>(h.cols.size());
@@ -699,6 +700,7 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
   if (ctx->tb.fpidx) HIPC(up(const_cast<int*>(ctx->tb.fpidx), tb.fpidx, s));
   if (ctx->tb.Qf) HIPC(up(const_cast<double*>(ctx->tb.Qf), tb.Qf, s));
   if (ctx->tb.cond) HIPC(up(const_cast<double*>(ctx->tb.cond), tb.cond, s));
+  if (ctx->tb.res) HIPC(up(const_cast<double*>(ctx->tb.res), tb.res, s));
   HIPC(up(const_cast<int*>(ctx->A.cols), h.cols, s));
   HIPC(up(const_cast<double*>(ctx->A.vals), h.vals, s));
   HIPC(up(const_cast<double*>(ctx->A.dinv), h.dinv, s));

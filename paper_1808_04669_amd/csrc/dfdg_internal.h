@@ -55,6 +55,24 @@ __host__ __device__ constexpr int nPairs(int NF, int NS) { return (NS * NF * NF 
 __host__ __device__ constexpr int facet_split(int NF, int NS) { return (NF % 2 == 0 && NS * NF * NF > 128) ? 2 : 1; }
 constexpr int kMaxEvalPts = 1024;
 
+// The modal tables of the tetrahedral residual in one array (offsets in doubles): traces
+// tr [4][P][NF] and reference gradients dg [4][P][NM][3] of the basis in face modes (NM =
+// dim P^{K-1}(F)), the modes' vertex permutations q [6][NF][NF], the modes at the face points
+// with the point's weight, and the basis at the volume points with the weighted modes of
+// P^{K-1}(T).
+struct ResLayout3 {
+  __host__ __device__ static constexpr int nm(int K) { return K * (K + 1) / 2; }
+  __host__ __device__ static constexpr int ptStride(int K) { return K == 1 ? 4 : 8; }
+  __host__ __device__ static constexpr int volStride(int K) { return K == 1 ? 6 : 14; }
+  __host__ __device__ static constexpr int tr(int) { return 0; }
+  __host__ __device__ static constexpr int dg(int K) { return tr(K) + 4 * nP3(K) * nF3(K); }
+  __host__ __device__ static constexpr int q(int K) { return dg(K) + 12 * nP3(K) * nm(K); }
+  __host__ __device__ static constexpr int lds(int K) { return q(K) + 6 * nF3(K) * nF3(K); }  // staged part
+  __host__ __device__ static constexpr int pt(int K) { return lds(K); }
+  __host__ __device__ static constexpr int vol(int K) { return pt(K) + nQF3(K) * ptStride(K); }
+  __host__ __device__ static constexpr int size(int K) { return vol(K) + nQV3(K) * volStride(K); }
+};
+
 // ---- reference tabulations (host, FP64) ---------------------------------------------
 struct RefTables {
   int dim = 2;
@@ -77,6 +95,7 @@ struct RefTables {
   std::vector<int> fpidx;            // [6][nqf]
   std::vector<double> Qf;            // [6][NF][NF]
   std::vector<double> cond;          // Ch as [4][P][NF], then Dh as [P][NP][3]
+  std::vector<double> res;           // ResLayout3
 };
 void gauss_legendre01(int n, std::vector<double>& x, std::vector<double>& w);
 void triangle_rule(int degree, std::vector<double>& pts, std::vector<double>& w);
@@ -132,6 +151,7 @@ struct DevTabs {
   const double* Zh;                    // triangles: RefTables::Zh
   const int* fpidx; const double* Qf;  // tetrahedra: face point and face basis permutations
   const double* cond;                  // tetrahedra: RefTables::cond
+  const double* res;                   // tetrahedra: RefTables::res
 };
 struct DevBsr {
   int ns;               // blocks per row: 5 (triangles) or 7 (tetrahedra)

@@ -43,6 +43,17 @@ __device__ inline void stage_tabs3(ResTabs3<K>& s, const DevTabs& tb) {
   __syncthreads();
 }
 
+// A new scalar pointer to the same table: what is read through it is loaded again.
+__device__ inline const double* again(const double* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+// Ends a group of table reads, after N basis functions.
+template <int N>
+__device__ inline void table_group(int i) {
+  if (i % N == N - 1) __builtin_amdgcn_sched_barrier(0);
+}
+
 __device__ inline void load_Jinv3(const DevGeo& g, int t, double (&Ji)[3][3]) {
 #pragma unroll
   for (int r = 0; r < 3; ++r)
@@ -57,68 +68,113 @@ __device__ inline void load_Jinv3(const DevGeo& g, int t, double (&Ji)[3][3]) {
 // own test function v
 //     -(un u_up - nu {grad u} n + nu sigma du) . v  +  (nu/2) (du (x) n) : grad v.
 // The volume term is int (u (x) u - nu grad u) : grad v.  VISC = false: nu = 0.
-// ---------------------------------------------------------------------------------------
+//
+// Everything polynomial is carried by modes.  A trace is in P^K of the face (NF modes), a normal
+// derivative in P^{K-1} (the first NM modes): the viscous face terms are products of modes,
+// and only the upwind flux goes to the face points, from the modes and back into them, so
+// that the basis (P functions) is applied once per face and side and not once per point.  A
+// neighbour's modes are permuted to the own face parameters.  In the volume grad v is in
+// P^{K-1}(T): the flux u (x) u is projected onto its NP modes point by point, the viscous flux
+// is formed in modes.  At K = 2 with viscosity 10700 FP64 multiply-adds an element in the
+// place of 24000 with values and gradients at every point.
+//
+// Bound: FP64 multiply-adds of two waves per SIMD (launch bounds: 256 registers, which the
+// accumulators and modes fill; with one wave 138 us in the place of 94) and the wait for the
+// neighbours' coefficients.  27^3 BDM_2 (118098 elements): 292 us before, 83-90 now; nu = 0:
+// 94 -> 66; 32^3 BDM_1: 78 -> 45; 8^3 BDM_2: 137 -> 49.
 template <int K, bool VISC>
-__global__ __launch_bounds__(kEBlk) void k_residual3(DevGeo g, DevTabs tb, const double* __restrict__ U,
+__global__ __launch_bounds__(kEBlk, 2) void k_residual3(DevGeo g, DevTabs tb, const double* __restrict__ U,
                                                      double* __restrict__ Lout, double nu) {
-  constexpr int P = nP3(K), NQV = nQV3(K), NQF = nQF3(K);
-  __shared__ ResTabs3<K> s;
-  stage_tabs3<K>(s, tb);
+  using RL = ResLayout3;
+  constexpr int P = nP3(K), NP = nPp3(K), NF = nF3(K), NM = RL::nm(K), NQV = nQV3(K), NQF = nQF3(K);
+  __shared__ __align__(16) double s[RL::lds(K)];  // the neighbour's tables differ from lane to lane
+  for (int i = threadIdx.x; i < RL::lds(K); i += blockDim.x) s[i] = tb.res[i];
+  __syncthreads();
   const int T = g.T;
   const int t = xcd_block() * blockDim.x + threadIdx.x;
   if (t >= T) return;
-  double u[3][P], acc[3][P];
-#pragma unroll
-  for (int c = 0; c < 3; ++c)
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      u[c][i] = U[(size_t)(c * P + i) * T + t];
-      acc[c][i] = 0;
-    }
-  double Ji[3][3];
-  load_Jinv3(g, t, Ji);
   const double isq = g.isq[t];
-
-  // volume: with a = sum_i u_i psihat_i (u = isq a at the point) and gr its reference
-  // gradient, the integrand times det J is [isq a (x) a - nu gr Jinv] Jinv^T : grad_ref v
-  for (int q = 0; q < NQV; ++q) {
-    double uq[3], gr[3][3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double a = 0, b0 = 0, b1 = 0, b2 = 0;
-#pragma unroll
-      for (int i = 0; i < P; ++i) {
-        a += u[c][i] * s.Vv[q][i];
-        if constexpr (VISC) {
-          b0 += u[c][i] * s.Gv[q][0][i];
-          b1 += u[c][i] * s.Gv[q][1][i];
-          b2 += u[c][i] * s.Gv[q][2][i];
-        }
-      }
-      uq[c] = a;
-      gr[c][0] = b0;
-      gr[c][1] = b1;
-      gr[c][2] = b2;
-    }
-    const double w = s.Wv[q];
-    double wG[3][3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double fl[3];
-      const double ua = isq * uq[c];
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        fl[j] = ua * uq[j];
-        if constexpr (VISC) fl[j] -= nu * (gr[c][0] * Ji[0][j] + gr[c][1] * Ji[1][j] + gr[c][2] * Ji[2][j]);
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) wG[c][a] = w * (fl[0] * Ji[a][0] + fl[1] * Ji[a][1] + fl[2] * Ji[a][2]);
-    }
+  double acc[3][P];
+  {
+    double u[3][P];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int i = 0; i < P; ++i)
-        acc[c][i] = fma(wG[c][2], s.Gv[q][2][i], fma(wG[c][1], s.Gv[q][1][i], fma(wG[c][0], s.Gv[q][0][i], acc[c][i])));
+      for (int i = 0; i < P; ++i) u[c][i] = U[(size_t)(c * P + i) * T + t];
+    double Ji[3][3];
+    load_Jinv3(g, t, Ji);
+    // modes of u_c u_d (c <= d) of the reference coefficients
+    double w[6][NP];
+#pragma unroll
+    for (int x = 0; x < 6; ++x)
+#pragma unroll
+      for (int j = 0; j < NP; ++j) w[x][j] = 0;
+    const auto vo = cst(tb.res + RL::vol(K));
+#pragma unroll 1
+    for (int q = 0; q < NQV; ++q) {
+      const auto row = vo + q * RL::volStride(K);
+      double a[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        a[c] = 0;
+#pragma unroll
+        for (int i = 0; i < P; ++i) a[c] += u[c][i] * row[i];
+      }
+      const double uu[6] = {a[0] * a[0], a[0] * a[1], a[0] * a[2], a[1] * a[1], a[1] * a[2], a[2] * a[2]};
+#pragma unroll
+      for (int x = 0; x < 6; ++x)
+#pragma unroll
+        for (int j = 0; j < NP; ++j) w[x][j] += uu[x] * row[P + j];
+    }
+    // flux modes fl[c][d] = isq w_cd - nu gr[c][e] Jinv[e][d], then their products with Jinv^T
+    constexpr int kD = 4 * P * NF;
+    double gr[3][3][NP];
+    if constexpr (VISC) {
+      const auto D = cst(again(tb.cond) + kD);
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+#pragma unroll
+          for (int j = 0; j < NP; ++j) gr[c][e][j] = 0;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) gr[c][e][j] += D[(i * NP + j) * 3 + e] * u[c][i];
+        table_group<3>(i);
+      }
+    }
+    constexpr int kSym[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        double fl[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          fl[d] = isq * w[kSym[c][d]][j];
+          if constexpr (VISC) fl[d] -= nu * (gr[c][0][j] * Ji[0][d] + gr[c][1][j] * Ji[1][d] + gr[c][2][j] * Ji[2][d]);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) gr[c][a][j] = fl[0] * Ji[a][0] + fl[1] * Ji[a][1] + fl[2] * Ji[a][2];
+      }
+    const auto D = cst(again(tb.cond) + kD);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[c][i] = 0;
+#pragma unroll
+      for (int j = 0; j < NP; ++j)
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) acc[c][i] += D[(i * NP + j) * 3 + e] * gr[c][e][j];
+      table_group<3>(i);
+    }
   }
 
   // faces
@@ -129,105 +185,183 @@ __global__ __launch_bounds__(kEBlk) void k_residual3(DevGeo g, DevTabs tb, const
     const int code = g.code[idx];
     // a closed boundary face (wall or inflow, nbr = -1): no term (u.n = 0 on a wall; on an
     // inflow the term acts on v.n only, which the increments keep 0); no viscous face terms
-    // on any boundary (interior faces only: free slip)
-    if (nb < 0 && !((code >> 6) & 1)) continue;
-    if (nb < 0) {  // outflow: -int max(u.n, 0) (u . v), own trace (backflow sees zero)
-      const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
-      const double li = g.flen[idx] * isq;
-      for (int r = 0; r < NQF; ++r) {
-        double uo[3];
+    // on any boundary (interior faces only: free slip).  On an outflow face the own trace
+    // stands on both sides: -int max(u.n, 0) (u . v), backflow sees zero.
+    const bool open = nb < 0;
+    if (open && !((code >> 6) & 1)) continue;
+    const int tn = open ? t : nb, fn = open ? f : code & 3, pid = open ? 0 : (code >> 2) & 7;
+    const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
+    const double li = g.flen[idx] * isq;
+    double nJ[3] = {}, gn[3][NM] = {};
+    if constexpr (VISC) {
+      const double* J = again(g.Jinv);  // read again for every face rather than held, as U below
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          double a = 0;
+      for (int a = 0; a < 3; ++a)
+        nJ[a] = n[0] * J[(size_t)(3 * a) * T + t] + n[1] * J[(size_t)(3 * a + 1) * T + t] +
+                n[2] * J[(size_t)(3 * a + 2) * T + t];
+    }
+    // the neighbour's trace and (sum of both sides') normal derivative, in its face parameters
+    double vn[3][NF], vo[3][NF];
+    {
+      const double isqn = g.isq[tn];
+      const double* tr = s + RL::tr(K) + fn * P * NF;
+      const double* dg = s + RL::dg(K) + fn * P * NM * 3;
+      double nJn[3] = {};
+      if constexpr (VISC) {
+        double Jn[3][3];
+        load_Jinv3(g, tn, Jn);
 #pragma unroll
-          for (int i = 0; i < P; ++i) a += u[c][i] * s.Vf[f][r][i];
-          uo[c] = a * isq;
-        }
-        const double un = uo[0] * n[0] + uo[1] * n[1] + uo[2] * n[2];
-        if (un > 0.0) {
-          const double w = s.Wf[r] * li;
+        for (int a = 0; a < 3; ++a) nJn[a] = n[0] * Jn[a][0] + n[1] * Jn[a][1] + n[2] * Jn[a][2];
+      }
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const double wq = -(w * un * uo[c]);
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
-            for (int i = 0; i < P; ++i) acc[c][i] = fma(wq, s.Vf[f][r][i], acc[c][i]);
-          }
+        for (int m = 0; m < NF; ++m) vo[c][m] = 0;
+      double gd[3][NM] = {};
+      // two coefficients at a time: with all unrolled, 512 registers and scratch; one at a
+      // time waits longer (94 us in the place of 83), five spill (90 us)
+      double w[2][3];
+#pragma unroll 1
+      for (int i0 = 0; i0 < P; i0 += 2) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) w[j][c] = isqn * U[(size_t)(c * P + i0 + j) * T + tn];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int i = i0 + j;
+#pragma unroll
+          for (int m = 0; m < NF; ++m)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) vo[c][m] += tr[i * NF + m] * w[j][c];
+          if constexpr (VISC)
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+              const int o = (i * NM + m) * 3;
+              const double b = nJn[0] * dg[o] + nJn[1] * dg[o + 1] + nJn[2] * dg[o + 2];
+#pragma unroll
+              for (int c = 0; c < 3; ++c) gd[c][m] += b * w[j][c];
+            }
+          table_group<1>(j);
         }
       }
-      continue;
+      // to the own face parameters (the modes of P^{K-1} among themselves)
+      const double* Q = s + RL::q(K) + pid * NF * NF;
+#pragma unroll
+      for (int m = 0; m < NF; ++m) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) vn[c][m] = 0;
+#pragma unroll
+        for (int k = 0; k < NF; ++k)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) vn[c][m] += Q[m * NF + k] * vo[c][k];
+        if constexpr (VISC)
+          if (m < NM)
+#pragma unroll
+            for (int k = 0; k < NM; ++k)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) gn[c][m < NM ? m : 0] += Q[m * NF + k] * gd[c][k];
+      }
     }
-    const int fn = code & 3, pid = (code >> 2) & 7;
-    const double n[3] = {g.nx[idx], g.ny[idx], g.nz[idx]};
-    double v[3][P];
+    // the own ones (vo: own trace)
+    {
+      const auto tr = cst(again(tb.res) + RL::tr(K) + f * P * NF);
+      const auto dg = cst(again(tb.res) + RL::dg(K) + f * P * NM * 3);
+      const double* Uo = again(U);  // read again for every face rather than held
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = 0; m < NF; ++m) vo[c][m] = 0;
+      double w[2][3];
+#pragma unroll 1
+      for (int i0 = 0; i0 < P; i0 += 2) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) w[j][c] = isq * Uo[(size_t)(c * P + i0 + j) * T + t];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int i = i0 + j;
+#pragma unroll
+          for (int m = 0; m < NF; ++m)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) vo[c][m] += tr[i * NF + m] * w[j][c];
+          if constexpr (VISC)
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+              const int o = (i * NM + m) * 3;
+              const double b = nJ[0] * dg[o] + nJ[1] * dg[o + 1] + nJ[2] * dg[o + 2];
+#pragma unroll
+              for (int c = 0; c < 3; ++c) gn[c][m] += b * w[j][c];
+            }
+          table_group<1>(j);
+        }
+      }
+    }
+    // upwind flux at the face points, back into modes
+    double q[3][NF];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int i = 0; i < P; ++i) v[c][i] = U[(size_t)(c * P + i) * T + nb];
-    const double isqn = g.isq[nb];
-    const double li = g.flen[idx] * isq;
-    double Jn[3][3] = {}, nJ[3] = {}, sig = 0;
-    if constexpr (VISC) {
-      sig = g.sig[idx];
-      load_Jinv3(g, nb, Jn);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) nJ[a] = n[0] * Ji[a][0] + n[1] * Ji[a][1] + n[2] * Ji[a][2];
-    }
+      for (int m = 0; m < NF; ++m) q[c][m] = 0;
+    const auto pt = cst(tb.res + RL::pt(K));
+#pragma unroll 1
     for (int r = 0; r < NQF; ++r) {
-      const int rn = s.pidx[pid][r];
-      double uo[3], un[3], go[3][3] = {}, gn[3][3] = {};
+      const auto L = pt + r * RL::ptStride(K);
+      double uo[3], un[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        double a = 0, an = 0, b[3] = {0, 0, 0}, bn[3] = {0, 0, 0};
+        uo[c] = un[c] = 0;
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-          a += u[c][i] * s.Vf[f][r][i];
-          an += v[c][i] * s.Vf[fn][rn][i];
-          if constexpr (VISC) {
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-              b[e] += u[c][i] * s.Gf[f][r][e][i];
-              bn[e] += v[c][i] * s.Gf[fn][rn][e][i];
-            }
-          }
-        }
-        uo[c] = a * isq;
-        un[c] = an * isqn;
-        if constexpr (VISC) {
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            go[c][j] = isq * (b[0] * Ji[0][j] + b[1] * Ji[1][j] + b[2] * Ji[2][j]);
-            gn[c][j] = isqn * (bn[0] * Jn[0][j] + bn[1] * Jn[1][j] + bn[2] * Jn[2][j]);
-          }
+        for (int m = 0; m < NF; ++m) {
+          uo[c] += L[m] * vo[c][m];
+          un[c] += L[m] * vn[c][m];
         }
       }
       const double unrm = 0.5 * ((uo[0] + un[0]) * n[0] + (uo[1] + un[1]) * n[1] + (uo[2] + un[2]) * n[2]);
       const bool own_up = unrm >= 0.0;
-      double Qv[3], du[3];
+      const double w = open && !own_up ? 0.0 : L[NF] * unrm;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const double up = own_up ? uo[c] : un[c];
-        du[c] = uo[c] - un[c];
-        Qv[c] = unrm * up;
-        if constexpr (VISC) {
-          const double avgn = 0.5 * ((go[c][0] + gn[c][0]) * n[0] + (go[c][1] + gn[c][1]) * n[1] + (go[c][2] + gn[c][2]) * n[2]);
-          Qv[c] = Qv[c] - nu * avgn + nu * sig * du[c];
-        }
+        const double fc = w * (own_up ? uo[c] : un[c]);
+#pragma unroll
+        for (int m = 0; m < NF; ++m) q[c][m] += L[m] * fc;
       }
-      const double w = s.Wf[r] * li;
+    }
+    // plus the viscous flux; du in vo
+    const double nuf = open ? 0.0 : nu, nsig = VISC ? nuf * g.sig[idx] : 0.0;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const double wq = -(w * Qv[c]);
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int m = 0; m < NF; ++m) {
         if constexpr (VISC) {
-          const double wh = w * (0.5 * nu * du[c]);
-          const double h0 = wh * nJ[0], h1 = wh * nJ[1], h2 = wh * nJ[2];
-#pragma unroll
-          for (int i = 0; i < P; ++i)
-            acc[c][i] = fma(wq, s.Vf[f][r][i],
-                            fma(h2, s.Gf[f][r][2][i], fma(h1, s.Gf[f][r][1][i], fma(h0, s.Gf[f][r][0][i], acc[c][i]))));
-        } else {
-#pragma unroll
-          for (int i = 0; i < P; ++i) acc[c][i] = fma(wq, s.Vf[f][r][i], acc[c][i]);
+          vo[c][m] -= vn[c][m];
+          q[c][m] += nsig * vo[c][m];
+          if (m < NM) {
+            q[c][m] -= 0.5 * nuf * gn[c][m < NM ? m : 0];
+            vo[c][m] *= 0.5 * nuf * li;
+          }
         }
+        q[c][m] *= -li;
+      }
+    {
+      const auto tr = cst(again(tb.res) + RL::tr(K) + f * P * NF);
+      const auto dg = cst(again(tb.res) + RL::dg(K) + f * P * NM * 3);
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+#pragma unroll
+        for (int m = 0; m < NF; ++m)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) acc[c][i] += tr[i * NF + m] * q[c][m];
+        if constexpr (VISC)
+#pragma unroll
+          for (int m = 0; m < NM; ++m) {
+            const int o = (i * NM + m) * 3;
+            const double b = nJ[0] * dg[o] + nJ[1] * dg[o + 1] + nJ[2] * dg[o + 2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc[c][i] += b * vo[c][m];
+          }
+        table_group<2>(i);
       }
     }
   }
@@ -424,17 +558,6 @@ __device__ inline void stage_cond3(CondTabs3<K>& s, const double* __restrict__ Q
   double* d = &s.Qf[0][0][0];
   for (int i = threadIdx.x; i < 6 * nF3(K) * nF3(K); i += blockDim.x) d[i] = Qf[i];
 }
-// A new scalar pointer to the same table: what is read through it is loaded again.
-__device__ inline const double* again(const double* p) {
-  asm volatile("" : "+s"(p));
-  return p;
-}
-// Ends a group of table reads, after N basis functions.
-template <int N>
-__device__ inline void table_group(int i) {
-  if (i % N == N - 1) __builtin_amdgcn_sched_barrier(0);
-}
-
 // y <- W_T y = y - D_T^T (D_T D_T^T)^{-1} D_T y, D_T = sum_a Jinv[a][c] Dh[a]
 template <int K>
 __device__ inline void apply_W3(double (&y)[3][nP3(K)], const double (&Ji)[3][3], const double* __restrict__ G, int T,

@@ -442,6 +442,48 @@ void build_ref_tables3(int K, RefTables& t) {
       for (int m = 0; m < NF; ++m)
         for (int n = 0; n < NF; ++n) t.Qf[((size_t)pid * NF + m) * NF + n] += cw[r] * mu2[m] * mu[n];
     }
+  // the residual's modal tables: face modes are the triangle's Dubiner basis, orthonormal under
+  // the face rule (weights summing to 1), degree by degree
+  {
+    const int nqf = t.nqf, NM = K * (K + 1) / 2, np = t.NP;
+    std::vector<double> Lm((size_t)nqf * NF), g2(2 * NF);
+    for (int r = 0; r < nqf; ++r) {
+      dubiner(K, fpts[2 * r], fpts[2 * r + 1], &Lm[(size_t)r * NF], g2.data());
+      for (int m = 0; m < NF; ++m) Lm[(size_t)r * NF + m] *= std::sqrt(0.5);
+    }
+    std::vector<double>& M = t.res;
+    M.assign(ResLayout3::size(K), 0.0);
+    double* tr = &M[ResLayout3::tr(K)];
+    double* dg = &M[ResLayout3::dg(K)];
+    for (int f = 0; f < 4; ++f)
+      for (int i = 0; i < P; ++i) {
+        for (int m = 0; m < NF; ++m)
+          for (int r = 0; r < nqf; ++r)
+            tr[((size_t)f * P + i) * NF + m] += t.fw[r] * Lm[(size_t)r * NF + m] * t.Vf[((size_t)f * nqf + r) * P + i];
+        for (int m = 0; m < NM; ++m)
+          for (int a = 0; a < 3; ++a)
+            for (int r = 0; r < nqf; ++r)
+              dg[(((size_t)f * P + i) * NM + m) * 3 + a] +=
+                  t.fw[r] * Lm[(size_t)r * NF + m] * t.Gf[(((size_t)f * nqf + r) * 3 + a) * P + i];
+      }
+    double* q = &M[ResLayout3::q(K)];
+    for (int pm = 0; pm < 6; ++pm)
+      for (int m = 0; m < NF; ++m)
+        for (int n = 0; n < NF; ++n)
+          for (int r = 0; r < nqf; ++r)
+            q[((size_t)pm * NF + m) * NF + n] +=
+                t.fw[r] * Lm[(size_t)r * NF + m] * Lm[(size_t)t.fpidx[pm * nqf + r] * NF + n];
+    double* pt = &M[ResLayout3::pt(K)];
+    for (int r = 0; r < nqf; ++r) {
+      for (int m = 0; m < NF; ++m) pt[(size_t)r * ResLayout3::ptStride(K) + m] = Lm[(size_t)r * NF + m];
+      pt[(size_t)r * ResLayout3::ptStride(K) + NF] = t.fw[r];
+    }
+    double* vo = &M[ResLayout3::vol(K)];
+    for (int r = 0; r < t.nqv; ++r) {
+      for (int i = 0; i < P; ++i) vo[(size_t)r * ResLayout3::volStride(K) + i] = t.Vv[(size_t)r * P + i];
+      for (int j = 0; j < np; ++j) vo[(size_t)r * ResLayout3::volStride(K) + P + j] = t.vw[r] * t.Vv[(size_t)r * P + j];
+    }
+  }
   for (int f = 0; f < 4; ++f)
     for (int i = 0; i < P; ++i)
       for (int m = 0; m < NF; ++m) t.cond.push_back(t.Ch[((size_t)f * NF + m) * P + i]);
