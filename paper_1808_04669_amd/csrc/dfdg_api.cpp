@@ -25,6 +25,7 @@ struct dfdg_mesh {
 
 constexpr int kHistSlots = 7;
 
+constexpr long kOneLaunchRows = 262144;  // launch_pcg_jacobi: 1024 blocks of 256
 constexpr int kHintRuns = 3;  // PCG runs whose iteration counts size the first chunk
 
 struct dfdg_ctx {
@@ -502,6 +503,7 @@ static void carve(dfdg_ctx* ctx, char* base) {
     pb->rz[0] = c.take<double>(2 * G);
     pb->rz[1] = c.take<double>(2 * G);
     pb->pq = c.take<double>(2 * G);
+    for (double*& pj : pb->pj) pj = c.take<double>(6 * kOneLaunchRows / 256);
   }
   if (mixed) {
     ctx->L32 = c.take<float>(nU);
@@ -925,6 +927,17 @@ static int capture_iteration(dfdg_ctx* ctx, int parity, int count, Step step, hi
 // scalars after each chunk.  The first chunk is the length of the previous run (*hint);
 // later chunks follow the mean contraction of (r, r) observed so far, so that few
 // iterations run past the end (those exit at their first instruction).
+// Point Jacobi with the update and the product in one kernel (launch_pcg_jacobi): on S in
+// blocks, while one pass of the grid covers the rows and the caller has not set a smaller grid.
+// An RK3 step, two kernels -> one: 32^2 BDM_2 8.9 -> 4.7 ms, 128^2 BDM_3 35 -> 29, 256^2 BDM_2
+// 128 -> 118, 6^3 7.0 -> 3.6, 16^3 22.5 -> 20.5; beyond, where the values of S count, three products of
+// a row cost more than they save (400^2 BDM_3: 350 -> 380).
+static bool one_launch_jacobi(const dfdg_ctx* ctx) {
+  const long parts = (long)ctx->E * facet_split(ctx->NF, ctx->A.ns);
+  return ctx->prm.precond == DFDG_JACOBI && !ctx->A.mfq && parts <= kOneLaunchRows &&
+         ctx->g.fgrid == facet_grid_size((int)parts, 0);
+}
+
 template <typename Step>
 static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGraphExec_t (&graph)[6], int* hint,
                     PcgScalars& fin) {
@@ -943,7 +956,8 @@ static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGrap
   // With the multigrid cycle (two levels or more) the last kernel of an iteration applies
   // the stopping test, so a run of n iterations takes n launches; otherwise the next
   // iteration's first kernel applies it and a run takes n + 1
-  const int extra = (amg && ctx->mg.nlev >= 2) ? 0 : 1;  // (the elimination likewise)
+  // (the elimination likewise; the one-launch Jacobi iteration tests the residual before last)
+  const int extra = (amg && ctx->mg.nlev >= 2) ? 0 : (one_launch_jacobi(ctx) && sc == ctx->pb.sc) ? 2 : 1;
   // the first chunk: the fewest iterations among the last kHintRuns runs.  With start
   // values that vary in quality the count varies from solve to solve; a chunk that falls
   // short costs one host round trip, while each iteration enqueued past the end still runs
@@ -971,9 +985,9 @@ static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGrap
     rc = read_scalars(ctx, sc, fin);
     if (rc) return rc;
     if (fin.done != PCG_RUNNING) break;
-    if (launched > maxit + 2) return fail(ctx, DFDG_E_NOT_CONVERGED, "PCG did not stop at its iteration limit");
-    // fin.rr is (r, r) after launched - 1 iterations; one more iteration has run and one
-    // further launch applies the test, so the estimate from fin.rr counts both
+    if (launched > maxit + 2 + extra) return fail(ctx, DFDG_E_NOT_CONVERGED, "PCG did not stop at its iteration limit");
+    // fin.rr is (r, r) after launched - extra iterations; the extra ones have run, and as many
+    // further launches apply the test, so the estimate from fin.rr counts both
     int next = std::max(chunk / 2, 2);
     if (fin.iters > 0 && fin.rr > 0 && fin.rr0 > fin.rr && fin.tol2 > 0) {
       const double rate = std::log(fin.rr / fin.rr0) / fin.iters;  // < 0
@@ -1095,9 +1109,16 @@ static int solve_facets(dfdg_ctx* ctx, double* lam, dfdg_solve_info* info, const
       if (c32) HIPC((launch_vcycle<float, double>(NF, g, A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
       else HIPC((launch_vcycle<double, double>(NF, g, A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
     }
+    const bool one = one_launch_jacobi(ctx);
     auto step = [&](int it, hipStream_t st) -> hipError_t {
       double* pin = ctx->p[(it - 1) & 1];
       double* pout = ctx->p[it & 1];
+      if (one) {  // r alternates between r (odd launches' input) and rb, S p between Sp and z
+        double* rs[2] = {ctx->rb, ctx->r};
+        double* ss[2] = {ctx->z, ctx->Sp};
+        return launch_pcg_jacobi(NF, g, A, rs[it & 1], rs[(it - 1) & 1], ss[it & 1], ss[(it - 1) & 1], pin, pout, x,
+                                 pb, it, st);
+      }
       if (fused) {  // residual alternates between r (even iterations) and rb (odd)
         double* rin = (it & 1) ? ctx->r : ctx->rb;
         double* rout = (it & 1) ? ctx->rb : ctx->r;

@@ -9,10 +9,24 @@ static constexpr int kEBlk = 128;  // element kernels
 
 static inline unsigned nblk(long n, int b) { return (unsigned)((n + b - 1) / b); }
 
+// x of another lane by a data-parallel-primitive move (0 where there is none), and the sum
+// over a full wave: within rows of 16 lanes, then across the rows into lane 63, whose value
+// every lane receives.  Register moves in the place of a round trip through LDS per step.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_move(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
 __device__ inline double wave_sum(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+  x += dpp_move<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8
+  x += dpp_move<0x112, 0xf>(x);
+  x += dpp_move<0x114, 0xf>(x);
+  x += dpp_move<0x118, 0xf>(x);
+  x += dpp_move<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+  x += dpp_move<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                          __builtin_amdgcn_readlane(__double2loint(x), 63));
 }
 __device__ inline double wave_max(double x) {
 #pragma unroll

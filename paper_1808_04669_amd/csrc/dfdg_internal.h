@@ -187,7 +187,7 @@ struct PcgScalars {
   double rr0;  // (r, r) at the start of the run (written with the first iteration)
   int iters, done, maxit, zero_rhs;
   int it;      // index of the next iteration (set to 1 at the start, advanced by the update kernel)
-  int pad;
+  int it2;     // launch_pcg_jacobi: the index of the next launch of even parity (it: odd parity)
 };
 enum { PCG_RUNNING = 0, PCG_CONVERGED = 1, PCG_BREAKDOWN = 2, PCG_MAXIT = 3, PCG_NONFINITE = 4 };
 

@@ -25,6 +25,7 @@ struct PcgBufs {
   double* gg;      // [G][2] (g,g),(z,g) partials; reused for the FP64 refinement residual
   double* rz[2];   // [G][2] (r,z),(r,r) partials of even / odd iterations
   double* pq;      // [G][2] (p,Sp), (z,Sp) partials (z the normalised kernel vector of S)
+  double* pj[2];   // [G][6] partials of launch_pcg_jacobi
 };
 // G: blocks of the facet kernels, ceil(E/256) up to 1024, or at most cap (> 0)
 int facet_grid_size(int E, int cap);
@@ -158,6 +159,12 @@ hipError_t launch_pcg_spmv(int NF, const DevGeo& g, const DevBsr& A, const doubl
 hipError_t launch_pcg_update(int NF, int pc, const DevGeo& g, const DevBsr& A, const double* p,
                              const double* Sp, double* x, double* r, double* z, const PcgBufs& pb, int it,
                              hipStream_t s);
+// Both of these for point Jacobi in one launch: the update of iteration it-1, then the product
+// of iteration it; the stopping test is on iteration it-2 (r_in, s_in, p_in: of launch it-1,
+// alternating buffers).
+hipError_t launch_pcg_jacobi(int NF, const DevGeo& g, const DevBsr& A, const double* r_in, double* r_out,
+                             const double* s_in, double* s_out, const double* p_in, double* p_out, double* x,
+                             const PcgBufs& pb, int it, hipStream_t s);
 // FP32 inner PCG (MIXED): the same kernels on float vectors and the FP32 copy of S.
 hipError_t launch_pcg32_init(int NF, bool block_jacobi, const DevGeo& g, const DevBsr& A, const double* r64,
                              float* x, float* r, float* z, float* p_old, const PcgBufs& pb, hipStream_t s);

@@ -695,6 +695,7 @@ __global__ __launch_bounds__(kBlk) void k_finalize_gather(const double* __restri
     sc->zero_rhs = !(gg > 1e-26 * t[2]);
     sc->iters = 0;
     sc->it = 1;
+    sc->it2 = 0;
     sc->rr = 0;
     sc->done = !isfinite(gg) ? PCG_NONFINITE : (sc->zero_rhs ? PCG_CONVERGED : PCG_RUNNING);
   }
@@ -765,6 +766,18 @@ constexpr int kSplit = facet_split(NF, NS);
 __device__ inline float half_at(const uint32_t* w, int j) {
   const uint32_t v = w[j >> 1];
   return (float)__builtin_bit_cast(_Float16, (uint16_t)((j & 1) ? (v >> 16) : (v & 0xffffu)));
+}
+
+// Reads the column indices of row part u and keeps them: a kernel whose first loads these are
+// waits for the stop flag and for them together, one round trip in the place of two.
+template <int SPL, int NS>
+__device__ inline void first_columns(const DevBsr& A, int E, int u) {
+  if (u >= E * SPL) return;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int c = A.cols[(size_t)s * E + u / SPL];
+    asm volatile("" ::"v"(c));
+  }
 }
 
 // Outputs [a0, a0 + NA) of row F of S x in the multigrid's arithmetic V (get(c, x_c) gives
@@ -974,17 +987,19 @@ __global__ __launch_bounds__(kBlk) void k_pcg_spmv(DevGeo g, DevBsr A, const V* 
                                                    V* __restrict__ Sp, PcgScalars* sc,
                                                    const double* __restrict__ rz_prev,
                                                    const double* __restrict__ rz_prev2, double* __restrict__ pq) {
-  if (sc->done != PCG_RUNNING) return;
-  const int it = sc->it;  // advanced only by the update kernel
+  constexpr int SPL = kSplit<NF, NS>, NA = NF / SPL;
   const int E = g.E;
   const int G = gridDim.x;
+  const int u0 = xcd_block() * blockDim.x + threadIdx.x;
+  const int done = sc->done, it = sc->it;  // (it: advanced only by the update kernel)
+  first_columns<SPL, NS>(A, E, u0);
+  if (done != PCG_RUNNING) return;
   // beta is not needed before the end: S p_new = S z + beta S p_old.  The partials are
   // loaded first and summed after this thread's first row, whose loads overlap them.
   PartLoad<2> q1, q2;
   partials_load<2>(rz_prev, G, true, q1);
   partials_load<2>(rz_prev2, G, it >= 2, q2);
   const M* vals = (sizeof(M) == 8) ? (const M*)A.vals : (const M*)A.vals32;
-  constexpr int SPL = kSplit<NF, NS>, NA = NF / SPL;
   // outputs [a0, a0 + NA) of row F
   auto row = [&](int u, V (&sz)[NA], V (&sp)[NA]) {
     const int F = u / SPL, a0 = (u % SPL) * NA;
@@ -1009,7 +1024,6 @@ __global__ __launch_bounds__(kBlk) void k_pcg_spmv(DevGeo g, DevBsr A, const V* 
         }
     }
   };
-  const int u0 = xcd_block() * blockDim.x + threadIdx.x;
   V sz[NA], sp[NA];
   if (u0 < E * SPL) row(u0, sz, sp);
   double t1[2];
@@ -1147,6 +1161,133 @@ __global__ __launch_bounds__(kBlk) void k_pcg_update(DevGeo g, DevBsr A, const V
   }
   block_write_partial<2>(v, rz_out);
   if (blockIdx.x == 0 && threadIdx.x == 0) sc->it = sc->it + 1;  // no other block reads it here
+}
+
+// One PCG iteration with point Jacobi in one kernel (FP64, S in blocks): the update of
+// iteration it-1 and the product of iteration it, with one reduction.  Launch it >= 1 enters
+// with r = r_{it-2}, s = S p_{it-1}, p = p_{it-1} and x = x_{it-2} (it = 1: r_0, no s, p = 0)
+// and the previous launch's partials
+//     (p, s), (z, s), (D^{-1} r, s), (D^{-1} s, s), (r, D^{-1} r), (r, r),
+// z the normalised kernel vector.  alpha = (r, D^{-1} r) / (p, s) gives x and r of it-1; beta
+// needs the new (r, D^{-1} r), which is predicted,
+//     (r, D^{-1} r) - 2 alpha (D^{-1} r, s) + alpha^2 (D^{-1} s, s),
+// and formed from the new r itself for the next launch, so that no prediction's rounding goes
+// further than one beta (predict-and-recompute conjugate gradients, T. Chen and E. Carson,
+// SIAM J. Sci. Comput. 42, 2020).  As z + beta p of a neighbour is not at hand,
+//     S p_it = S D^{-1} r - alpha (S D^{-1} s - (z, s) S D^{-1} z) + beta S p
+// by linearity, from the neighbours' r, s and p: none of it waits for the sums.  The stopping
+// test is on r_{it-2}, whose x the buffer then holds.
+//
+// One row part per thread.  Bound by the latency of the launch, of two dependent round trips to
+// memory and of the sums, once an iteration in the place of twice.
+template <int NF, int NS, int BLK>
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_pcg_jacobi(DevGeo g, DevBsr A, const double* __restrict__ r_in,
+                                                     double* __restrict__ r_out, const double* __restrict__ s_in,
+                                                     double* __restrict__ s_out, const double* __restrict__ p_in,
+                                                     double* __restrict__ p_out, double* __restrict__ x,
+                                                     PcgScalars* sc, int odd, const double* __restrict__ rz0,
+                                                     const double* __restrict__ part_in, double* __restrict__ part_out) {
+  const int done = sc->done, it = odd ? sc->it : sc->it2;  // tested after the first row's loads
+  const bool first = it == 1;
+  const int E = g.E, G = gridDim.x;
+  double t[6] = {0, 0, 0, 0, 0, 0};
+  if (first) {
+    for (int b = threadIdx.x; b < g.fgrid; b += BLK) {
+      t[4] += rz0[2 * b];
+      t[5] += rz0[2 * b + 1];
+    }
+  } else {
+    for (int b = threadIdx.x; b < G; b += BLK)
+#pragma unroll
+      for (int i = 0; i < 6; ++i) t[i] += part_in[b * 6 + i];
+  }
+  constexpr int SPL = kSplit<NF, NS>, NA = NF / SPL;
+  const double* __restrict__ vals = A.vals;
+  const double* __restrict__ dinv = A.dinv;
+  const int u = xcd_block() * BLK + threadIdx.x, F = u / SPL, a0 = (u % SPL) * NA;
+  const bool on = u < E * SPL;
+  // outputs [a0, a0 + NA) of S D^{-1} r, S D^{-1} s, S p and S D^{-1} z
+  double yr[NA], ys[NA], yp[NA], yz[NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a) yr[a] = ys[a] = yp[a] = yz[a] = 0;
+  if (on) {
+#pragma unroll
+    for (int s5 = 0; s5 < NS; ++s5) {
+      const int c = A.cols[(size_t)s5 * E + F];
+      double rc[NF], wc[NF], pc[NF];
+      const double zc = g.zdef[c] * dinv[(size_t)c * NF];
+#pragma unroll
+      for (int b = 0; b < NF; ++b) {
+        const size_t o = (size_t)c * NF + b;
+        const double d = dinv[o];
+        rc[b] = d * r_in[o];
+        wc[b] = d * s_in[o];
+        pc[b] = p_in[o];
+      }
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < NF; ++b) {
+          const double m = vals[(((size_t)s5 * NF + a0 + a) * NF + b) * E + F];
+          yr[a] += m * rc[b];
+          ys[a] += m * wc[b];
+          yp[a] += m * pc[b];
+          if (b == 0) yz[a] += m * zc;
+        }
+    }
+  }
+  if (done != PCG_RUNNING) return;
+  block_sum_values<6>(t, t);
+  double alpha = 0, beta = 0;
+  int status = PCG_RUNNING;
+  if (!isfinite(t[4]) || !isfinite(t[5])) status = PCG_NONFINITE;
+  else if (t[5] <= sc->tol2) status = PCG_CONVERGED;
+  else if (it - 2 >= sc->maxit || (first && sc->maxit < 1)) status = PCG_MAXIT;
+  else if (!first) {
+    if (!isfinite(t[0])) status = PCG_NONFINITE;
+    else if (!(t[0] > 0)) status = PCG_BREAKDOWN;
+    else {
+      alpha = t[4] / t[0];
+      beta = fmax(t[4] - alpha * (2 * t[2] - alpha * t[3]), 0.0) / t[4];
+      if (!isfinite(alpha) || !isfinite(beta)) status = PCG_NONFINITE;
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc->iters = first ? 0 : it - 2;
+    sc->rr = t[5];
+    sc->rz = t[4];
+    if (first) sc->rr0 = t[5];
+    if (status != PCG_RUNNING) sc->done = status;
+    else (odd ? sc->it2 : sc->it) = it + 1;  // the other parity's launch reads it
+  }
+  if (status != PCG_RUNNING) return;
+  const double dz = t[1];
+  double v[6] = {0, 0, 0, 0, 0, 0};
+  if (on) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      const size_t o = (size_t)F * NF + a0 + a;
+      const double d = dinv[o], pi = p_in[o];
+      double rn = r_in[o], sn = yr[a];
+      const double zf = a0 + a == 0 ? g.zdef[F] : 0.0;
+      if (!first) {  // (the first launch reads no s)
+        rn -= alpha * (s_in[o] - dz * zf);
+        sn += beta * yp[a] - alpha * (ys[a] - dz * yz[a]);
+        x[o] += alpha * pi;
+      }
+      const double zn = d * rn, pn = first ? zn : zn + beta * pi;
+      r_out[o] = rn;
+      p_out[o] = pn;
+      s_out[o] = sn;
+      v[0] += pn * sn;
+      v[1] += zf * sn;
+      v[2] += zn * sn;
+      v[3] += d * sn * sn;
+      v[4] += rn * zn;
+      v[5] += rn * rn;
+    }
+  }
+  block_write_partial<6>(v, part_out);
 }
 
 // Inner FP32 PCG start for S d = r64 (d = 0): r = (float) r64; partials (r,z), (r,r).
@@ -1533,9 +1674,13 @@ __global__ __launch_bounds__(kBlk) void k_pcg_upd_mg0_pre(DevGeo g, DevBsr A, co
                                                           V* __restrict__ x2, CheB cb, PcgScalars* sc,
                                                           const double* __restrict__ rz_prev,
                                                           const double* __restrict__ pq, double* __restrict__ rz_out) {
-  if (sc->done != PCG_RUNNING) return;
+  constexpr int SPL = kSplit<NF, NS>, NA = NF / SPL;
   const int E = g.E;
   const int G = gridDim.x;
+  const int u0 = xcd_block() * blockDim.x + threadIdx.x;
+  const int done = sc->done;
+  first_columns<SPL, NS>(A, E, u0);
+  if (done != PCG_RUNNING) return;
   // alpha is not needed before the end: with u = D^{-1} r_old / th and w = D^{-1} S p / th,
   // S x1 = S u - alpha S w.  The partials are loaded first and summed after this thread's
   // first row, whose loads overlap them.
@@ -1544,7 +1689,6 @@ __global__ __launch_bounds__(kBlk) void k_pcg_upd_mg0_pre(DevGeo g, DevBsr A, co
   partials_load<2>(pq, G, true, q2);
   const V* dinv = bsr_dinv<NF, V>(A);
   const V ith = (V)(1.0 / cb.th), c1 = (V)cb.c1, c2 = (V)cb.c2;
-  constexpr int SPL = kSplit<NF, NS>, NA = NF / SPL;
   auto row = [&](int u, V (&su)[NA], V (&sw)[NA]) {
     spmv_part_mg2<NF, NS, NA, V>(A, E, u / SPL, (u % SPL) * NA, [&](int c, V (&uc)[NF], V (&wc)[NF]) {
 #pragma unroll
@@ -1556,7 +1700,6 @@ __global__ __launch_bounds__(kBlk) void k_pcg_upd_mg0_pre(DevGeo g, DevBsr A, co
       }
     }, su, sw);
   };
-  const int u0 = xcd_block() * blockDim.x + threadIdx.x;
   V su[NA], sw[NA];
   if (u0 < E * SPL) row(u0, su, sw);
   double t1[2], t2[2];
@@ -2296,6 +2439,27 @@ hipError_t launch_pcg_update(int NF, int pc, const DevGeo& g, const DevBsr& A, c
                              double* x, double* r, double* z, const PcgBufs& pb, int it, hipStream_t s) {
   if (A.mfq && pc != 2) return launch_mf_update3(NF, pc == 1, g, A, p, x, r, z, pb, it, s);
   return update_any<double>(NF, pc, g, A, p, Sp, x, r, z, pb, it, s);
+}
+hipError_t launch_pcg_jacobi(int NF, const DevGeo& g, const DevBsr& A, const double* r_in, double* r_out,
+                             const double* s_in, double* s_out, const double* p_in, double* p_out, double* x,
+                             const PcgBufs& pb, int it, hipStream_t s) {
+  // one row part per thread and at most 4 partials per thread to sum; the smallest blocks that
+  // give that, since they spread the gathers over the most CUs (64^2 BDM_2, 12288 facets: 17.8 ms
+  // an RK4 step with blocks of 64, 33.3 with blocks of 256)
+  const int units = g.E * facet_split(NF, A.ns);
+  const int B = units > 4 * 128 * 128 ? 256 : units > 4 * 64 * 64 ? 128 : 64;
+  const int G = (units + B - 1) / B;
+  if (G > kMaxFacetGrid) return hipErrorInvalidValue;
+  auto run = [&](auto ker) {
+    hipLaunchKernelGGL(ker, dim3(G), dim3(B), 0, s, g, A, r_in, r_out, s_in, s_out, p_in, p_out, x, pb.sc, it & 1,
+                       (const double*)pb.rz[0], (const double*)pb.pj[(it - 1) & 1], pb.pj[it & 1]);
+  };
+  DFDG_DISPATCH_NFS(NF, A.ns, {
+    if (B == 64) run(k_pcg_jacobi<NN, SS, 64>);
+    else if (B == 128) run(k_pcg_jacobi<NN, SS, 128>);
+    else run(k_pcg_jacobi<NN, SS, 256>);
+  });
+  return hipGetLastError();
 }
 hipError_t launch_pcg32_spmv(int NF, const DevGeo& g, const DevBsr& A, const float* z, const float* p_old,
                              float* p_new, float* Sp, const PcgBufs& pb, int it, hipStream_t s) {
