@@ -448,7 +448,49 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
     Csr R = transpose(P);
     Csr AP = matmul(L.A, P);
     Csr Ac = matmul(R, AP);
-    if (level > 0) {  // for the fused transfer kernels of the coarse levels
+    if (level > 0) {  // the smoothing steps of the coarse levels within their transfers
+      const double ith = 1.0 / amg_coarse_theta(L.lmax);
+      Csr C;  // P - D^{-1} A P / th, on the columns of A P (which has those of P)
+      C.n = n;
+      C.m = P.m;
+      C.ptr.assign(n + 1, 0);
+      Csr& W = L.Ps;
+      W.n = n;
+      W.m = n + P.m;
+      W.ptr.assign(n + 1, 0);
+      for (Csr* M : {&C, &W}) {
+        const size_t nz = AP.nnz() + (M == &W ? L.A.nnz() : 0);
+        M->col.reserve(nz);
+        M->val.reserve(nz);
+      }
+      std::vector<int> pos(P.m, -1);
+      for (int i = 0; i < n; ++i) {
+        const double w = ith * L.dinv[i];
+        for (int k = L.A.ptr[i]; k < L.A.ptr[i + 1]; ++k) {
+          const int c = L.A.col[k];
+          W.col.push_back(c);
+          W.val.push_back((c == i ? 2.0 * w : 0.0) - w * L.A.val[k] * (ith * L.dinv[c]));
+        }
+        const size_t c0 = C.col.size();
+        auto add = [&](int c, double v) {
+          if (pos[c] < 0) {
+            pos[c] = (int)C.col.size();
+            C.col.push_back(c);
+            C.val.push_back(0.0);
+          }
+          C.val[pos[c]] += v;
+        };
+        for (int k = AP.ptr[i]; k < AP.ptr[i + 1]; ++k) add(AP.col[k], -w * AP.val[k]);
+        for (int k = P.ptr[i]; k < P.ptr[i + 1]; ++k) add(P.col[k], P.val[k]);
+        for (size_t k = c0; k < C.col.size(); ++k) {
+          pos[C.col[k]] = -1;
+          W.col.push_back(n + C.col[k]);
+          W.val.push_back(C.val[k]);
+        }
+        C.ptr[i + 1] = (int)C.col.size();
+        W.ptr[i + 1] = (int)W.col.size();
+      }
+      L.Rs = transpose(C);
       L.RA = transpose(AP);
       L.AP = std::move(AP);
     }
@@ -506,6 +548,22 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
   }
   H.coarse_inv = std::move(D);
   H.n_coarse = nc;
+  H.coarse_fold.clear();
+  if (H.lv.size() >= 3) {
+    const Csr& Rs = H.lv[H.lv.size() - 2].Rs;
+    if ((long)nc * Rs.m <= kAmgFoldValues) {
+      H.coarse_fold.assign((size_t)nc * Rs.m, 0.0);
+      parallel_chunks(nc, [&](int, int r0, int r1) {
+        for (int i = r0; i < r1; ++i) {
+          double* row = &H.coarse_fold[(size_t)i * Rs.m];
+          for (int j = 0; j < nc; ++j) {
+            const double a = H.coarse_inv[(size_t)i * nc + j];
+            for (int k = Rs.ptr[j]; k < Rs.ptr[j + 1]; ++k) row[Rs.col[k]] += a * Rs.val[k];
+          }
+        }
+      });
+    }
+  }
   return 0;
 }
 

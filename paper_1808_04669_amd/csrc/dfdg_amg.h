@@ -22,13 +22,24 @@ struct AmgLevel {
   Csr P;            // prolongator from the next coarser level to this one (empty on the coarsest)
   Csr R;            // restriction = P^T
   Csr AP, RA;       // A P and R A = (A P)^T, kept on levels >= 1 that have a coarser level
+  // on those levels, with one damped Jacobi step x1 = D^{-1} b / th around the coarse correction e:
+  Csr Rs;           // the restricted residual of x1 from b, R (I - A D^{-1} / th)
+  Csr Ps;           // the result from [b; e]: (2 - D^{-1} A / th) D^{-1} / th, then Rs^T
 };
+inline double amg_smooth_lmax(double lmax) { return 1.05 * lmax; }
+// th of the coarse levels: the centre of [lmax / 30, lmax]
+inline double amg_coarse_theta(double lmax) { return 0.5 * amg_smooth_lmax(lmax) * (1.0 + 1.0 / 30.0); }
 
 struct AmgHierarchy {
   std::vector<AmgLevel> lv;          // lv[0] = fine operator S
   std::vector<double> coarse_inv;    // dense pseudo-inverse (n_c x n_c) of the coarsest operator
   int n_coarse = 0;
+  // with three levels or more: coarse_inv Rs of the level above (n_c x its unknowns), if within
+  // kAmgFoldValues
+  std::vector<double> coarse_fold;
 };
+// 32 MB in FP32, read at the rate of the memory-side cache in about the time of the launch saved
+constexpr long kAmgFoldValues = 8l << 20;
 
 // Builds the hierarchy for the BSR facet matrix (cols [NS][E], vals [NS][NF][NF][E]) with the
 // near-null vector z (the constant multiplier, scalar length E*NF); singular: z spans the

@@ -552,22 +552,16 @@ static void carve(dfdg_ctx* ctx, char* base) {
   for (int l = 0; l < mg.nlev; ++l) {
     const AmgLevel& L = H.lv[l];
     const long n = L.A.n;
-    if (l > 0) {
-      take_csr(L.A, mg.A[l], 1);
-      mg.dinv[l] = c.take<double>(n);
-      mg.dinv32[l] = f32 ? c.take<float>(n) : nullptr;
-    }
-    if (l < mg.nlev - 1) {
+    if (l == 0 && mg.nlev > 1) {
       // the restriction from the finest level gathers from the largest vector: a few
       // lanes per row (8 for rows of ~40 entries), each with one batch of entries, keep
       // more of those gathers in flight;
       // the finest-level transfers of an FP32 cycle in FP16 (P packed, R = P^T rounded alike)
-      const bool packed = take_csr(L.P, mg.P[l], 1, l == 0 && f16);
-      take_csr(L.R, mg.R[l], l == 0 ? 4 : 1, false, packed);
-      if (l > 0) {
-        take_csr(L.AP, mg.AP[l], 1);
-        take_csr(L.RA, mg.RA[l], 1);
-      }
+      const bool packed = take_csr(L.P, mg.P0, 1, f16);
+      take_csr(L.R, mg.R0, 4, false, packed);
+    } else if (l > 0 && l < mg.nlev - 1) {
+      take_csr(L.Rs, mg.Rs[l], 1);
+      take_csr(L.Ps, mg.Ps[l], 1);
     }
     MgVec<double>& v = mg.v64[l];
     v.b = (l > 0) ? c.take<double>(n) : nullptr;
@@ -591,16 +585,20 @@ static void carve(dfdg_ctx* ctx, char* base) {
     }
     // Chebyshev on [lmin, lmax], lmax = 1.05 rho(D^{-1} A): degree 2 on [lmax/15, lmax] on the
     // finest level, degree 1 (damped Jacobi with weight 1/th) on [lmax/30, lmax] on the
-    // coarser ones (intervals chosen by the PCG iteration count they give)
-    const double lmax = 1.05 * L.lmax, lmin = lmax / (l == 0 ? 15.0 : 30.0);
-    const double th = 0.5 * (lmax + lmin), de = 0.5 * (lmax - lmin);
-    const double sig = th / de, rho0 = 1.0 / sig, rho1 = 1.0 / (2.0 * sig - rho0);
-    mg.cheb[l] = CheB{th, rho1 * rho0, 2.0 * rho1 / de};
+    // coarser ones, within their matrices (intervals chosen by the PCG iteration count they give)
+    if (l == 0) {
+      const double lmax = amg_smooth_lmax(L.lmax), lmin = lmax / 15.0;
+      const double th = 0.5 * (lmax + lmin), de = 0.5 * (lmax - lmin);
+      const double sig = th / de, rho0 = 1.0 / sig, rho1 = 1.0 / (2.0 * sig - rho0);
+      mg.cheb = CheB{th, rho1 * rho0, 2.0 * rho1 / de};
+    }
   }
   if (mg.nlev > 0) {
     mg.n_coarse = H.n_coarse;
-    mg.coarse_inv = c.take<double>(H.coarse_inv.size());
-    mg.coarse_inv32 = f32 ? c.take<float>(H.coarse_inv.size()) : nullptr;
+    mg.fold = !H.coarse_fold.empty();
+    const size_t nd = (mg.fold ? H.coarse_fold : H.coarse_inv).size();
+    mg.coarse_inv = c.take<double>(nd);
+    mg.coarse_inv32 = f32 ? c.take<float>(nd) : nullptr;
   }
   if (ctx->el_on) {
     const ElimHost& h2 = ctx->eh;
@@ -779,23 +777,18 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
     keep.reserve(8 * kMaxLev + 2);
     for (int l = 0; l < mg.nlev; ++l) {
       const AmgLevel& L = H.lv[l];
-      if (l > 0) {
-        if (int rc = up_csr(L.A, mg.A[l])) return rc;
-        HIPC(up(const_cast<double*>(mg.dinv[l]), L.dinv, s));
-        if (mixed) HIPC(up(const_cast<float*>(mg.dinv32[l]), f32(L.dinv), s));
-      }
-      if (l < mg.nlev - 1) {
-        if (int rc = up_csr(L.P, mg.P[l])) return rc;
-        if (int rc = up_csr(L.R, mg.R[l])) return rc;
-        if (l > 0) {
-          if (int rc = up_csr(L.AP, mg.AP[l])) return rc;
-          if (int rc = up_csr(L.RA, mg.RA[l])) return rc;
-        }
+      if (l == 0 && mg.nlev > 1) {
+        if (int rc = up_csr(L.P, mg.P0)) return rc;
+        if (int rc = up_csr(L.R, mg.R0)) return rc;
+      } else if (l > 0 && l < mg.nlev - 1) {
+        if (int rc = up_csr(L.Rs, mg.Rs[l])) return rc;
+        if (int rc = up_csr(L.Ps, mg.Ps[l])) return rc;
       }
     }
     if (mg.nlev > 0) {
-      HIPC(up(const_cast<double*>(mg.coarse_inv), H.coarse_inv, s));
-      if (mixed) HIPC(up(const_cast<float*>(mg.coarse_inv32), f32(H.coarse_inv), s));
+      const std::vector<double>& dense = mg.fold ? H.coarse_fold : H.coarse_inv;
+      HIPC(up(const_cast<double*>(mg.coarse_inv), dense, s));
+      if (mixed) HIPC(up(const_cast<float*>(mg.coarse_inv32), f32(dense), s));
     }
     HIPC(hipStreamSynchronize(s));
   }
@@ -1813,11 +1806,11 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
           if (l == 0) {  // transfers of the finest level
             b += (L.P.nnz() + L.R.nnz()) * (vb + 4.0) + (2.0 * L.A.n + 2.0 * nn) * vb;
           } else {  // restriction with the smoothing step, prolongation with the post-smoothing
-            b += (L.A.nnz() + L.R.nnz() + L.RA.nnz() + L.AP.nnz() + L.P.nnz()) * (vb + 4.0) +
-                 5.0 * L.A.n * vb + 2.0 * nn * vb;
+            const bool fold = l + 2 == H.lv.size() && !H.coarse_fold.empty();
+            b += ((fold ? 0 : L.Rs.nnz()) + L.Ps.nnz()) * (vb + 4.0) + 3.0 * L.A.n * vb + 2.0 * nn * vb;
           }
         }
-        b += H.n_coarse * (double)H.n_coarse * vb;
+        b += (double)std::max(H.coarse_inv.size(), H.coarse_fold.size()) * vb;
         break;
       }
       case 5:    // F in, face coefficients out; Jinv; the packed local inverse (FE4: and det J,

@@ -56,27 +56,22 @@ template <typename V>
 struct MgVec { V *b, *x, *y, *d, *r, *z; };
 struct MgDev {
   int nlev = 0;
-  DevCsr A[kMaxLev];   // A[0] unused (the BSR facet matrix)
-  DevCsr P[kMaxLev];   // prolongation from level l+1 to level l (rows: level l)
-  DevCsr R[kMaxLev];   // restriction P^T
-  DevCsr AP[kMaxLev];  // A P and R A on levels >= 1 (fused transfers; unused on level 0)
-  DevCsr RA[kMaxLev];
-  const double* dinv[kMaxLev];
-  const float* dinv32[kMaxLev];
-  CheB cheb[kMaxLev];
+  DevCsr P0, R0;       // prolongation to the finest level and restriction P0^T
+  DevCsr Rs[kMaxLev];  // levels >= 1: AmgLevel::Rs and Ps
+  DevCsr Ps[kMaxLev];
+  CheB cheb;  // of the finest level
   MgVec<double> v64[kMaxLev];
   MgVec<float> v32[kMaxLev];
   int n_coarse = 0;
+  // the dense solve: from the coarsest level's right-hand side, or (AmgHierarchy::coarse_fold)
+  // from that of the level above
+  bool fold = false;
   const double* coarse_inv = nullptr;
   const float* coarse_inv32 = nullptr;
 };
 template <typename V>
 inline const MgVec<V>& mg_vec(const MgDev& m, int l) {
   if constexpr (sizeof(V) == 8) return m.v64[l]; else return m.v32[l];
-}
-template <typename V>
-inline const V* mg_dinv(const MgDev& m, int l) {
-  if constexpr (sizeof(V) == 8) return m.dinv[l]; else return m.dinv32[l];
 }
 // z = V-cycle(b) (one smoothed-aggregation multigrid cycle run in type V on PCG vectors
 // of type VB); writes the (b, z) partial of each facet block into rz[2*block].  Every

@@ -10,6 +10,8 @@
 // block reduces its lanes with wavefront shuffles and LDS and writes one partial; the next
 // kernel's blocks each sum all partials in the same fixed order.  (A per-block device-scope
 // release fence would write back the XCD's whole L2 on every block.)
+#include <climits>
+
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -1364,7 +1366,7 @@ __global__ __launch_bounds__(kBlk) void k_finalize_ir(const double* __restrict__
 // ---------------------------------------------------------------------------------------
 // Finest level: Chebyshev(2) smoothing with the point-Jacobi scaling D^{-1}, residual,
 // restriction R = P^T, coarse correction, prolongation, Chebyshev(2) post-smoothing (the
-// coarser levels use degree 1, see k_mgc_restrict).
+// coarser levels use degree 1, see k_mgc_apply).
 // With th, de the centre and half-width of the smoothing interval, c1 = rho1 rho0 and
 // c2 = 2 rho1 / de (rho0 = de/th, rho1 = 1/(2 th/de - rho0)):
 //   pre  (x0 = 0):  x1 = D^{-1} b / th,  x2 = (1 + c1) x1 + c2 D^{-1} (b - A x1)
@@ -1577,46 +1579,23 @@ __device__ inline V csr_row_group(const DevCsr& A, const V* __restrict__ vals, i
 
 // Coarse levels (below the finest) smooth with one Chebyshev(1) step, i.e. damped Jacobi
 // with weight 1/th, before and after the coarse correction: x1 = D^{-1} b / th, and after
-// the correction x3 = x1 + P e, z = x3 + D^{-1} (b - A x3) / th.  Two kernels per level:
-//   restriction of the smoothed residual, b_c = R (b - A x1) = R b - (R A) x1, with R A
-//   precomputed and x1 formed on the fly (neither x1 nor the residual is stored);
-//   prolongation fused with the post-smoothing step, A x3 = A x1 + (A P) e.
+// the correction x3 = x1 + P e, z = x3 + D^{-1} (b - A x3) / th.  Everything in it is linear in b
+// and e, so a level is two products with matrices formed once (AmgLevel::Rs, Ps): the restricted
+// residual of x1 from b, and z from [b; e].  Bound by the round trips matrix - columns - vector
+// of their short rows: one chain a kernel, where the separate R, R A and A, A P, P took two and
+// three.  256^2 BDM_2 (36304, 7228 and 852 unknowns): corrections 9.1 and 5.1 us before, 7.1 and 4.7
+// now, restriction 5.1, 4.7 now; the last restriction and the dense solve 4.5 and 4.3, one kernel
+// of 6.3 now.  128^2 (8.8k, 1764 and 238 unknowns) adjoint step: 941 -> 851 us.
+// y = M [b; e], nb the length of b.
 template <int LPR, typename V>
-__global__ __launch_bounds__(kBlk) void k_mgc_restrict(DevCsr R, DevCsr RA, const V* __restrict__ b,
-                                                       const V* __restrict__ dinv, CheB cb, V* __restrict__ bc,
-                                                       const PcgScalars* sc) {
+__global__ __launch_bounds__(kBlk) void k_mgc_apply(DevCsr M, int nb, const V* __restrict__ b,
+                                                    const V* __restrict__ e, V* __restrict__ y,
+                                                    const PcgScalars* sc) {
   const bool live = sc->done == PCG_RUNNING;  // tested before the store only
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   const int i = g / LPR, sub = g % LPR;
-  const V ith = (V)(1.0 / cb.th);
-  V s = 0;
-  if (i < R.n)
-    s = ell_part<LPR, V>(R, i, sub, [&](int c) { return b[c]; }) -
-        ell_part<LPR, V>(RA, i, sub, [&](int c) { return dinv[c] * b[c] * ith; });
-  s = group_sum<LPR, V>(s);
-  if (live && i < R.n && sub == 0) bc[i] = s;
-}
-
-template <int LPR, typename V>
-__global__ __launch_bounds__(kBlk) void k_mgc_post(DevCsr A, DevCsr AP, DevCsr P, const V* __restrict__ dinv,
-                                                   const V* __restrict__ b, const V* __restrict__ e,
-                                                   V* __restrict__ z, CheB cb, const PcgScalars* sc) {
-  const bool live = sc->done == PCG_RUNNING;  // tested before the store only
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = g / LPR, sub = g % LPR;
-  const V ith = (V)(1.0 / cb.th);
-  V pe = 0, ax = 0;
-  if (i < A.n) {
-    pe = ell_part<LPR, V>(P, i, sub, [&](int c) { return e[c]; });
-    ax = ell_part<LPR, V>(A, i, sub, [&](int c) { return dinv[c] * b[c] * ith; }) +
-         ell_part<LPR, V>(AP, i, sub, [&](int c) { return e[c]; });
-  }
-  pe = group_sum<LPR, V>(pe);
-  ax = group_sum<LPR, V>(ax);
-  if (live && i < A.n && sub == 0) {
-    const V x1 = dinv[i] * b[i] * ith;
-    z[i] = (x1 + pe) + dinv[i] * (b[i] - ax) * ith;
-  }
+  const V s = csr_row_group<LPR, V>(M, csr_vals<V>(M), i, sub, [&](int c) { return c < nb ? b[c] : e[c - nb]; });
+  if (live && i < M.n && sub == 0) y[i] = s;
 }
 
 // y = M x (restriction with M = R), or y = y0 + M x (prolongation-add, add != 0).
@@ -1759,23 +1738,26 @@ __global__ __launch_bounds__(kBlk) void k_partial_dot(long n, const V* __restric
   }
 }
 
-// Coarsest level: x = Ainv b with the dense (regularised) inverse; a wavefront per row.
+// Coarsest level: x = M b with the dense (regularised) inverse, or that times the restriction
+// from the level above (n rows, m columns); a block per row, so that a lane has few entries and
+// all their loads in flight (852 rows of 7228: a wavefront per row 11.8 us).
 template <typename V>
-__global__ __launch_bounds__(kBlk) void k_dense_mv(int n, const double* __restrict__ Ainv, const float* __restrict__ Ainv32,
-                                                   const V* __restrict__ b, V* __restrict__ x, const PcgScalars* sc) {
+__global__ __launch_bounds__(kBlk) void k_dense_mv(int n, int m, const double* __restrict__ M64,
+                                                   const float* __restrict__ M32, const V* __restrict__ b,
+                                                   V* __restrict__ x, const PcgScalars* sc) {
   const bool live = sc->done == PCG_RUNNING;  // tested before the store only
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = g >> 6, lane = g & 63;
-  const V* M = (sizeof(V) == 8) ? (const V*)Ainv : (const V*)Ainv32;
-  V s = 0;
-  if (i < n)  // entries lane, lane + 64, ...; the column index is the entry's own
-    s = ell_batched<64, 8, V>((size_t)lane, lane_entries<64>(n, lane), [&](size_t k, int& c, V& v) {
-      c = (int)k;
-      v = M[(size_t)i * n + k];
-    }, [&](int c) { return b[c]; });
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (live && i < n && lane == 0) x[i] = s;
+  const int i = blockIdx.x, t = threadIdx.x;
+  const V* __restrict__ M = ((sizeof(V) == 8) ? (const V*)M64 : (const V*)M32) + (size_t)i * m;
+  // entries t, t + kBlk, ...; the column index is the entry's own
+  V s = ell_batched<kBlk, 8, V>((size_t)t, m > t ? (m - t + kBlk - 1) / kBlk : 0, [&](size_t k, int& c, V& v) {
+    c = (int)k;
+    v = M[k];
+  }, [&](int c) { return b[c]; });
+  s = group_sum<64, V>(s);
+  __shared__ V sh[kBlk / 64];
+  if ((t & 63) == 0) sh[t >> 6] = s;
+  __syncthreads();
+  if (live && t == 0) x[i] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 __global__ void k_add_f32(long n, const float* __restrict__ x, double* __restrict__ y) {
@@ -2527,36 +2509,27 @@ static void vcycle_body(int NF, const DevGeo& g, const DevBsr& A, const MgDev& m
   const MgVec<V>& v0 = mg_vec<V>(mg, 0);
   DFDG_DISPATCH_NFS_VOID(NF, A.ns, hipLaunchKernelGGL((k_mg0_resid<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A,
                                                        b, (const V*)v0.x, v0.r, sc));
-  csr_apply<V>(mg.R[0], (const V*)v0.r, (const V*)nullptr, mg_vec<V>(mg, 1).b, 0, sc, s);
-  for (int l = 1; l < L - 1; ++l) {
-    const MgVec<V>& v = mg_vec<V>(mg, l);
-    const DevCsr& R = mg.R[l];
-    const DevCsr& RA = mg.RA[l];
-    DFDG_DISPATCH_LPR(std::max(R.lpr, RA.lpr),
-                      hipLaunchKernelGGL((k_mgc_restrict<LP, V>), dim3(nblk((long)R.n * LP, kBlk)), dim3(kBlk), 0, s, R,
-                                         RA, (const V*)v.b, mg_dinv<V>(mg, l), mg.cheb[l], mg_vec<V>(mg, l + 1).b, sc));
-  }
-  {
-    const MgVec<V>& vc = mg_vec<V>(mg, L - 1);
-    hipLaunchKernelGGL((k_dense_mv<V>), dim3(nblk((long)mg.n_coarse * 64, kBlk)), dim3(kBlk), 0, s, mg.n_coarse,
-                       mg.coarse_inv, mg.coarse_inv32, (const V*)vc.b, vc.z, sc);
-  }
+  csr_apply<V>(mg.R0, (const V*)v0.r, (const V*)nullptr, mg_vec<V>(mg, 1).b, 0, sc, s);
+  auto apply = [&](const DevCsr& M, int nb, const V* bb, const V* e, V* y) {
+    DFDG_DISPATCH_LPR(M.lpr, hipLaunchKernelGGL((k_mgc_apply<LP, V>), dim3(nblk((long)M.n * LP, kBlk)), dim3(kBlk), 0,
+                                                s, M, nb, bb, e, y, sc));
+  };
+  const int last = mg.fold ? L - 2 : L - 1;  // the level whose right-hand side the dense solve takes
+  for (int l = 1; l < last; ++l)
+    apply(mg.Rs[l], INT_MAX, (const V*)mg_vec<V>(mg, l).b, nullptr, mg_vec<V>(mg, l + 1).b);
+  hipLaunchKernelGGL((k_dense_mv<V>), dim3(mg.n_coarse), dim3(kBlk), 0, s, mg.n_coarse,
+                     mg.fold ? mg.Ps[last].n : mg.n_coarse, mg.coarse_inv, mg.coarse_inv32,
+                     (const V*)mg_vec<V>(mg, last).b, mg_vec<V>(mg, L - 1).z, sc);
   for (int l = L - 2; l >= 1; --l) {
     const MgVec<V>& v = mg_vec<V>(mg, l);
-    const DevCsr& Al = mg.A[l];
-    const DevCsr& AP = mg.AP[l];
-    const DevCsr& P = mg.P[l];
-    DFDG_DISPATCH_LPR(std::max(Al.lpr, std::max(AP.lpr, P.lpr)),
-                      hipLaunchKernelGGL((k_mgc_post<LP, V>), dim3(nblk((long)Al.n * LP, kBlk)), dim3(kBlk), 0, s, Al,
-                                         AP, P, mg_dinv<V>(mg, l), (const V*)v.b, (const V*)mg_vec<V>(mg, l + 1).z, v.z,
-                                         mg.cheb[l], sc));
+    apply(mg.Ps[l], mg.Ps[l].n, (const V*)v.b, (const V*)mg_vec<V>(mg, l + 1).z, v.z);
   }
-  csr_apply<V>(mg.P[0], (const V*)mg_vec<V>(mg, 1).z, (const V*)v0.x, v0.x, 1, sc, s);
+  csr_apply<V>(mg.P0, (const V*)mg_vec<V>(mg, 1).z, (const V*)v0.x, v0.x, 1, sc, s);
   DFDG_DISPATCH_NFS_VOID(NF, A.ns, {
     hipLaunchKernelGGL((k_mg0_post1<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b, (const V*)v0.x, v0.y, v0.d,
-                       mg.cheb[0], sc);
+                       mg.cheb, sc);
     hipLaunchKernelGGL((k_mg0_post2<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b, (const V*)v0.y,
-                       (const V*)v0.d, z, mg.cheb[0], rz, sc);
+                       (const V*)v0.d, z, mg.cheb, rz, sc);
   });
 }
 
@@ -2567,13 +2540,13 @@ hipError_t launch_vcycle(int NF, const DevGeo& g, const DevBsr& A, const MgDev& 
   const int L = mg.nlev;
   const MgVec<V>& v0 = mg_vec<V>(mg, 0);
   if (L == 1) {  // the facet matrix itself is the coarsest level: exact (regularised) solve in VB
-    hipLaunchKernelGGL((k_dense_mv<VB>), dim3(nblk((long)mg.n_coarse * 64, kBlk)), dim3(kBlk), 0, s, mg.n_coarse,
-                       mg.coarse_inv, mg.coarse_inv32, b, z, sc);
+    hipLaunchKernelGGL((k_dense_mv<VB>), dim3(mg.n_coarse), dim3(kBlk), 0, s, mg.n_coarse,
+                       mg.n_coarse, mg.coarse_inv, mg.coarse_inv32, b, z, sc);
     hipLaunchKernelGGL((k_partial_dot<VB>), dim3(G), dim3(kBlk), 0, s, (long)g.E * NF, b, (const VB*)z, rz, sc);
     return hipGetLastError();
   }
   DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_mg0_pre<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b,
-                                                 v0.x, mg.cheb[0], sc));
+                                                 v0.x, mg.cheb, sc));
   vcycle_body<V, VB>(NF, g, A, mg, b, z, rz, sc, s);
   return hipGetLastError();
 }
@@ -2591,7 +2564,7 @@ hipError_t launch_pcg_iteration_mg(int NF, const DevGeo& g, const DevBsr& A, con
   double* out = pb.rz[it & 1];
   DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_pcg_upd_mg0_pre<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A,
                                           (const VB*)p_new, (const VB*)Sp, x, r_old, r_new, mg_vec<V>(mg, 0).x,
-                                          mg.cheb[0], pb.sc, prev, (const double*)pb.pq, out));
+                                          mg.cheb, pb.sc, prev, (const double*)pb.pq, out));
   vcycle_body<V, VB>(NF, g, A, mg, (const VB*)r_new, z, out, pb.sc, s);
   return hipGetLastError();
 }
