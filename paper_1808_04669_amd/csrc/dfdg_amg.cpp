@@ -546,6 +546,27 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
       for (int j = 0; j < nc; ++j)
         D[(size_t)i * nc + j] += (-Db[i] * B[j] - B[i] * Db[j] + B[i] * B[j] * bDb / bb) / bb;
   }
+  if (H.lv.size() >= 2) {
+    const Csr& P = H.lv[0].P;
+    const int nf0 = P.n / E;
+    std::vector<int> seen(P.m, -1), count(P.m, 0);
+    H.p0_ptr.assign(E + 1, 0);
+    H.p0_col.clear();
+    H.p0_col.reserve(P.nnz() / nf0);
+    H.p0_w = 0;
+    for (int F = 0; F < E; ++F) {
+      for (int k = P.ptr[F * nf0]; k < P.ptr[(F + 1) * nf0]; ++k) {
+        const int c = P.col[k];
+        if (seen[c] == F) continue;
+        seen[c] = F;
+        ++count[c];
+        H.p0_col.push_back(c);
+      }
+      H.p0_ptr[F + 1] = (int)H.p0_col.size();
+      H.p0_w = std::max(H.p0_w, H.p0_ptr[F + 1] - H.p0_ptr[F]);
+    }
+    H.p0_wr = *std::max_element(count.begin(), count.end());
+  }
   H.coarse_inv = std::move(D);
   H.n_coarse = nc;
   H.coarse_fold.clear();

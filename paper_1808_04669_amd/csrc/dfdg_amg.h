@@ -34,6 +34,9 @@ struct AmgHierarchy {
   std::vector<AmgLevel> lv;          // lv[0] = fine operator S
   std::vector<double> coarse_inv;    // dense pseudo-inverse (n_c x n_c) of the coarsest operator
   int n_coarse = 0;
+  // finest prolongator by facets: the columns of facet F's rows, p0_ptr[F] .. p0_ptr[F + 1]
+  std::vector<int> p0_ptr, p0_col;
+  int p0_w = 0, p0_wr = 0;           // the most columns of a facet, and facets of a column
   // with three levels or more: coarse_inv Rs of the level above (n_c x its unknowns), if within
   // kAmgFoldValues
   std::vector<double> coarse_fold;

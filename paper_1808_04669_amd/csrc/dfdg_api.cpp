@@ -524,44 +524,50 @@ static void carve(dfdg_ctx* ctx, char* base) {
   mg = MgDev{};
   const AmgHierarchy& H = ctx->H;
   mg.nlev = (int)H.lv.size();
-  // lanes per row: the largest power of two not above the mean row length / div (<= 64)
-  // returns whether the rows were packed (decided from the matrix, never from a pointer:
-  // the sizing pass carves with a null base)
-  auto take_csr = [&](const Csr& M, DevCsr& D, int div, bool pack = false, bool half = false) -> bool {
+  // lanes per row: the largest power of two not above the mean row length (<= 64)
+  auto take_csr = [&](const Csr& M, DevCsr& D) {
     D.n = M.n;
     const double avg = M.n ? (double)M.nnz() / M.n : 1.0;
     D.lpr = 1;
-    while (D.lpr < 64 && 2 * D.lpr * div <= avg) D.lpr *= 2;
+    while (D.lpr < 64 && 2 * D.lpr <= avg) D.lpr *= 2;
     int wmax = 1;
     for (int i = 0; i < M.n; ++i) wmax = std::max(wmax, M.ptr[i + 1] - M.ptr[i]);
-    // short rows: one lane reads its whole row at once (16-byte loads; rows of up to 16
-    // entries when they are packed into FP16 with 16-bit columns, 4 entries per load)
-    const bool pack16 = pack && wmax <= 16 && M.m < 65536;
-    if (wmax <= 4 || pack16) D.lpr = 1;
-    D.w = wmax <= 4 ? 4 : pack16 ? (wmax + 3) / 4 * 4 : (wmax + D.lpr - 1) / D.lpr * D.lpr;
+    D.w = (wmax + D.lpr - 1) / D.lpr * D.lpr;
     const size_t ne = (size_t)M.n * D.w;
     D.col = c.take<int>(ne);
     D.val = c.take<double>(ne);
     D.val32 = f32 ? c.take<float>(ne) : nullptr;
-    const bool packed = pack && D.w % 4 == 0 && D.w <= 16 && D.lpr == 1 && M.m < 65536;
-    D.pk = packed ? c.take<uint32_t>((size_t)D.w * M.n) : nullptr;
-    D.val16 = half ? c.take<uint16_t>(ne) : nullptr;
-    D.pscale = 1.0f;
-    return packed;
   };
+  if (mg.nlev > 1) {
+    // the finest level's transfers, in an FP32 cycle with FP16 values of S in FP16 as well, where
+    // a facet has at most 16 columns and their ids fit 16 bits; restriction: four or more facets of
+    // a row to a lane (256^2 BDM_2, 512^2 BDM_3: 6.8 and 29.6 us; two or more: 8.1 and 31.9)
+    DevXfer& X = mg.X0;
+    X.E = (int)E;
+    X.n = H.lv[1].A.n;
+    X.w = (H.p0_w + 3) / 4 * 4;
+    X.lpr = 4;
+    while (X.lpr < 64 && 4l * X.lpr * X.n <= (long)H.p0_col.size()) X.lpr *= 2;
+    X.wr = (H.p0_wr + X.lpr - 1) / X.lpr * X.lpr;
+    X.half = f16 && H.p0_w <= 16 && X.n < 65536;
+    X.pscale = 1.0f;
+    const size_t np = (size_t)X.w * E, nr = (size_t)X.n * X.wr;
+    X.pcol = c.take<int>(np);
+    X.pval = c.take<double>(np * NF);
+    X.rcol = c.take<int>(nr);
+    X.rval = c.take<double>(nr * NF);
+    X.pval32 = f32 && !X.half ? c.take<float>(np * NF) : nullptr;
+    X.rval32 = f32 && !X.half ? c.take<float>(nr * NF) : nullptr;
+    X.pcol16 = X.half ? c.take<uint32_t>(np / 2) : nullptr;
+    X.pval16 = X.half ? c.take<uint32_t>(np / 2 * NF) : nullptr;
+    X.rval16 = X.half ? c.take<uint32_t>(nr * ((NF + 1) / 2)) : nullptr;
+  }
   for (int l = 0; l < mg.nlev; ++l) {
     const AmgLevel& L = H.lv[l];
     const long n = L.A.n;
-    if (l == 0 && mg.nlev > 1) {
-      // the restriction from the finest level gathers from the largest vector: a few
-      // lanes per row (8 for rows of ~40 entries), each with one batch of entries, keep
-      // more of those gathers in flight;
-      // the finest-level transfers of an FP32 cycle in FP16 (P packed, R = P^T rounded alike)
-      const bool packed = take_csr(L.P, mg.P0, 1, f16);
-      take_csr(L.R, mg.R0, 4, false, packed);
-    } else if (l > 0 && l < mg.nlev - 1) {
-      take_csr(L.Rs, mg.Rs[l], 1);
-      take_csr(L.Ps, mg.Ps[l], 1);
+    if (l > 0 && l < mg.nlev - 1) {
+      take_csr(L.Rs, mg.Rs[l]);
+      take_csr(L.Ps, mg.Ps[l]);
     }
     MgVec<double>& v = mg.v64[l];
     v.b = (l > 0) ? c.take<double>(n) : nullptr;
@@ -733,7 +739,7 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
     for (double v : h.vals) smax = std::max(smax, std::fabs(v));
     if (!(smax > 0)) smax = 1;
     ctx->A.scale16 = (float)smax;
-    HIPC(launch_pack_half_pairs(ctx->NF, ctx->A.ns, ctx->E, ctx->A.vals, 1.0 / smax, const_cast<uint32_t*>(ctx->A.vals16),
+    HIPC(launch_half_planes((long)ctx->A.ns * ctx->NF * ctx->NF, ctx->E, ctx->A.vals, 1.0 / smax, const_cast<uint32_t*>(ctx->A.vals16),
                                 s));
   }
   {
@@ -763,26 +769,60 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
       HIPC(up(const_cast<int*>(D.col), keep_i.back(), s));
       HIPC(up(const_cast<double*>(D.val), ve, s));
       if (mixed) HIPC(up(const_cast<float*>(D.val32), f32(ve), s));
-      if (D.pk || D.val16) {  // the same values in P and R: the same scale and rounding
-        double vmax = 0;
-        for (double x : ve) vmax = std::max(vmax, std::fabs(x));
-        if (!(vmax > 0)) vmax = 1;
-        D.pscale = (float)vmax;
-        if (D.pk) HIPC(launch_pack_rows(M.n, D.w, D.col, D.val, 1.0 / vmax, const_cast<uint32_t*>(D.pk), s));
-        if (D.val16)
-          HIPC(launch_to_half((long)ve.size(), D.val, 1.0 / vmax, const_cast<uint16_t*>(D.val16), s));
-      }
       return DFDG_OK;
     };
     keep.reserve(8 * kMaxLev + 2);
     for (int l = 0; l < mg.nlev; ++l) {
       const AmgLevel& L = H.lv[l];
-      if (l == 0 && mg.nlev > 1) {
-        if (int rc = up_csr(L.P, mg.P0)) return rc;
-        if (int rc = up_csr(L.R, mg.R0)) return rc;
-      } else if (l > 0 && l < mg.nlev - 1) {
+      if (l > 0 && l < mg.nlev - 1) {
         if (int rc = up_csr(L.Rs, mg.Rs[l])) return rc;
         if (int rc = up_csr(L.Ps, mg.Ps[l])) return rc;
+      }
+    }
+    if (mg.nlev > 1) {
+      const DevXfer& X = mg.X0;
+      const Csr& P = H.lv[0].P;
+      const int NF = (int)ctx->NF, E = X.E;
+      const size_t np = (size_t)X.w * E, nr = (size_t)X.n * X.wr;
+      keep_i.emplace_back(np, 0);
+      std::vector<int>& pc = keep_i.back();
+      keep_i.emplace_back(nr, 0);
+      std::vector<int>& rc = keep_i.back();
+      keep_d.emplace_back(np * NF, 0.0);
+      std::vector<double>& pv = keep_d.back();
+      keep_d.emplace_back(nr * NF, 0.0);
+      std::vector<double>& rv = keep_d.back();
+      std::vector<int> fill(X.n, 0);
+      double vmax = 0;
+      for (int F = 0; F < E; ++F) {
+        const int b = H.p0_ptr[F], len = H.p0_ptr[F + 1] - b;
+        for (int j = 0; j < X.w; ++j) pc[(size_t)j * E + F] = len ? H.p0_col[b + std::min(j, len - 1)] : 0;
+        for (int j = 0; j < len; ++j) rc[(size_t)H.p0_col[b + j] * X.wr + fill[H.p0_col[b + j]]++] = F;
+        for (int a = 0; a < NF; ++a)
+          for (int k = P.ptr[F * NF + a], j = 0; k < P.ptr[F * NF + a + 1]; ++k, ++j) {
+            if (j >= len || H.p0_col[b + j] != P.col[k])  // (rows of a facet mostly list the same columns)
+              j = (int)(std::find(H.p0_col.begin() + b, H.p0_col.begin() + b + len, P.col[k]) - H.p0_col.begin()) - b;
+            pv[((size_t)j * NF + a) * E + F] = P.val[k];
+            rv[((size_t)P.col[k] * X.wr + fill[P.col[k]] - 1) * NF + a] = P.val[k];
+            vmax = std::max(vmax, std::fabs(P.val[k]));
+          }
+      }
+      for (int i = 0; i < X.n; ++i)
+        for (int k = std::max(fill[i], 1); k < X.wr; ++k) rc[(size_t)i * X.wr + k] = rc[(size_t)i * X.wr + std::max(fill[i], 1) - 1];
+      HIPC(up(const_cast<int*>(X.pcol), pc, s));
+      HIPC(up(const_cast<int*>(X.rcol), rc, s));
+      HIPC(up(const_cast<double*>(X.pval), pv, s));
+      HIPC(up(const_cast<double*>(X.rval), rv, s));
+      if (X.pval32) {
+        HIPC(up(const_cast<float*>(X.pval32), f32(pv), s));
+        HIPC(up(const_cast<float*>(X.rval32), f32(rv), s));
+      }
+      if (X.half) {  // the same values in P and R: the same scale and rounding
+        if (!(vmax > 0)) vmax = 1;
+        mg.X0.pscale = (float)vmax;
+        HIPC(launch_half_planes((long)X.w * NF, E, X.pval, 1.0 / vmax, const_cast<uint32_t*>(X.pval16), s));
+        HIPC(launch_col_planes(X.w, E, X.pcol, const_cast<uint32_t*>(X.pcol16), s));
+        HIPC(launch_half_entries(NF, (long)nr, X.rval, 1.0 / vmax, const_cast<uint32_t*>(X.rval16), s));
       }
     }
     if (mg.nlev > 0) {

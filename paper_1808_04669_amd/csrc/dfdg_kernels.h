@@ -43,20 +43,27 @@ struct DevCsr {
   const int* col;
   const double* val;
   const float* val32;
-  // rows of 4, 8, 12 or 16 entries (w) in an FP32 cycle with fewer than 65536 columns: one 16-byte
-  // word per 4 entries of a row, 4 16-bit column ids then 4 FP16 values of val / pscale (or
-  // null)
-  const uint32_t* pk;
+};
+// The transfer between the finest level and the first coarse one by facets: the NF rows of a
+// facet share their columns.  Prolongation: per facet w columns (a multiple of 4), column- and
+// value-major over the facets, pcol [w][E], pval [w][NF][E]; restriction: per coarse row wr
+// facets (a multiple of lpr), rcol [n][wr], rval [n][wr][NF].  Shorter ones repeat a column with
+// values 0.  half: values in FP16, scaled by pscale and in pairs, two to a word (restriction: NF
+// rounded up to pairs), and columns of P in 16 bits, two to a word.
+struct DevXfer {
+  int E, n, w, wr, lpr;
+  bool half;
   float pscale;
-  // FP16 values / pscale in the padded layout (the finest-level restriction of an FP32
-  // cycle, rounded like the packed prolongation so that R = P^T holds exactly), or null
-  const uint16_t* val16;
+  const int *pcol, *rcol;
+  const double *pval, *rval;
+  const float *pval32, *rval32;
+  const uint32_t *pcol16, *pval16, *rval16;
 };
 template <typename V>
 struct MgVec { V *b, *x, *y, *d, *r, *z; };
 struct MgDev {
   int nlev = 0;
-  DevCsr P0, R0;       // prolongation to the finest level and restriction P0^T
+  DevXfer X0;
   DevCsr Rs[kMaxLev];  // levels >= 1: AmgLevel::Rs and Ps
   DevCsr Ps[kMaxLev];
   CheB cheb;  // of the finest level
@@ -223,14 +230,12 @@ hipError_t launch_pj_update(long n, int nb, const PjVecs& B, const PjVecs& SB, c
 // column nb of T and nrm[nb] from the partials of launch_pj_update
 hipError_t launch_pj_small(long n, int nb, int mode, const double* part, double* T, double* nrm, double* w,
                            hipStream_t s);
-// pk[4i..4i+3] = row i of a 4-wide padded matrix packed as above (columns < 65536).
-hipError_t launch_pack_rows(int n, int w, const int* col, const double* val, double inv_scale, uint32_t* pk,
-                             hipStream_t s);
-// out[i] = FP16 bits of x[i] * scale (round to nearest even).
-hipError_t launch_to_half(long n, const double* x, double scale, uint16_t* out, hipStream_t s);
-// S (FP64, [5][NF][NF][E]) times scale in FP16, two values per word (DevBsr::vals16)
-hipError_t launch_pack_half_pairs(int NF, int ns, int E, const double* vals, double scale, uint32_t* out,
-                                  hipStream_t s);
+// nv value planes of E each, times scale, in FP16 pairs of planes (out [(nv + 1) / 2][E]: DevBsr::vals16,
+// DevXfer::pval16); nv (even) column planes in 16-bit pairs; entries of NF values in pairs within
+// the entry (DevXfer::rval16).
+hipError_t launch_half_planes(long nv, long E, const double* vals, double scale, uint32_t* out, hipStream_t s);
+hipError_t launch_col_planes(long nv, long E, const int* cols, uint32_t* out, hipStream_t s);
+hipError_t launch_half_entries(int NF, long entries, const double* vals, double scale, uint32_t* out, hipStream_t s);
 
 // Allocation-free diagnostics: a static device scratch of kNoAllocDiagBlocks partials (one per
 // element block of the diagnostics kernel, i.e. meshes of up to 2097152 elements) plus the

@@ -1598,46 +1598,104 @@ __global__ __launch_bounds__(kBlk) void k_mgc_apply(DevCsr M, int nb, const V* _
   if (live && i < M.n && sub == 0) y[i] = s;
 }
 
-// y = M x (restriction with M = R), or y = y0 + M x (prolongation-add, add != 0).
-template <int LPR, typename V>
-__global__ __launch_bounds__(kBlk) void k_csr_apply(DevCsr M, const V* __restrict__ x, const V* __restrict__ y0,
-                                                    V* __restrict__ y, int add, const PcgScalars* sc) {
+// Transfers of the finest level (DevXfer), one facet or one part of a coarse row's facets at a
+// time: a column id and a vector gather serve the facet's NF rows.  H: the values' storage
+// (uint32_t: FP16 pairs).  Bound by the values' and columns' bytes; as scalar rows (a 16-byte word
+// per 4 entries of one row and a gather each) 32^3 BDM_2 took 46.6 us to prolong and 34 to
+// restrict (now 20.9 and 21.9), 256^2 BDM_2 7.9 and 7.1 (5.0 and 6.8), in FP32 at 512^2 BDM_3 59 and 38
+// (29.2 and 29.6).
+constexpr int kXferBlk = 64;  // a thread per facet: small blocks spread over the CUs
+template <int NF, typename V, typename H>
+__global__ __launch_bounds__(kXferBlk) void k_prolong0(DevXfer X, const H* __restrict__ val,
+                                                       const V* __restrict__ e, V* __restrict__ x,
+                                                       const PcgScalars* sc) {
   const bool live = sc->done == PCG_RUNNING;  // tested before the stores only
+  constexpr bool kHalf = sizeof(H) == 4 && !std::is_same<H, float>::value;
+  const size_t E = X.E;
+  const int F = xcd_block() * kXferBlk + threadIdx.x;
+  if (F >= X.E) return;
+  V s[NF], x0[NF];
+#pragma unroll
+  for (int a = 0; a < NF; ++a) {
+    s[a] = 0;
+    x0[a] = x[(size_t)F * NF + a];
+  }
+  for (int j = 0; j < X.w; j += 4) {
+    int c[4];
+    if constexpr (kHalf) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const uint32_t w = X.pcol16[(size_t)(j / 2 + q) * E + F];
+        c[2 * q] = w & 0xffffu;
+        c[2 * q + 1] = w >> 16;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c[q] = X.pcol[(size_t)(j + q) * E + F];
+    }
+    V m[4 * NF], ec[4];
+    if constexpr (kHalf) {
+      uint32_t w[2 * NF];
+#pragma unroll
+      for (int q = 0; q < 2 * NF; ++q) w[q] = val[((size_t)(j / 2) * NF + q) * E + F];
+#pragma unroll
+      for (int q = 0; q < 4 * NF; ++q) m[q] = (V)half_at(w, q);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4 * NF; ++q) m[q] = val[((size_t)j * NF + q) * E + F];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ec[q] = e[c[q]];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int a = 0; a < NF; ++a) s[a] += m[q * NF + a] * ec[q];
+  }
+  if (live)
+#pragma unroll
+    for (int a = 0; a < NF; ++a) x[(size_t)F * NF + a] = x0[a] + (kHalf ? s[a] * (V)X.pscale : s[a]);
+}
+template <int NF, int LPR, typename V, typename H>
+__global__ __launch_bounds__(kBlk) void k_restrict0(DevXfer X, const H* __restrict__ val, const V* __restrict__ r,
+                                                    V* __restrict__ y, const PcgScalars* sc) {
+  const bool live = sc->done == PCG_RUNNING;  // tested before the store only
+  constexpr bool kHalf = sizeof(H) == 4 && !std::is_same<H, float>::value;
+  constexpr int NW = kHalf ? (NF + 1) / 2 : NF;  // words of an entry
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   const int i = g / LPR, sub = g % LPR;
   V s = 0;
-  if (sizeof(V) == 4 && LPR == 1 && M.pk) {  // packed rows: one 16-byte load per 4 entries
-    if (i < M.n) {
-      const int ng = M.w >> 2;  // 1 to 4 groups of 4 entries
-      for (int gi = 0; gi < ng; ++gi) {
-        const uint4 w = *reinterpret_cast<const uint4*>(M.pk + ((size_t)i * ng + gi) * 4);
-        const _Float16 h0 = __builtin_bit_cast(_Float16, (uint16_t)(w.z & 0xffffu));
-        const _Float16 h1 = __builtin_bit_cast(_Float16, (uint16_t)(w.z >> 16));
-        const _Float16 h2 = __builtin_bit_cast(_Float16, (uint16_t)(w.w & 0xffffu));
-        const _Float16 h3 = __builtin_bit_cast(_Float16, (uint16_t)(w.w >> 16));
-        s += (V)h0 * x[w.x & 0xffffu] + (V)h1 * x[w.x >> 16] + (V)h2 * x[w.y & 0xffffu] + (V)h3 * x[w.y >> 16];
+  if (i < X.n) {
+    const int n = X.wr / LPR;  // entries of this lane
+    const size_t base = (size_t)i * X.wr + sub;
+    for (int k0 = 0; k0 < n; k0 += 2) {  // two at a time; the last one alone repeats with weight 0
+      int c[2];
+      H w[2][NW];
+      V rc[2][NF];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const size_t o = base + (size_t)min(k0 + u, n - 1) * LPR;
+        c[u] = X.rcol[o];
+#pragma unroll
+        for (int h = 0; h < NW; ++h) w[u][h] = val[o * NW + h];
       }
-      s *= (V)M.pscale;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int a = 0; a < NF; ++a) rc[u][a] = r[(size_t)c[u] * NF + a];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int a = 0; a < NF; ++a) {
+          V m;
+          if constexpr (kHalf) m = (V)half_at(w[u], a);
+          else m = w[u][a];
+          s += m * (k0 + u < n ? rc[u][a] : (V)0);
+        }
     }
-  } else if (LPR == 1 && M.w == 4) {  // rows of 4 entries, 16-byte aligned: vector loads
-    if (i < M.n) {
-      const int4 c = *reinterpret_cast<const int4*>(M.col + (size_t)i * 4);
-      const V* v = csr_vals<V>(M) + (size_t)i * 4;
-      s = v[0] * x[c.x] + v[1] * x[c.y] + v[2] * x[c.z] + v[3] * x[c.w];
-    }
-  } else if (sizeof(V) == 4 && M.val16) {
-    const _Float16* __restrict__ v16 = reinterpret_cast<const _Float16*>(M.val16);
-    const int* __restrict__ col = M.col;
-    if (i < M.n)
-      s = ell_sum<LPR, V>(M.w, sub, (size_t)i * M.w + sub, [&](size_t k, int& c, V& v) {
-        c = col[k];
-        v = (V)v16[k];
-      }, [&](int c) { return x[c]; });
-    s = group_sum<LPR, V>(s) * (V)M.pscale;
-  } else {
-    s = csr_row_group<LPR, V>(M, csr_vals<V>(M), i, sub, [&](int c) { return x[c]; });
   }
-  if (live && i < M.n && sub == 0) y[i] = add ? y0[i] + s : s;
+  s = group_sum<LPR, V>(s);
+  if (kHalf) s *= (V)X.pscale;
+  if (live && i < X.n && sub == 0) y[i] = s;
 }
 
 // ---- PCG update fused with the first smoothing step of the cycle ----------------------
@@ -2494,10 +2552,34 @@ int facet_grid_size(int E, int cap) {
     default: { constexpr int LP = 64; __VA_ARGS__; } break;        \
   }
 
+template <int NF, typename V, typename H>
+static void xfer_launch(const DevXfer& X, bool up, const H* val, const V* in, V* out, const PcgScalars* sc,
+                        hipStream_t s) {
+  if (up) {
+    hipLaunchKernelGGL((k_prolong0<NF, V, H>), dim3(nblk(X.E, kXferBlk)), dim3(kXferBlk), 0, s, X, val, in, out, sc);
+    return;
+  }
+  DFDG_DISPATCH_LPR(X.lpr, hipLaunchKernelGGL((k_restrict0<NF, LP, V, H>), dim3(nblk((long)X.n * LP, kBlk)), dim3(kBlk),
+                                              0, s, X, val, in, out, sc));
+}
+// out += P in (up), out = P^T in, between the finest level and the next
 template <typename V>
-static void csr_apply(const DevCsr& M, const V* x, const V* y0, V* y, int add, const PcgScalars* sc, hipStream_t s) {
-  DFDG_DISPATCH_LPR(M.lpr, hipLaunchKernelGGL((k_csr_apply<LP, V>), dim3(nblk((long)M.n * LP, kBlk)), dim3(kBlk), 0, s,
-                                              M, x, y0, y, add, sc));
+static void xfer(int NF, const DevXfer& X, bool up, const V* in, V* out, const PcgScalars* sc, hipStream_t s) {
+  auto run = [&](auto nf) {
+    constexpr int N = decltype(nf)::value;
+    if constexpr (sizeof(V) == 8) {
+      xfer_launch<N, V, double>(X, up, up ? X.pval : X.rval, in, out, sc, s);
+    } else {
+      if (X.half) xfer_launch<N, V, uint32_t>(X, up, up ? X.pval16 : X.rval16, in, out, sc, s);
+      else xfer_launch<N, V, float>(X, up, up ? X.pval32 : X.rval32, in, out, sc, s);
+    }
+  };
+  switch (NF) {
+    case 2: run(std::integral_constant<int, 2>{}); break;
+    case 3: run(std::integral_constant<int, 3>{}); break;
+    case 4: run(std::integral_constant<int, 4>{}); break;
+    default: run(std::integral_constant<int, 6>{}); break;
+  }
 }
 
 // Everything of a cycle after the first pre-smoothing step (x2 = pre(b) already in v0.x).
@@ -2509,7 +2591,7 @@ static void vcycle_body(int NF, const DevGeo& g, const DevBsr& A, const MgDev& m
   const MgVec<V>& v0 = mg_vec<V>(mg, 0);
   DFDG_DISPATCH_NFS_VOID(NF, A.ns, hipLaunchKernelGGL((k_mg0_resid<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A,
                                                        b, (const V*)v0.x, v0.r, sc));
-  csr_apply<V>(mg.R0, (const V*)v0.r, (const V*)nullptr, mg_vec<V>(mg, 1).b, 0, sc, s);
+  xfer<V>(NF, mg.X0, false, (const V*)v0.r, mg_vec<V>(mg, 1).b, sc, s);
   auto apply = [&](const DevCsr& M, int nb, const V* bb, const V* e, V* y) {
     DFDG_DISPATCH_LPR(M.lpr, hipLaunchKernelGGL((k_mgc_apply<LP, V>), dim3(nblk((long)M.n * LP, kBlk)), dim3(kBlk), 0,
                                                 s, M, nb, bb, e, y, sc));
@@ -2524,7 +2606,7 @@ static void vcycle_body(int NF, const DevGeo& g, const DevBsr& A, const MgDev& m
     const MgVec<V>& v = mg_vec<V>(mg, l);
     apply(mg.Ps[l], mg.Ps[l].n, (const V*)v.b, (const V*)mg_vec<V>(mg, l + 1).z, v.z);
   }
-  csr_apply<V>(mg.P0, (const V*)mg_vec<V>(mg, 1).z, (const V*)v0.x, v0.x, 1, sc, s);
+  xfer<V>(NF, mg.X0, true, (const V*)mg_vec<V>(mg, 1).z, v0.x, sc, s);
   DFDG_DISPATCH_NFS_VOID(NF, A.ns, {
     hipLaunchKernelGGL((k_mg0_post1<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b, (const V*)v0.x, v0.y, v0.d,
                        mg.cheb, sc);
@@ -2617,65 +2699,54 @@ hipError_t launch_axpby(long n, double a, const double* x, double b, double* y, 
   hipLaunchKernelGGL(k_axpby, dim3(nblk(n, kBlk)), dim3(kBlk), 0, s, n, a, x, b, y);
   return hipGetLastError();
 }
-__global__ void k_to_half(long n, const double* __restrict__ x, double scale, _Float16* __restrict__ out) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    out[i] = (_Float16)(float)(x[i] * scale);
+__device__ inline uint32_t half_pair(double lo, double hi) {
+  return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(float)lo) |
+         ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(float)hi) << 16);
 }
-
-__global__ void k_pack_half_pairs(int nv, int E, const double* __restrict__ vals, double scale,
-                                  uint32_t* __restrict__ out, long n) {
+// Value planes of E each, times scale, in FP16 pairs of planes; column planes in 16-bit pairs;
+// entries of NF values each in pairs within the entry (the last one padded).
+__global__ void k_half_planes(long nv, long E, const double* __restrict__ vals, double scale,
+                              uint32_t* __restrict__ out, long n) {
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
     const long j = i / E, F = i % E;
-    const _Float16 lo = (_Float16)(float)(vals[2 * j * E + F] * scale);
-    const _Float16 hi = (2 * j + 1 < nv) ? (_Float16)(float)(vals[(2 * j + 1) * E + F] * scale) : (_Float16)0.0f;
-    out[i] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
+    out[i] = half_pair(vals[2 * j * E + F] * scale, 2 * j + 1 < nv ? vals[(2 * j + 1) * E + F] * scale : 0.0);
+  }
+}
+__global__ void k_col_planes(long E, const int* __restrict__ cols, uint32_t* __restrict__ out, long n) {
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
+    const long j = i / E, F = i % E;
+    out[i] = (uint32_t)(cols[2 * j * E + F] & 0xffff) | ((uint32_t)cols[(2 * j + 1) * E + F] << 16);
+  }
+}
+__global__ void k_half_entries(int NF, const double* __restrict__ vals, double scale, uint32_t* __restrict__ out,
+                               long n) {
+  const int NW = (NF + 1) / 2;
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
+    const long o = i / NW;
+    const int h = (int)(i % NW);
+    out[i] = half_pair(vals[o * NF + 2 * h] * scale, 2 * h + 1 < NF ? vals[o * NF + 2 * h + 1] * scale : 0.0);
   }
 }
 
-// Packed rows of w = 4 ng entries (ng = 1..4): group g of row i is one 16-byte word (4 16-bit column ids,
-// then the 4 values in FP16, scaled), entries 4g .. 4g+3 of the padded row.
-__global__ void k_pack_rows(int n, int w, const int* __restrict__ col, const double* __restrict__ val,
-                            double inv_scale, uint32_t* __restrict__ pk) {
-  const long u = (long)blockIdx.x * blockDim.x + threadIdx.x;  // one group per thread
-  const int ng = w >> 2;
-  if (u >= (long)n * ng) return;
-  const long e = 4 * u;  // the group's first entry in the padded row-major layout
-  uint32_t q[4];
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-    q[k] = (uint32_t)(col[e + 2 * k] & 0xffff) | ((uint32_t)(col[e + 2 * k + 1] & 0xffff) << 16);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const uint16_t lo = __builtin_bit_cast(uint16_t, (_Float16)(float)(val[e + 2 * k] * inv_scale));
-    const uint16_t hi = __builtin_bit_cast(uint16_t, (_Float16)(float)(val[e + 2 * k + 1] * inv_scale));
-    q[2 + k] = (uint32_t)lo | ((uint32_t)hi << 16);
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) pk[4 * u + k] = q[k];
-}
-
-hipError_t launch_pack_rows(int n, int w, const int* col, const double* val, double inv_scale, uint32_t* pk,
-                            hipStream_t s) {
+hipError_t launch_half_planes(long nv, long E, const double* vals, double scale, uint32_t* out, hipStream_t s) {
+  const long n = (nv + 1) / 2 * E;
   if (n <= 0) return hipSuccess;
-  if (w % 4 != 0 || w < 4 || w > 16) return hipErrorInvalidValue;
-  const long groups = (long)n * (w / 4);
-  hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, n, w, col, val, inv_scale,
-                     pk);
+  hipLaunchKernelGGL(k_half_planes, dim3((unsigned)std::min<long>(nblk(n, 256), 65536)), dim3(256), 0, s, nv, E, vals,
+                     scale, out, n);
   return hipGetLastError();
 }
-
-hipError_t launch_to_half(long n, const double* x, double scale, uint16_t* out, hipStream_t s) {
+hipError_t launch_col_planes(long nv, long E, const int* cols, uint32_t* out, hipStream_t s) {
+  const long n = nv / 2 * E;
   if (n <= 0) return hipSuccess;
-  const long nb = std::min<long>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_to_half, dim3((unsigned)nb), dim3(256), 0, s, n, x, scale, reinterpret_cast<_Float16*>(out));
+  hipLaunchKernelGGL(k_col_planes, dim3((unsigned)std::min<long>(nblk(n, 256), 65536)), dim3(256), 0, s, E, cols, out,
+                     n);
   return hipGetLastError();
 }
-
-hipError_t launch_pack_half_pairs(int NF, int ns, int E, const double* vals, double scale, uint32_t* out,
-                                  hipStream_t s) {
-  const long n = (long)nPairs(NF, ns) * E;
-  const long nb = std::min<long>(nblk(n, 256), 65536);
-  hipLaunchKernelGGL(k_pack_half_pairs, dim3((unsigned)nb), dim3(256), 0, s, ns * NF * NF, E, vals, scale, out, n);
+hipError_t launch_half_entries(int NF, long entries, const double* vals, double scale, uint32_t* out, hipStream_t s) {
+  const long n = entries * ((NF + 1) / 2);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_half_entries, dim3((unsigned)std::min<long>(nblk(n, 256), 65536)), dim3(256), 0, s, NF, vals,
+                     scale, out, n);
   return hipGetLastError();
 }
 hipError_t launch_fill(long n, double v, double* y, hipStream_t s) {

@@ -82,3 +82,23 @@ def test_iterations_equal_the_cycle_written_out(dim, N, k, levels, mg_fp32):
     its = _pcg(A, M, g, rtol)
     print(dim, N, k, "levels", L, "iterations", info.iterations, its, flush=True)
     assert abs(info.iterations - its) <= 1
+
+
+@pytest.mark.parametrize("kw,tol", [(dict(mg_fp32=False), 1e-10), (dict(mg_fp32=True, mg_fine_fp16=False), 1e-4),
+                                    (dict(mg_fp32=True), 1e-2)], ids=["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("dim,N,k,mesh", [(2, 37, 1, {}), (2, 21, 2, dict(walls=True)), (2, 15, 3, dict(inout=True)),
+                                          (2, 24, 2, dict(mg_fine_smooth=3)), (3, 7, 1, dict(inout=True)),
+                                          (3, 6, 2, dict(walls=True))])
+def test_one_cycle_equals_the_cycle_written_out(dim, N, k, mesh, kw, tol):
+    """One cycle on a random vector: the rounding of FP64 and FP32 (1e-16 and 6e-8 a step, times
+    the coarse operator's condition, some 1e3) or of the FP16 values (5e-4 each)."""
+    _, s, _, _ = make_pair(N, k, dim=dim, oracle=False, precond="amg", facet_blocks=64, **mesh, **kw)
+    _, M, L = _cycle(s)
+    assert L >= 2
+    b = torch.randn(s.n_lambda, generator=torch.Generator().manual_seed(N), dtype=torch.float64)
+    db, dz = b.to(s.device), s.new_vector("lambda")
+    assert s._lib.dfdg_debug_vcycle(s._h, ctypes.c_void_p(db.data_ptr()), ctypes.c_void_p(dz.data_ptr())) == 0
+    z = M(b.numpy())
+    err = np.linalg.norm(dz.cpu().numpy() - z) / np.linalg.norm(z)
+    print(dim, N, k, mesh, kw, "levels", L, err, flush=True)
+    assert err < tol
