@@ -402,7 +402,9 @@ static void carve(dfdg_ctx* ctx, char* base) {
   g.T = (int)T;
   g.E = (int)E;
   // one thread per facet row, or two for split rows (facet_split)
-  g.fgrid = facet_grid_size((int)(E * facet_split((int)NF, d3slots(ctx))), ctx->prm.facet_blocks);
+  const int parts = (int)(E * facet_split((int)NF, d3slots(ctx)));
+  g.fgrid = facet_grid_size(parts, ctx->prm.facet_blocks);
+  g.fblk = facet_block_size(parts, ctx->prm.facet_blocks);
   const long dm = ctx->dim, nfac = dm + 1;
   g.Jinv = c.take<double>(dm * dm * T);
   g.detJ = c.take<double>(T);

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kBlk) void k_el_dot(long n, const double* __restric
                                                  double* __restrict__ rz, const PcgScalars* sc) {
   if (sc->done != PCG_RUNNING) return;
   double v[1] = {0}, t[1];
-  for (long i = (long)blockIdx.x * kBlk + threadIdx.x; i < n; i += (long)gridDim.x * kBlk) v[0] += r[i] * z[i];
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) v[0] += r[i] * z[i];
   block_sum_values<1>(v, t);
   if (threadIdx.x == 0) rz[2 * blockIdx.x] = t[0];
 }
@@ -370,7 +370,7 @@ hipError_t launch_elim_apply(const ElimDev& D, const DevGeo& g, const double* r,
                      g.fgrid, sc);
   hipLaunchKernelGGL(k_el_top, dim3((n + kTopRows - 1) / kTopRows), dim3(64 * kTopRows), top, s, D, r, z, csc);
   hipLaunchKernelGGL(k_el_backward, dim3(D.nc, (D.maxB + rows - 1) / rows), dim3(kBlk), front, s, D, r, z, rows, csc);
-  hipLaunchKernelGGL(k_el_dot, dim3(g.fgrid), dim3(kBlk), 0, s, (long)g.E * NF, r, (const double*)z, rz, csc);
+  hipLaunchKernelGGL(k_el_dot, dim3(g.fgrid), dim3(g.fblk), 0, s, (long)g.E * NF, r, (const double*)z, rz, csc);
   return hipGetLastError();
 }
 

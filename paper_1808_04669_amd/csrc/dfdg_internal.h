@@ -116,7 +116,7 @@ bool spd_inverse(int n, double* A);
 // ---- device-side views --------------------------------------------------------------
 struct DevGeo {
   int T, E;
-  int fgrid;            // blocks of the facet-row kernels (grid-stride loops over the rows)
+  int fgrid, fblk;      // blocks of the facet-row kernels (grid-stride loops over the rows), their threads
   // triangles unless stated; tetrahedra: Jinv [9][T] at (3r+j)*T + t, per-face arrays
   // [4][T], code bits 0-1 neighbour's local face, 2-4 the permutation p (0..5) carrying
   // this element's face vertices to the neighbour's, bit 5 this element is the R side;

@@ -27,8 +27,9 @@ struct PcgBufs {
   double* pq;      // [G][2] (p,Sp), (z,Sp) partials (z the normalised kernel vector of S)
   double* pj[2];   // [G][6] partials of launch_pcg_jacobi
 };
-// G: blocks of the facet kernels, ceil(E/256) up to 1024, or at most cap (> 0)
-int facet_grid_size(int E, int cap);
+// G: blocks of the facet kernels for E facets' row parts, up to 1024, or at most cap (> 0)
+int facet_grid_size(int parts, int cap);
+int facet_block_size(int parts, int cap);  // their threads
 
 // Multigrid hierarchy on the device (level 0 = the BSR facet matrix itself).
 constexpr int kMaxLev = 16;

@@ -634,10 +634,6 @@ __global__ __launch_bounds__(kEBlk) void k_recover(DevGeo g, DevTabs tb, const F
 
 // Facet kernels run a grid-stride loop over facet rows on a grid of at most kMaxFacetGrid
 // blocks, so that the partial buffers (and the redundant reductions) stay small.
-__host__ __device__ inline int facet_grid(int E) {
-  const int g = (E + kBlk - 1) / kBlk;
-  return g < kMaxFacetGrid ? g : kMaxFacetGrid;
-}
 
 // g_F = q_{L,f_L} + q_{R,f_R}; partials (g,g), (zdef,g) and (q_L,q_L) + (q_R,q_R), the size
 // of the element contributions that the sum cancels.
@@ -2402,7 +2398,7 @@ hipError_t launch_recover(int K, bool fp32in, const DevGeo& g, const DevTabs& tb
 hipError_t launch_gather_g(int NF, const DevGeo& g, const double* q, double* gv, const PcgBufs& pb, double rtol,
                            int maxit, hipStream_t s) {
   const int G = g.fgrid;
-  DFDG_DISPATCH_NF(NF, hipLaunchKernelGGL((k_gather_g<NN>), dim3(G), dim3(kBlk), 0, s, g, q, gv, pb.gg));
+  DFDG_DISPATCH_NF(NF, hipLaunchKernelGGL((k_gather_g<NN>), dim3(G), dim3(g.fblk), 0, s, g, q, gv, pb.gg));
   hipLaunchKernelGGL(k_finalize_gather, dim3(1), dim3(kBlk), 0, s, (const double*)pb.gg, G, pb.sc, rtol, maxit);
   return hipGetLastError();
 }
@@ -2410,8 +2406,8 @@ hipError_t launch_gather_g(int NF, const DevGeo& g, const double* q, double* gv,
 hipError_t launch_deflate(int NF, const DevGeo& g, double* x, double* part, hipStream_t s) {
   const int G = g.fgrid;
   DFDG_DISPATCH_NF(NF, {
-    hipLaunchKernelGGL((k_zdot<NN>), dim3(G), dim3(kBlk), 0, s, g, (const double*)x, part);
-    hipLaunchKernelGGL((k_zdeflate<NN>), dim3(G), dim3(kBlk), 0, s, g, x, (const double*)part, G);
+    hipLaunchKernelGGL((k_zdot<NN>), dim3(G), dim3(g.fblk), 0, s, g, (const double*)x, part);
+    hipLaunchKernelGGL((k_zdeflate<NN>), dim3(G), dim3(g.fblk), 0, s, g, x, (const double*)part, G);
   });
   return hipGetLastError();
 }
@@ -2427,11 +2423,11 @@ hipError_t launch_pcg_init(int NF, bool bj, const DevGeo& g, const DevBsr& A, co
     hipError_t e = launch_deflate(NF, g, x, pb.gg, s);
     if (e != hipSuccess) return e;
   }
-  DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_pcg_init<NN, SS>), dim3(G), dim3(kBlk), 0, s, g, A, gv, x, r, z,
+  DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_pcg_init<NN, SS>), dim3(G), dim3(g.fblk), 0, s, g, A, gv, x, r, z,
                                                  p_old, (const PcgScalars*)pb.sc, pb.gg));
   DFDG_DISPATCH_NF(NF, {
-    if (bj) hipLaunchKernelGGL((k_pcg_init_defl<NN, true>), dim3(G), dim3(kBlk), 0, s, g, A, r, z, (const PcgScalars*)pb.sc, (const double*)pb.gg, pb.rz[0]);
-    else hipLaunchKernelGGL((k_pcg_init_defl<NN, false>), dim3(G), dim3(kBlk), 0, s, g, A, r, z, (const PcgScalars*)pb.sc, (const double*)pb.gg, pb.rz[0]);
+    if (bj) hipLaunchKernelGGL((k_pcg_init_defl<NN, true>), dim3(G), dim3(g.fblk), 0, s, g, A, r, z, (const PcgScalars*)pb.sc, (const double*)pb.gg, pb.rz[0]);
+    else hipLaunchKernelGGL((k_pcg_init_defl<NN, false>), dim3(G), dim3(g.fblk), 0, s, g, A, r, z, (const PcgScalars*)pb.sc, (const double*)pb.gg, pb.rz[0]);
   });
   return hipGetLastError();
 }
@@ -2447,7 +2443,7 @@ static hipError_t spmv_any(int NF, const DevGeo& g, const DevBsr& A, const V* z,
                                       it, form_Sp, s);
   }
   if (sizeof(V) == 4 && A.ns != kSlots) return hipErrorInvalidValue;  // FP32 copies: triangles only
-  DFDG_DISPATCH_NFS(NF, A.ns, DFDG_LAUNCH_TIMED((k_pcg_spmv<NN, SS, V, V>), dim3(G), dim3(kBlk), 0, s, g, A, z, p_old,
+  DFDG_DISPATCH_NFS(NF, A.ns, DFDG_LAUNCH_TIMED((k_pcg_spmv<NN, SS, V, V>), dim3(G), dim3(g.fblk), 0, s, g, A, z, p_old,
                                                 p_new, Sp, pb.sc, prev, prev2, pb.pq));
   return hipGetLastError();
 }
@@ -2464,9 +2460,9 @@ static hipError_t update_any(int NF, int pc, const DevGeo& g, const DevBsr& A, c
   const double* prev = pb.rz[(it - 1) & 1];
   double* out = pb.rz[it & 1];
   DFDG_DISPATCH_NF(NF, {
-    if (pc == 1) hipLaunchKernelGGL((k_pcg_update<NN, 1, V, V>), dim3(G), dim3(kBlk), 0, s, g, A, p, Sp, x, r, z, pb.sc, prev, (const double*)pb.pq, out);
-    else if (pc == 2) hipLaunchKernelGGL((k_pcg_update<NN, 2, V, V>), dim3(G), dim3(kBlk), 0, s, g, A, p, Sp, x, r, z, pb.sc, prev, (const double*)pb.pq, out);
-    else hipLaunchKernelGGL((k_pcg_update<NN, 0, V, V>), dim3(G), dim3(kBlk), 0, s, g, A, p, Sp, x, r, z, pb.sc, prev, (const double*)pb.pq, out);
+    if (pc == 1) hipLaunchKernelGGL((k_pcg_update<NN, 1, V, V>), dim3(G), dim3(g.fblk), 0, s, g, A, p, Sp, x, r, z, pb.sc, prev, (const double*)pb.pq, out);
+    else if (pc == 2) hipLaunchKernelGGL((k_pcg_update<NN, 2, V, V>), dim3(G), dim3(g.fblk), 0, s, g, A, p, Sp, x, r, z, pb.sc, prev, (const double*)pb.pq, out);
+    else hipLaunchKernelGGL((k_pcg_update<NN, 0, V, V>), dim3(G), dim3(g.fblk), 0, s, g, A, p, Sp, x, r, z, pb.sc, prev, (const double*)pb.pq, out);
   });
   return hipGetLastError();
 }
@@ -2483,11 +2479,10 @@ hipError_t launch_pcg_update(int NF, int pc, const DevGeo& g, const DevBsr& A, c
 hipError_t launch_pcg_jacobi(int NF, const DevGeo& g, const DevBsr& A, const double* r_in, double* r_out,
                              const double* s_in, double* s_out, const double* p_in, double* p_out, double* x,
                              const PcgBufs& pb, int it, hipStream_t s) {
-  // one row part per thread and at most 4 partials per thread to sum; the smallest blocks that
-  // give that, since they spread the gathers over the most CUs (64^2 BDM_2, 12288 facets: 17.8 ms
-  // an RK4 step with blocks of 64, 33.3 with blocks of 256)
+  // one row part per thread, the smallest blocks that keep the partials few (64^2 BDM_2, 12288 facets: 17.8 ms an RK4 step with blocks of 64, 33.3
+  // with blocks of 256)
   const int units = g.E * facet_split(NF, A.ns);
-  const int B = units > 4 * 128 * 128 ? 256 : units > 4 * 64 * 64 ? 128 : 64;
+  const int B = units > kPartsPerThread * 128 * 128 ? 256 : units > kPartsPerThread * 64 * 64 ? 128 : 64;
   const int G = (units + B - 1) / B;
   if (G > kMaxFacetGrid) return hipErrorInvalidValue;
   auto run = [&](auto ker) {
@@ -2514,8 +2509,8 @@ hipError_t launch_pcg32_init(int NF, bool bj, const DevGeo& g, const DevBsr& A, 
                              float* z, float* p_old, const PcgBufs& pb, hipStream_t s) {
   const int G = g.fgrid;
   DFDG_DISPATCH_NF(NF, {
-    if (bj) hipLaunchKernelGGL((k_pcg32_init<NN, true>), dim3(G), dim3(kBlk), 0, s, g, A, r64, x, r, z, p_old, pb.rz[0]);
-    else hipLaunchKernelGGL((k_pcg32_init<NN, false>), dim3(G), dim3(kBlk), 0, s, g, A, r64, x, r, z, p_old, pb.rz[0]);
+    if (bj) hipLaunchKernelGGL((k_pcg32_init<NN, true>), dim3(G), dim3(g.fblk), 0, s, g, A, r64, x, r, z, p_old, pb.rz[0]);
+    else hipLaunchKernelGGL((k_pcg32_init<NN, false>), dim3(G), dim3(g.fblk), 0, s, g, A, r64, x, r, z, p_old, pb.rz[0]);
   });
   return hipGetLastError();
 }
@@ -2528,15 +2523,20 @@ hipError_t launch_ir_residual(int NF, const DevGeo& g, const DevBsr& A, const do
     const long n = (long)g.E * NF;
     hipLaunchKernelGGL(k_add_f32, dim3(nblk(n, kBlk)), dim3(kBlk), 0, s, n, x32, lam);
   }
-  DFDG_DISPATCH_NF(NF, hipLaunchKernelGGL((k_ir_residual<NN>), dim3(G), dim3(kBlk), 0, s, g, A, gv, lam, r64,
+  DFDG_DISPATCH_NF(NF, hipLaunchKernelGGL((k_ir_residual<NN>), dim3(G), dim3(g.fblk), 0, s, g, A, gv, lam, r64,
                                           (const PcgScalars*)pb64.sc, pb64.gg));
   hipLaunchKernelGGL(k_finalize_ir, dim3(1), dim3(kBlk), 0, s, (const double*)pb64.gg, G, pb64.sc, sc32, inner_rtol,
                      inner_maxit);
   return hipGetLastError();
 }
 
-int facet_grid_size(int E, int cap) {
-  const int g = facet_grid(E);
+// Blocks of 64 threads while each sums at most kPartsPerThread partials (16384 row parts): they
+// spread a small mesh's gathers over four times as many CUs.  A step at 16^2 BDM_1 431 -> 388 us,
+// the gradient at 48^2 BDM_2 11.56 -> 10.95 ms; blocks of 128 beyond gave nothing (128^2 adjoint
+// step 829 -> 846 us).
+int facet_block_size(int parts, int cap) { return cap <= 0 && parts <= kPartsPerThread * 64 * 64 ? 64 : kBlk; }
+int facet_grid_size(int parts, int cap) {
+  const int b = facet_block_size(parts, cap), g = std::min((parts + b - 1) / b, kMaxFacetGrid);
   return (cap > 0 && cap < g) ? cap : g;
 }
 
@@ -2589,7 +2589,7 @@ static void vcycle_body(int NF, const DevGeo& g, const DevBsr& A, const MgDev& m
   const int G = g.fgrid;
   const int L = mg.nlev;
   const MgVec<V>& v0 = mg_vec<V>(mg, 0);
-  DFDG_DISPATCH_NFS_VOID(NF, A.ns, hipLaunchKernelGGL((k_mg0_resid<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A,
+  DFDG_DISPATCH_NFS_VOID(NF, A.ns, hipLaunchKernelGGL((k_mg0_resid<NN, SS, V, VB>), dim3(G), dim3(g.fblk), 0, s, g, A,
                                                        b, (const V*)v0.x, v0.r, sc));
   xfer<V>(NF, mg.X0, false, (const V*)v0.r, mg_vec<V>(mg, 1).b, sc, s);
   auto apply = [&](const DevCsr& M, int nb, const V* bb, const V* e, V* y) {
@@ -2608,9 +2608,9 @@ static void vcycle_body(int NF, const DevGeo& g, const DevBsr& A, const MgDev& m
   }
   xfer<V>(NF, mg.X0, true, (const V*)mg_vec<V>(mg, 1).z, v0.x, sc, s);
   DFDG_DISPATCH_NFS_VOID(NF, A.ns, {
-    hipLaunchKernelGGL((k_mg0_post1<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b, (const V*)v0.x, v0.y, v0.d,
+    hipLaunchKernelGGL((k_mg0_post1<NN, SS, V, VB>), dim3(G), dim3(g.fblk), 0, s, g, A, b, (const V*)v0.x, v0.y, v0.d,
                        mg.cheb, sc);
-    hipLaunchKernelGGL((k_mg0_post2<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b, (const V*)v0.y,
+    hipLaunchKernelGGL((k_mg0_post2<NN, SS, V, VB>), dim3(G), dim3(g.fblk), 0, s, g, A, b, (const V*)v0.y,
                        (const V*)v0.d, z, mg.cheb, rz, sc);
   });
 }
@@ -2624,10 +2624,10 @@ hipError_t launch_vcycle(int NF, const DevGeo& g, const DevBsr& A, const MgDev& 
   if (L == 1) {  // the facet matrix itself is the coarsest level: exact (regularised) solve in VB
     hipLaunchKernelGGL((k_dense_mv<VB>), dim3(mg.n_coarse), dim3(kBlk), 0, s, mg.n_coarse,
                        mg.n_coarse, mg.coarse_inv, mg.coarse_inv32, b, z, sc);
-    hipLaunchKernelGGL((k_partial_dot<VB>), dim3(G), dim3(kBlk), 0, s, (long)g.E * NF, b, (const VB*)z, rz, sc);
+    hipLaunchKernelGGL((k_partial_dot<VB>), dim3(G), dim3(g.fblk), 0, s, (long)g.E * NF, b, (const VB*)z, rz, sc);
     return hipGetLastError();
   }
-  DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_mg0_pre<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A, b,
+  DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_mg0_pre<NN, SS, V, VB>), dim3(G), dim3(g.fblk), 0, s, g, A, b,
                                                  v0.x, mg.cheb, sc));
   vcycle_body<V, VB>(NF, g, A, mg, b, z, rz, sc, s);
   return hipGetLastError();
@@ -2644,7 +2644,7 @@ hipError_t launch_pcg_iteration_mg(int NF, const DevGeo& g, const DevBsr& A, con
   if (e != hipSuccess) return e;
   const double* prev = pb.rz[(it - 1) & 1];
   double* out = pb.rz[it & 1];
-  DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_pcg_upd_mg0_pre<NN, SS, V, VB>), dim3(G), dim3(kBlk), 0, s, g, A,
+  DFDG_DISPATCH_NFS(NF, A.ns, hipLaunchKernelGGL((k_pcg_upd_mg0_pre<NN, SS, V, VB>), dim3(G), dim3(g.fblk), 0, s, g, A,
                                           (const VB*)p_new, (const VB*)Sp, x, r_old, r_new, mg_vec<V>(mg, 0).x,
                                           mg.cheb, pb.sc, prev, (const double*)pb.pq, out));
   vcycle_body<V, VB>(NF, g, A, mg, (const VB*)r_new, z, out, pb.sc, s);
