@@ -182,6 +182,11 @@ struct DevBsr {
 
 // Scalars of one PCG run (device memory).  Written by block 0 of a kernel (or by a
 // one-block finishing kernel) and read by later kernels and by the host.
+// Block 0 sets `done` while other blocks of its own launch read it, so two waves of a block
+// may see different values.  A kernel that sets it and writes what outlives the run (x)
+// therefore tests it behind its block sums, which all waves of a block enter: either the
+// flag was set before the launch and all leave, or all form the status from whole sums.
+// Kernels whose writes nobody reads after the end may leave at the flag at once.
 struct PcgScalars {
   double rz, rr, gg, tol2, zg;
   double rr0;  // (r, r) at the start of the run (written with the first iteration)

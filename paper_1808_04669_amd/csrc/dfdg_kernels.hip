@@ -1076,12 +1076,13 @@ __global__ __launch_bounds__(kBlk) void k_pcg_update(DevGeo g, DevBsr A, const V
                                                      V* __restrict__ z, PcgScalars* sc,
                                                      const double* __restrict__ rz_prev,
                                                      const double* __restrict__ pq, double* __restrict__ rz_out) {
-  if (sc->done != PCG_RUNNING) return;
+  const int done = sc->done;  // tested after the sums (see PcgScalars)
   const int E = g.E;
   const int G = gridDim.x;
   double t1[2], t2[2];
   block_sum_partials<2>(rz_prev, G, t1);
   block_sum_partials<2>(pq, G, t2);
+  if (done != PCG_RUNNING) return;
   int status = PCG_RUNNING;
   if (!isfinite(t2[0])) status = PCG_NONFINITE;
   else if (!(t2[0] > 0)) status = PCG_BREAKDOWN;
@@ -1185,7 +1186,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
                                                      double* __restrict__ p_out, double* __restrict__ x,
                                                      PcgScalars* sc, int odd, const double* __restrict__ rz0,
                                                      const double* __restrict__ part_in, double* __restrict__ part_out) {
-  const int done = sc->done, it = odd ? sc->it : sc->it2;  // tested after the first row's loads
+  const int done = sc->done, it = odd ? sc->it : sc->it2;  // done: tested after the sums (see PcgScalars)
   const bool first = it == 1;
   const int E = g.E, G = gridDim.x;
   double t[6] = {0, 0, 0, 0, 0, 0};
@@ -1234,8 +1235,8 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         }
     }
   }
-  if (done != PCG_RUNNING) return;
   block_sum_values<6>(t, t);
+  if (done != PCG_RUNNING) return;
   double alpha = 0, beta = 0;
   int status = PCG_RUNNING;
   if (!isfinite(t[4]) || !isfinite(t[5])) status = PCG_NONFINITE;
@@ -1711,9 +1712,8 @@ __global__ __launch_bounds__(kBlk) void k_pcg_upd_mg0_pre(DevGeo g, DevBsr A, co
   const int E = g.E;
   const int G = gridDim.x;
   const int u0 = xcd_block() * blockDim.x + threadIdx.x;
-  const int done = sc->done;
+  const int done = sc->done;  // tested after the sums (see PcgScalars)
   first_columns<SPL, NS>(A, E, u0);
-  if (done != PCG_RUNNING) return;
   // alpha is not needed before the end: with u = D^{-1} r_old / th and w = D^{-1} S p / th,
   // S x1 = S u - alpha S w.  The partials are loaded first and summed after this thread's
   // first row, whose loads overlap them.
@@ -1734,10 +1734,11 @@ __global__ __launch_bounds__(kBlk) void k_pcg_upd_mg0_pre(DevGeo g, DevBsr A, co
     }, su, sw);
   };
   V su[NA], sw[NA];
-  if (u0 < E * SPL) row(u0, su, sw);
+  if (done == PCG_RUNNING && u0 < E * SPL) row(u0, su, sw);
   double t1[2], t2[2];
   partials_sum<2>(q1, G, t1);
   partials_sum<2>(q2, G, t2);
+  if (done != PCG_RUNNING) return;
   int status = PCG_RUNNING;
   if (!isfinite(t2[0])) status = PCG_NONFINITE;
   else if (!(t2[0] > 0)) status = PCG_BREAKDOWN;

@@ -893,11 +893,12 @@ __global__ __launch_bounds__(kBlk) void k_mf_update(DevGeo g, DevBsr A, const do
                                                     double* __restrict__ z, PcgScalars* sc,
                                                     const double* __restrict__ rz_prev,
                                                     const double* __restrict__ pq, double* __restrict__ rz_out) {
-  if (sc->done != PCG_RUNNING) return;
+  const int done = sc->done;  // tested after the sums (see PcgScalars)
   const int G = gridDim.x;
   double t1[2], t2[2];
   block_sum_partials<2>(rz_prev, G, t1);
   block_sum_partials<2>(pq, G, t2);
+  if (done != PCG_RUNNING) return;
   int status = PCG_RUNNING;
   if (!isfinite(t2[0])) status = PCG_NONFINITE;
   else if (!(t2[0] > 0)) status = PCG_BREAKDOWN;
