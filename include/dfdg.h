@@ -80,6 +80,7 @@ enum { DFDG_FP64 = 0, DFDG_MIXED = 1 };            /* dfdg_params.precision */
 #define DFDG_EXTRAPOLATE_PROJECT 6   /* dfdg_params.extrapolate: projection onto earlier solutions */
 enum { DFDG_JACOBI = 0, DFDG_BLOCK_JACOBI = 1, DFDG_AMG = 2 };  /* dfdg_params.precond */
 enum { DFDG_LOCAL_FE3 = 0, DFDG_LOCAL_FE4 = 1 };  /* dfdg_params.local_space */
+enum { DFDG_ELIM_AUTO = 0, DFDG_ELIM_OFF = 1, DFDG_ELIM_ON = 2 };  /* dfdg_params.elimination */
 
 typedef struct dfdg_mesh dfdg_mesh;
 typedef struct dfdg_ctx dfdg_ctx;
@@ -96,12 +97,8 @@ typedef struct {
                         finest level, one Chebyshev(1) step before and after the
                         correction on the coarser levels; coarse space spanned by the
                         constant multiplier; built on the host at context creation).  Small
-                        meshes (up to 32768 multipliers on triangles, 65536 on tetrahedra if
-                        the matrices fit) with mg_fp32 = 1 or the Krylov refinement and
-                        facet_blocks = 0 take an exact solve in FP32 in the cycle's place: the
-                        interiors of cells of elements eliminated, the interface between the
-                        cells inverted densely (factored on the GPU when the workspace is
-                        bound) */
+                        meshes take an exact solve in FP32 in the cycle's place (see
+                        elimination) */
   double ir_rtol;    /* MIXED: outer FP64 refinement target (relative residual) */
   double inner_rtol; /* MIXED, mixed_solver = 0: FP32 inner PCG reduction per refinement step */
   int extrapolate;   /* rk3_step: 0 = warm start from the last same-stage multiplier,
@@ -127,11 +124,14 @@ typedef struct {
                         FP32), 0 = S in FP32.  The preconditioner then uses a symmetric
                         perturbation of S of relative size 2^-11; the PCG itself keeps the
                         FP64 S and its stopping test. */
-  int facet_blocks;  /* blocks of 256 threads of the facet-row kernels: 0 = ceil(E/256) up to
-                        1024 (default); 1..1024 = at most that many.  With fewer blocks
-                        than rows/256, each thread walks several facet rows in a grid-
-                        stride loop (the path every mesh above 262144 facets takes); the
-                        results are the same up to the order of the partial sums. */
+  int facet_blocks;  /* blocks of the facet-row kernels: 0 = one row per thread, up to 1024
+                        blocks (default; 256 threads a block, 64 on meshes of up to 16384
+                        rows); 1..1024 = at most that many.  Where the default grid has more
+                        blocks than that, blocks of 256 threads walk several facet rows a
+                        thread in a grid-stride loop (the path every mesh above 262144 facets
+                        takes), and point Jacobi runs its update and its product as two such
+                        kernels.  The results of the PCG are the same up to rounding.  DFDG_AMG:
+                        a value > 0 also selects the cycle while elimination is 0 */
   int matrix_free;   /* tetrahedral meshes, FP64 PCG: 1 = form S p element by element as
                         sum_T C_T W_T C_T^T p from the element data (two passes, no matrix
                         read) instead of reading the assembled S; 0 = assembled S (default)
@@ -161,6 +161,17 @@ typedef struct {
                         packed (Z^T Z)^{-1}, (2P-n_p)(2P-n_p+1)/2 doubles).  Same facet
                         system and velocity up to rounding.  Tetrahedral meshes: must be
                         DFDG_LOCAL_FE3 (else DFDG_E_UNSUPPORTED). */
+  int elimination;   /* DFDG_AMG: what preconditions the facet PCG.  The elimination is an exact
+                        solve in FP32: the interiors of cells of elements eliminated, the
+                        interface between the cells inverted densely (factored on the GPU when
+                        the workspace is bound); two to five PCG iterations.
+                        DFDG_ELIM_AUTO (0, default): the elimination on small meshes (up to
+                        32768 multipliers on triangles, 65536 on tetrahedra if the matrices
+                        fit; two multigrid levels or more) whose cycle would run in FP32
+                        (mg_fp32 = 1, or the Krylov refinement) and with facet_blocks = 0,
+                        else the cycle; DFDG_ELIM_OFF: the cycle; DFDG_ELIM_ON: the
+                        elimination, whatever facet_blocks (DFDG_E_UNSUPPORTED where a mesh or
+                        the parameters do not allow it) */
 } dfdg_params;
 
 typedef struct {

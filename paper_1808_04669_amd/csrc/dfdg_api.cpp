@@ -230,6 +230,7 @@ extern "C" void dfdg_params_default(dfdg_params* p) {
   p->mixed_solver = 1;
   p->local_space = DFDG_LOCAL_FE3;
   p->mg_fine_smooth = 2;
+  p->elimination = DFDG_ELIM_AUTO;
 }
 
 static_assert(DFDG_HISTORY_DEPTH == kHistDepth, "history depth of the ABI and the kernels");
@@ -265,6 +266,7 @@ static int check_params(const dfdg_params* p, std::string& e) {
   if (p->matrix_free != 0 && p->matrix_free != 1) { e = "matrix_free must be 0 or 1"; return -1; }
   if (p->mixed_solver != 0 && p->mixed_solver != 1) { e = "mixed_solver must be 0 or 1"; return -1; }
   if (p->mg_fine_smooth < 1 || p->mg_fine_smooth > 3) { e = "mg_fine_smooth must be in 1..3"; return -1; }
+  if (p->elimination < DFDG_ELIM_AUTO || p->elimination > DFDG_ELIM_ON) { e = "elimination must be in 0..2"; return -1; }
   if (p->local_space != DFDG_LOCAL_FE3 && p->local_space != DFDG_LOCAL_FE4) {
     e = "local_space must be DFDG_LOCAL_FE3 or DFDG_LOCAL_FE4";
     return -1;
@@ -302,10 +304,12 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
     return DFDG_E_UNSUPPORTED;
   }
   ctx->hs.fe4 = ctx->dim == 2 && prm->local_space == DFDG_LOCAL_FE4;
-  // small meshes precondition with the block elimination in the FP32 cycle's place, unless the
-  // caller asked for a launch shape of the facet kernels (see kElimUnknowns)
+  // small meshes precondition with the block elimination in the FP32 cycle's place (see
+  // kElimUnknowns).  With facet_blocks set, the automatic choice is the cycle: the elimination's
+  // kernels have no such grid.
   const bool krylov = prm->precision == DFDG_FP64 ? prm->mg_fp32 != 0 : prm->mixed_solver == 1;
-  if (prm->precond == DFDG_AMG && krylov && prm->facet_blocks == 0)
+  const bool ask = prm->elimination == DFDG_ELIM_ON || (prm->elimination == DFDG_ELIM_AUTO && prm->facet_blocks == 0);
+  if (prm->precond == DFDG_AMG && krylov && ask)
     ctx->el_on = build_elim(mesh->m, ctx->dim == 3 ? nF3(prm->k) : nF(prm->k), ctx->eh);
   ctx->hs.keep_ST = ctx->el_on;
   if ((ctx->dim == 3 ? build_setup3(mesh->m, prm->k, prm->alpha, ctx->hs, e)
@@ -340,6 +344,11 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
   ctx->nL = (long)ctx->NF * ctx->E;
   // a hierarchy of one level is solved densely as it is
   if (ctx->H.lv.size() < 2) ctx->el_on = false;
+  if (prm->elimination == DFDG_ELIM_ON && !ctx->el_on) {
+    g_mesh_err = "elimination: not for this mesh or these parameters";
+    delete ctx;
+    return DFDG_E_UNSUPPORTED;
+  }
   *out = ctx;
   return DFDG_OK;
 }

@@ -27,7 +27,7 @@ struct PcgBufs {
   double* pq;      // [G][2] (p,Sp), (z,Sp) partials (z the normalised kernel vector of S)
   double* pj[2];   // [G][6] partials of launch_pcg_jacobi
 };
-// G: blocks of the facet kernels for E facets' row parts, up to 1024, or at most cap (> 0)
+// Blocks of the facet kernels for so many row parts, up to 1024 and at most cap (> 0)
 int facet_grid_size(int parts, int cap);
 int facet_block_size(int parts, int cap);  // their threads
 

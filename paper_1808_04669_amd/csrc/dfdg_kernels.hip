@@ -2534,8 +2534,11 @@ hipError_t launch_ir_residual(int NF, const DevGeo& g, const DevBsr& A, const do
 // Blocks of 64 threads while each sums at most kPartsPerThread partials (16384 row parts): they
 // spread a small mesh's gathers over four times as many CUs.  A step at 16^2 BDM_1 431 -> 388 us,
 // the gradient at 48^2 BDM_2 11.56 -> 10.95 ms; blocks of 128 beyond gave nothing (128^2 adjoint
-// step 829 -> 846 us).
-int facet_block_size(int parts, int cap) { return cap <= 0 && parts <= kPartsPerThread * 64 * 64 ? 64 : kBlk; }
+// step 829 -> 846 us).  A cap below that number of blocks takes blocks of 256; one above
+// changes nothing.
+int facet_block_size(int parts, int cap) {
+  return parts <= kPartsPerThread * 64 * 64 && (cap <= 0 || cap >= (parts + 63) / 64) ? 64 : kBlk;
+}
 int facet_grid_size(int parts, int cap) {
   const int b = facet_block_size(parts, cap), g = std::min((parts + b - 1) / b, kMaxFacetGrid);
   return (cap > 0 && cap < g) ? cap : g;
