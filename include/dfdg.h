@@ -167,7 +167,8 @@ typedef struct {
                         the workspace is bound); two to five PCG iterations.
                         DFDG_ELIM_AUTO (0, default): the elimination on small meshes (up to
                         32768 multipliers on triangles, 65536 on tetrahedra if the matrices
-                        fit; two multigrid levels or more) whose cycle would run in FP32
+                        fit; two multigrid levels or more; not on meshes stretched so far
+                        that an inverse in FP32 loses its meaning) whose cycle would run in FP32
                         (mg_fp32 = 1, or the Krylov refinement) and with facet_blocks = 0,
                         else the cycle; DFDG_ELIM_OFF: the cycle; DFDG_ELIM_ON: the
                         elimination, whatever facet_blocks (DFDG_E_UNSUPPORTED where a mesh or

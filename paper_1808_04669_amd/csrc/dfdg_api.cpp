@@ -318,6 +318,11 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
     delete ctx;
     return DFDG_E_MESH;
   }
+  if (ctx->el_on && !elim_conditioned(mesh->m, ctx->hs, ctx->dim == 3 ? nF3(prm->k) : nF(prm->k))) {
+    ctx->el_on = false;
+    ctx->hs.ST.clear();
+    ctx->hs.ST.shrink_to_fit();
+  }
   if (prm->precond == DFDG_AMG) {
     const HostSetup& h = ctx->hs;
     const int NFk = ctx->dim == 3 ? nF3(prm->k) : nF(prm->k);

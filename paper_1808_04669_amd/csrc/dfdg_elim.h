@@ -39,4 +39,14 @@ constexpr int kElimMaxVec = 12288;  // unknowns of a front or of the interface, 
 // The partition with the fewest values in its matrices; false if none is within the limits.
 bool build_elim(const MeshHost& m, int NF, ElimHost& el);
 
+// Whether S is conditioned well enough for an inverse in FP32.  Rounding the inverse entry by
+// entry perturbs the preconditioned system by some 6e-8 kappa, kappa the condition of S scaled
+// by its diagonal: a square of 24^2 BDM_2 stretched by 30 (kappa 6e5), 100 (7e6), 300 (6e7),
+// 1000 (7e8) takes 4, 5, 9, 53 iterations to 1e-12 and by 2000 (3e9) never ends, where the
+// cycle takes 181, 282, 309, 278 and 630.  The line lies a factor of 100 below that; the
+// estimate was within 1 % of the dense eigenvalues on stretched squares and cubes and low by
+// 14 % at most on layers growing from one wall.
+constexpr double kElimCondition = 3e7;
+bool elim_conditioned(const MeshHost& m, const HostSetup& h, int NF);
+
 }  // namespace dfdg

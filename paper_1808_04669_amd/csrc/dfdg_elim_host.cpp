@@ -3,6 +3,7 @@
 #include "dfdg_elim.h"
 
 #include <algorithm>
+#include <cmath>
 #include <numeric>
 
 namespace dfdg {
@@ -162,6 +163,172 @@ bool build_elim(const MeshHost& m, int NF, ElimHost& el) {
   el.boff.push_back((int)el.bfac.size());
   el.noff.push_back((int)el.ngam.size());
   return true;
+}
+
+// Extreme eigenvalues of a symmetric tridiagonal matrix, by bisection on Sturm counts.
+static void tridiagonal_extremes(const std::vector<double>& a, const std::vector<double>& b, double& lo, double& hi) {
+  const int n = (int)a.size();
+  auto below = [&](double x) {  // eigenvalues < x
+    int c = 0;
+    double q = 1;
+    for (int i = 0; i < n; ++i) {
+      q = a[i] - x - (i ? b[i - 1] * b[i - 1] / q : 0.0);
+      if (q == 0) q = 1e-300;
+      c += q < 0;
+    }
+    return c;
+  };
+  double g0 = a[0], g1 = a[0];
+  for (int i = 0; i < n; ++i) {
+    const double r = (i ? std::fabs(b[i - 1]) : 0.0) + (i + 1 < n ? std::fabs(b[i]) : 0.0);
+    g0 = std::min(g0, a[i] - r);
+    g1 = std::max(g1, a[i] + r);
+  }
+  for (int k : {0, n - 1}) {
+    double l = g0, u = g1;
+    for (int it = 0; it < 100; ++it) {
+      const double x = 0.5 * (l + u);
+      (below(x) > k ? u : l) = x;
+    }
+    (k ? hi : lo) = u;
+    if (n == 1) hi = lo;
+  }
+}
+
+// The condition of D^{-1/2} S D^{-1/2} (off its kernel) from below: Lanczos steps from a wave
+// along each axis in turn, near the lowest modes of a stretched mesh, projected onto the facets'
+// modes (by the means alone its steps across thin elements would hide the low modes).
+static double condition_estimate(const MeshHost& m, const HostSetup& h, int NF) {
+  constexpr int kSteps = 16;
+  const int E = h.E, dim = m.dim, nf = dim + 1, NS = (int)(h.cols.size() / E);
+  const long n = (long)E * NF;
+  std::vector<double> q(n), qo(n), w(n), y(n), sd(n), z;
+  for (long i = 0; i < n; ++i) sd[i] = std::sqrt(h.dinv[i]);  // D^{-1/2}
+  double lo[3], hi[3];
+  for (int c = 0; c < dim; ++c) {
+    lo[c] = hi[c] = m.xyz[c];
+    for (size_t i = c; i < m.xyz.size(); i += dim) {
+      lo[c] = std::min(lo[c], m.xyz[i]);
+      hi[c] = std::max(hi[c], m.xyz[i]);
+    }
+  }
+  // projection onto the facet's basis (edges: Legendre polynomials from vertex f + 1 to f + 2;
+  // faces: Dubiner polynomials from the lowest local vertex)
+  std::vector<double> pt, pw, mode;
+  if (dim == 2) gauss_legendre01(NF + 1, pt, pw);
+  else sym_face_rule(6, pt, pw);
+  const int np = (int)pw.size();
+  mode.resize((size_t)np * NF);
+  for (int r = 0; r < np; ++r) {
+    if (dim == 2) {
+      for (int a = 0; a < NF; ++a) mode[r * NF + a] = pw[r] * legendre01_orthonormal(a, pt[r]);
+    } else {
+      dubiner(NF == 3 ? 1 : 2, pt[2 * r], pt[2 * r + 1], &mode[r * NF], nullptr);
+      for (int a = 0; a < NF; ++a) mode[r * NF + a] *= pw[r] * std::sqrt(0.5);
+    }
+  }
+  const double pi = std::acos(-1.0);
+  if (h.singular) {
+    z.assign(n, 0.0);
+    double zz = 0;
+    for (int F = 0; F < E; ++F) {
+      z[(size_t)F * NF] = h.zdef[F] / sd[(size_t)F * NF];
+      zz += z[(size_t)F * NF] * z[(size_t)F * NF];
+    }
+    for (double& x : z) x /= std::sqrt(zz);
+  }
+  auto deflate = [&](std::vector<double>& x) {
+    double t = 0;
+    for (size_t i = 0; i < z.size(); ++i) t += z[i] * x[i];
+    for (size_t i = 0; i < z.size(); ++i) x[i] -= t * z[i];
+  };
+  auto norm = [&](const std::vector<double>& x) {
+    double t = 0;
+    for (double v : x) t += v * v;
+    return std::sqrt(t);
+  };
+  double least = HUGE_VAL, most = 0;
+  for (int c = 0; c < dim; ++c) {
+    std::fill(q.begin(), q.end(), 0.0);
+    for (int F = 0; F < E; ++F) {
+      const double* v = &m.xyz[(size_t)m.fL[F] * nf * dim];
+      const int f = m.fLloc[F];
+      int vert[3], k = 0;
+      if (dim == 2) {
+        vert[0] = (f + 1) % 3;
+        vert[1] = (f + 2) % 3;
+      } else {
+        for (int i = 0; i < 4; ++i)
+          if (i != f) vert[k++] = i;
+      }
+      for (int r = 0; r < np; ++r) {
+        const double* o = v + vert[0] * dim;
+        double x = o[c];
+        for (int i = 1; i < dim; ++i) x += pt[(dim - 1) * r + i - 1] * (v[vert[i] * dim + c] - o[c]);
+        const double s = std::cos((m.period[c] > 0 ? 2 * pi / m.period[c] : pi / (hi[c] - lo[c])) * (x - lo[c]));
+        for (int a = 0; a < NF; ++a) q[(size_t)F * NF + a] += s * mode[r * NF + a] * h.nearnull[F];
+      }
+    }
+    for (long i = 0; i < n; ++i) q[i] /= sd[i];
+    deflate(q);
+    const double q0 = norm(q);
+    if (!(q0 > 0)) continue;
+    for (double& x : q) x /= q0;
+    std::vector<double> al, be;
+    for (int it = 0; it < kSteps; ++it) {
+      for (long i = 0; i < n; ++i) {
+        y[i] = sd[i] * q[i];
+        w[i] = 0;
+      }
+      for (int s = 0; s < NS; ++s)
+        for (int a = 0; a < NF; ++a)
+          for (int b = 0; b < NF; ++b) {
+            const double* v = &h.vals[(((size_t)s * NF + a) * NF + b) * E];
+            const int* col = &h.cols[(size_t)s * E];
+            for (int F = 0; F < E; ++F) w[(size_t)F * NF + a] += v[F] * y[(size_t)col[F] * NF + b];
+          }
+      double t = 0;
+      for (long i = 0; i < n; ++i) {
+        w[i] = sd[i] * w[i] - (it ? be.back() * qo[i] : 0.0);
+        t += w[i] * q[i];
+      }
+      for (long i = 0; i < n; ++i) w[i] -= t * q[i];
+      deflate(w);
+      al.push_back(t);
+      const double b = norm(w);
+      if (!(b > 1e-14)) break;
+      be.push_back(b);
+      qo.swap(q);
+      for (long i = 0; i < n; ++i) q[i] = w[i] / b;
+    }
+    double l = 0, u = 0;
+    tridiagonal_extremes(al, be, l, u);
+    least = std::min(least, l);
+    most = std::max(most, u);
+  }
+  return least > 0 ? most / least : HUGE_VAL;
+}
+
+bool elim_conditioned(const MeshHost& m, const HostSetup& h, int NF) {
+  // On elements without thin directions the scaled condition grows with the number of
+  // facets across the mesh only: far below the line at the sizes of kElimUnknowns.
+  const int T = m.T, dim = m.dim, nf = dim + 1;
+  bool thin = false;
+  for (int t = 0; t < T && !thin; ++t) {
+    const double* v = &m.xyz[(size_t)t * nf * dim];
+    double edge = 0, face = 0;
+    for (int i = 0; i < nf; ++i) {
+      face = std::max(face, h.flen[(size_t)i * T + t]);
+      for (int k = 0; k < i; ++k) {
+        double d = 0;
+        for (int c = 0; c < dim; ++c) d += (v[i * dim + c] - v[k * dim + c]) * (v[i * dim + c] - v[k * dim + c]);
+        edge = std::max(edge, std::sqrt(d));
+      }
+    }
+    const double height = h.detJ[t] / (dim == 3 ? 2 * face : face);
+    thin = !(edge <= 16 * height);
+  }
+  return !thin || condition_estimate(m, h, NF) <= kElimCondition;
 }
 
 }  // namespace dfdg
