@@ -80,6 +80,7 @@ enum { DFDG_FP64 = 0, DFDG_MIXED = 1 };            /* dfdg_params.precision */
 #define DFDG_EXTRAPOLATE_PROJECT 6   /* dfdg_params.extrapolate: projection onto earlier solutions */
 enum { DFDG_JACOBI = 0, DFDG_BLOCK_JACOBI = 1, DFDG_AMG = 2 };  /* dfdg_params.precond */
 enum { DFDG_LOCAL_FE3 = 0, DFDG_LOCAL_FE4 = 1 };  /* dfdg_params.local_space */
+#define DFDG_ASSEMBLED 2  /* dfdg_params.matrix_free */
 enum { DFDG_ELIM_AUTO = 0, DFDG_ELIM_OFF = 1, DFDG_ELIM_ON = 2 };  /* dfdg_params.elimination */
 
 typedef struct dfdg_mesh dfdg_mesh;
@@ -132,12 +133,12 @@ typedef struct {
                         takes), and point Jacobi runs its update and its product as two such
                         kernels.  The results of the PCG are the same up to rounding.  DFDG_AMG:
                         a value > 0 also selects the cycle while elimination is 0 */
-  int matrix_free;   /* tetrahedral meshes, FP64 PCG: 1 = form S p element by element as
-                        sum_T C_T W_T C_T^T p from the element data (two passes, no matrix
-                        read) instead of reading the assembled S; 0 = assembled S (default)
-                        below 32768 elements, element by element above, where S no longer
-                        fits the cache.
-                        The multigrid smoothing still reads S.  Triangle meshes: must be 0. */
+  int matrix_free;   /* tetrahedral meshes, FP64 PCG: how S p is formed.  1 = element by element,
+                        as sum_T C_T W_T C_T^T p from the element data (no matrix read),
+                        DFDG_ASSEMBLED = 2 from the assembled S, 0 (default) = the faster of
+                        the two by the number of elements: assembled below 32768, element by
+                        element from there on.  Same results up to rounding.  The multigrid
+                        smoothing reads S in every case.  Triangle meshes: must be 0. */
   int mixed_solver;  /* MIXED facet solves (the residual is FP32 in both):
                         1 = Krylov refinement (default): FP64 PCG iterations (FP64 S, vectors,
                         dot products, stopping test at ir_rtol) whose preconditioner, the

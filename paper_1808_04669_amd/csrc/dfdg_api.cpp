@@ -263,7 +263,7 @@ static int check_params(const dfdg_params* p, std::string& e) {
   if (p->mg_fp32 != 0 && p->mg_fp32 != 1) { e = "mg_fp32 must be 0 or 1"; return -1; }
   if (p->mg_fine_fp16 != 0 && p->mg_fine_fp16 != 1) { e = "mg_fine_fp16 must be 0 or 1"; return -1; }
   if (p->facet_blocks < 0 || p->facet_blocks > 1024) { e = "facet_blocks must be in 0..1024"; return -1; }
-  if (p->matrix_free != 0 && p->matrix_free != 1) { e = "matrix_free must be 0 or 1"; return -1; }
+  if (p->matrix_free < 0 || p->matrix_free > DFDG_ASSEMBLED) { e = "matrix_free must be in 0..2"; return -1; }
   if (p->mixed_solver != 0 && p->mixed_solver != 1) { e = "mixed_solver must be 0 or 1"; return -1; }
   if (p->mg_fine_smooth < 1 || p->mg_fine_smooth > 3) { e = "mg_fine_smooth must be in 1..3"; return -1; }
   if (p->elimination < DFDG_ELIM_AUTO || p->elimination > DFDG_ELIM_ON) { e = "elimination must be in 0..2"; return -1; }
@@ -398,13 +398,14 @@ struct Carver {
 
 static int d3slots(const dfdg_ctx* ctx) { return ctx->dim == 3 ? kSlots3 : kSlots; }
 
-// Whether the FP64 PCG forms its products element by element instead of reading S: when the
-// caller asks for it, and on tetrahedral meshes from 32768 elements on.  Measured, Jacobi
-// iteration with and without: BDM_2 16^3 (24576 elements) 35 / 36 us, 20^3 41 / 53, 24^3 50 /
-// 133, 32^3 87 / 240 (S no longer fits the Infinity Cache from 21^3 on); BDM_1 16^3 19 / 20,
-// 24^3 33 / 37, 32^3 54 / 86.
+// Whether the FP64 PCG forms its products element by element instead of reading S: as the
+// caller asks, else on tetrahedral meshes from 32768 elements on.  Measured, Jacobi iteration
+// with and without: BDM_2 16^3 (24576 elements) 35 / 36 us, 20^3 41 / 53, 24^3 50 / 133, 32^3
+// 87 / 240 (S no longer fits the Infinity Cache from 21^3 on); BDM_1 16^3 19 / 20, 24^3 33 / 37,
+// 32^3 54 / 86.
 static bool mf_products(const dfdg_ctx* ctx) {
-  return ctx->prm.matrix_free != 0 || (ctx->dim == 3 && ctx->T >= 32768);
+  if (ctx->prm.matrix_free) return ctx->prm.matrix_free != DFDG_ASSEMBLED;
+  return ctx->dim == 3 && ctx->T >= 32768;
 }
 
 static void carve(dfdg_ctx* ctx, char* base) {

@@ -20,6 +20,7 @@ STATUS = {0: "OK", -1: "E_INVALID_ARG", -2: "E_MESH", -3: "E_WORKSPACE", -4: "E_
           -5: "E_NOT_CONVERGED", -6: "E_NONFINITE", -7: "E_BREAKDOWN", -8: "E_UNSUPPORTED"}
 FP64, MIXED = 0, 1
 JACOBI, BLOCK_JACOBI, AMG = 0, 1, 2
+ASSEMBLED = 2  # matrix_free="assembled": products from the assembled S at any size
 HISTORY_DEPTH = 6  # DFDG_HISTORY_DEPTH: earlier multipliers kept per stage
 EXTRAPOLATE_ADAPTIVE = 5  # extrapolate="adaptive": order chosen per solve by a one-step backtest
 EXTRAPOLATE_PROJECT = 6  # extrapolate="project": projection onto earlier solutions (S-norm)
@@ -241,7 +242,7 @@ class Solver:
         p.mg_fp32 = 1 if mg_fp32 else 0
         p.mg_fine_fp16 = 1 if mg_fine_fp16 else 0
         p.facet_blocks = int(facet_blocks)
-        p.matrix_free = 1 if matrix_free else 0
+        p.matrix_free = ASSEMBLED if matrix_free == "assembled" else 1 if matrix_free else 0
         p.mixed_solver = {"krylov": 1, "restarted": 0}[mixed_solver]
         p.local_space = {"fe3": 0, "fe4": 1}[local_space]
         if mg_fine_smooth is not None:
