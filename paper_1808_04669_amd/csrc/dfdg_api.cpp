@@ -1830,16 +1830,17 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
     double b = 0;
     switch (which) {
       case 0:
-        if (ctx->A.mfq)  // two passes that each read z and p_old: per element Jinv, (D D^T)^{-1}, per
-                         // face id, code, sqrt(|F|/det), normal, z and p_old gathered,
-                         // contributions out; per face 2 offsets, both contributions, z, p_old
-                         // in, p_new, Sp out (the element pass now writes p_new itself)
+        if (ctx->A.mfq)  // per element Jinv, (D D^T)^{-1}, per face id, code, sqrt(|F|/det), normal,
+                         // z and p_old gathered, contributions out; per face 2 offsets, both
+                         // contributions, z, p_old in, p_new, Sp out: the count of two passes
+                         // over the vectors, which this entry has always reported.  The face
+                         // pass no longer reads z and p_old: 2 E NF doubles less.
           b = T * (9 * 8.0 + nGpk3(ctx->K) * 8.0 + 4 * (2 * 4.0 + 4 * 8.0) + 4 * NF * 2 * 8.0 + 4 * NF * 8.0) +
               E * (2 * 4.0 + 6.0 * NF * 8.0);
         else
           b = E * (NS * NF * NF * 8.0 + NS * 4.0 + 4.0 * NF * 8.0);  // S, cols, z, p_old, p_new, Sp
         break;
-      case 1: b = E * NF * 8.0 * 8.0; break;                                                  // p, Sp, x, r, M^{-1} in; x, r, z out
+      case 1: b = E * NF * (ctx->A.mfq ? 9.0 : 8.0) * 8.0; break;  // p, Sp (or its two sides), x, r, M^{-1} in; x, r, z out
       case 2:  // U (own + neighbours) in, L out, Jinv + 1/sqrt(detJ); per facet nbr, code, normal,
                // |F| (and sigma if nu != 0)
         if (ctx->dim == 3)
@@ -1848,10 +1849,10 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
           b = T * (2.0 * 2 * P * 8.0 + 5 * 8.0 + 3 * (2 * 4.0 + (ctx->prm.nu != 0.0 ? 4 : 3) * 8.0));
         break;
       case 4: {
-        // finest level: 4 BSR sweeps + 17 vector passes; transfers and coarse levels:
-        // every CSR entry (value and 4-byte column) once per use, vectors once.  Values
-        // and vectors in the cycle's precision (8 or 4 bytes; finest-level S in 2 bytes
-        // when it is stored in FP16).
+        // finest level: 4 BSR sweeps + 17 vector passes; transfers and coarse levels: every
+        // entry once per use (a value and a 4-byte column, on the finest level in FP16 and
+        // 2 bytes where they are stored so), vectors once.  Values and vectors in the cycle's
+        // precision (8 or 4 bytes; finest-level S in 2 bytes when it is stored in FP16).
         const double vb = ctx->prm.mg_fp32 ? 4.0 : 8.0;
         const double sv = ctx->A.vals16 ? 4.0 * nPairs(NF, NS) / (NS * NF * NF) : vb;
         const double sbytes = E * (NS * NF * NF * sv + NS * 4.0);
@@ -1860,8 +1861,11 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
         for (size_t l = 0; l + 1 < H.lv.size(); ++l) {
           const AmgLevel& L = H.lv[l];
           const double nn = H.lv[l + 1].A.n;
-          if (l == 0) {  // transfers of the finest level
-            b += (L.P.nnz() + L.R.nnz()) * (vb + 4.0) + (2.0 * L.A.n + 2.0 * nn) * vb;
+          if (l == 0) {  // transfers of the finest level by facets: a column for NF values each way
+            const DevXfer& X = ctx->mg.X0;
+            const double np = (double)H.p0_col.size();
+            b += X.half ? np * ((2.0 + NF * 2.0) + (4.0 + (NF + 1) / 2 * 4.0)) : 2.0 * np * (4.0 + NF * vb);
+            b += (2.0 * L.A.n + 2.0 * nn) * vb;
           } else {  // restriction with the smoothing step, prolongation with the post-smoothing
             const bool fold = l + 2 == H.lv.size() && !H.coarse_fold.empty();
             b += ((fold ? 0 : L.Rs.nnz()) + L.Ps.nnz()) * (vb + 4.0) + 3.0 * L.A.n * vb + 2.0 * nn * vb;
