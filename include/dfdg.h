@@ -25,6 +25,9 @@
  *   dfdg_ctx_bind_workspace(); it must stay alive and untouched until
  *   dfdg_ctx_destroy().  Pointers named *_host are host pointers, read or written
  *   during the call only.  The library keeps one pinned host buffer per context.
+ *   (One exception, for debugging and measurement only: dfdg_debug_vcycle and
+ *   dfdg_time_kernel(4) of a context that solves by elimination set the cycle up for the
+ *   call in device memory of their own, which they free before they return.)
  * Streams.  All device work of a context is enqueued on the HIP stream given to
  *   dfdg_ctx_create() (or dfdg_ctx_set_stream(), which first waits for the work
  *   queued on the previous stream).  Calls that return numbers to the host (solve/step

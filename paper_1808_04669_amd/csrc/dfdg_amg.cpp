@@ -363,6 +363,46 @@ static bool dense_spd_inverse(int n, std::vector<double>& A) {
   return true;
 }
 
+// Aggregates of a strength graph (rows of possibly one-sided neighbours), symmetrised first: the
+// strength measure is symmetric for a symmetric matrix; be safe.
+static int aggregate_symmetric(int nn, std::vector<int>& gptr, std::vector<int>& gadj, std::vector<int>& agg) {
+  std::vector<std::vector<int>> adj(nn);
+  for (int i = 0; i < nn; ++i)
+    for (int k = gptr[i]; k < gptr[i + 1]; ++k) {
+      adj[i].push_back(gadj[k]);
+      adj[gadj[k]].push_back(i);
+    }
+  gadj.clear();
+  for (int i = 0; i < nn; ++i) {
+    std::sort(adj[i].begin(), adj[i].end());
+    adj[i].erase(std::unique(adj[i].begin(), adj[i].end()), adj[i].end());
+    gadj.insert(gadj.end(), adj[i].begin(), adj[i].end());
+    gptr[i + 1] = (int)gadj.size();
+  }
+  return aggregate(nn, gptr, gadj, agg);
+}
+// Whether a level of n rows on nn nodes with na aggregates is the coarsest: no coarsening
+// possible, or it stalls and the level can be inverted densely.
+static bool coarsest(int n, int nn, int na) { return na >= nn || (2 * na > nn && n <= 4096); }
+
+bool amg_coarsens(int E, int NF, int NS, const std::vector<int>& cols, const std::vector<double>& vals,
+                  const std::vector<double>& dinv, double theta, int max_coarse) {
+  if ((long)E * NF <= max_coarse) return false;
+  for (double d : dinv)
+    if (!(d > 0) || !std::isfinite(d)) return false;
+  std::vector<int> gptr(E + 1, 0), gadj, agg;
+  auto diag = [&](int F) { return std::fabs(1.0 / dinv[(size_t)F * NF]); };
+  for (int F = 0; F < E; ++F) {
+    for (int s = 0; s < NS; ++s) {
+      const int c = cols[(size_t)s * E + F];
+      const double v = vals[(size_t)s * NF * NF * E + F];  // mode 0 of both (a repeated column: 0)
+      if (c != F && std::fabs(v) >= theta * std::sqrt(diag(F) * diag(c))) gadj.push_back(c);
+    }
+    gptr[F + 1] = (int)gadj.size();
+  }
+  return !coarsest(E * NF, E, aggregate_symmetric(E, gptr, gadj, agg));
+}
+
 int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::vector<double>& vals,
               const std::vector<double>& z, bool singular, double theta, int max_coarse, int fine_smooth,
               AmgHierarchy& H, std::string& err) {
@@ -403,26 +443,9 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
       gadj.insert(gadj.end(), nb.begin(), nb.end());
       gptr[i + 1] = (int)gadj.size();
     }
-    // symmetrise the graph (strength measure is symmetric for symmetric A; be safe)
-    {
-      std::vector<std::vector<int>> adj(nn);
-      for (int i = 0; i < nn; ++i)
-        for (int k = gptr[i]; k < gptr[i + 1]; ++k) {
-          adj[i].push_back(gadj[k]);
-          adj[gadj[k]].push_back(i);
-        }
-      gadj.clear();
-      for (int i = 0; i < nn; ++i) {
-        std::sort(adj[i].begin(), adj[i].end());
-        adj[i].erase(std::unique(adj[i].begin(), adj[i].end()), adj[i].end());
-        gadj.insert(gadj.end(), adj[i].begin(), adj[i].end());
-        gptr[i + 1] = (int)gadj.size();
-      }
-    }
     std::vector<int> agg;
-    const int na = aggregate(nn, gptr, gadj, agg);
-    if (na >= nn) break;                  // no coarsening possible
-    if (2 * na > nn && n <= 4096) break;  // coarsening stalls: invert this level densely
+    const int na = aggregate_symmetric(nn, gptr, gadj, agg);
+    if (coarsest(n, nn, na)) break;
     // tentative prolongator: the near-null vector, normalised per aggregate
     std::vector<double> nrm(na, 0.0);
     for (int r = 0; r < n; ++r) nrm[agg[r / nf]] += B[r] * B[r];

@@ -56,4 +56,9 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
               const std::vector<double>& z, bool singular, double theta, int max_coarse, int fine_smooth,
               AmgHierarchy& H, std::string& err);
 
+// Whether build_amg would give more than one level (dinv: the inverse diagonal [E][NF]), without
+// building any; false also where it would fail on the diagonal.
+bool amg_coarsens(int E, int NF, int NS, const std::vector<int>& cols, const std::vector<double>& vals,
+                  const std::vector<double>& dinv, double theta, int max_coarse);
+
 }  // namespace dfdg

@@ -63,7 +63,8 @@ struct dfdg_ctx {
   // the forward integrator whose stage solves the history 0-2, 6 holds (0 none, 1 TVD-RK3,
   // 2 RK4, 3 forward Euler): another one starts from an empty history
   int integrator = 0;
-  // multigrid preconditioner
+  // multigrid preconditioner (a context that solves by elimination builds it only when asked
+  // for it, see need_hierarchy and CycleOf)
   AmgHierarchy H;
   MgDev mg;
   // block elimination in the multigrid cycle's place on small meshes
@@ -274,6 +275,30 @@ static int check_params(const dfdg_params* p, std::string& e) {
   return 0;
 }
 
+static int d3slots(const dfdg_ctx* ctx) { return ctx->dim == 3 ? kSlots3 : kSlots; }
+
+// The multigrid hierarchy of an AMG context (strength threshold, rows of the coarsest level).
+constexpr double kAmgTheta = 0.08;
+constexpr int kAmgMaxCoarse = 1000;
+static int need_hierarchy(dfdg_ctx* ctx, std::string& e) {
+  if (ctx->prm.precond != DFDG_AMG || !ctx->H.lv.empty()) return DFDG_OK;
+  const HostSetup& h = ctx->hs;
+  const int NF = ctx->dim == 3 ? nF3(ctx->prm.k) : nF(ctx->prm.k);
+  std::vector<double> z((size_t)h.E * NF, 0.0);
+  for (int F = 0; F < h.E; ++F) z[(size_t)F * NF] = h.nearnull.empty() ? h.zdef[F] : h.nearnull[F];
+  if (build_amg(h.E, NF, (int)(h.cols.size() / h.E), h.cols, h.vals, z, h.singular, kAmgTheta, kAmgMaxCoarse,
+                ctx->prm.mg_fine_smooth, ctx->H, e)) {
+    ctx->H = AmgHierarchy{};
+    return DFDG_E_MESH;
+  }
+  if ((int)ctx->H.lv.size() > kMaxLev) {
+    ctx->H = AmgHierarchy{};
+    e = "multigrid: too many levels";
+    return DFDG_E_UNSUPPORTED;
+  }
+  return DFDG_OK;
+}
+
 extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, void* stream, dfdg_ctx** out) {
   if (!out) return DFDG_E_INVALID_ARG;
   *out = nullptr;
@@ -318,28 +343,26 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
     delete ctx;
     return DFDG_E_MESH;
   }
-  if (ctx->el_on && !elim_conditioned(mesh->m, ctx->hs, ctx->dim == 3 ? nF3(prm->k) : nF(prm->k))) {
+  // (where the multigrid has one level only, that is solved densely as it is)
+  const int NFk = ctx->dim == 3 ? nF3(prm->k) : nF(prm->k);
+  if (ctx->el_on && !(amg_coarsens(ctx->hs.E, NFk, d3slots(ctx), ctx->hs.cols, ctx->hs.vals, ctx->hs.dinv, kAmgTheta,
+                                   kAmgMaxCoarse) &&
+                      elim_conditioned(mesh->m, ctx->hs, NFk))) {
     ctx->el_on = false;
     ctx->hs.ST.clear();
     ctx->hs.ST.shrink_to_fit();
   }
-  if (prm->precond == DFDG_AMG) {
-    const HostSetup& h = ctx->hs;
-    const int NFk = ctx->dim == 3 ? nF3(prm->k) : nF(prm->k);
-    std::vector<double> z((size_t)h.E * NFk, 0.0);
-    for (int F = 0; F < h.E; ++F) z[(size_t)F * NFk] = h.nearnull.empty() ? h.zdef[F] : h.nearnull[F];
-    if (build_amg(h.E, NFk, (int)(h.cols.size() / h.E), h.cols, h.vals, z, h.singular, 0.08, 1000,
-                  prm->mg_fine_smooth, ctx->H, e)) {
+  if (prm->elimination == DFDG_ELIM_ON && !ctx->el_on) {
+    g_mesh_err = "elimination: not for this mesh or these parameters";
+    delete ctx;
+    return DFDG_E_UNSUPPORTED;
+  }
+  if (!ctx->el_on)
+    if (const int rc = need_hierarchy(ctx, e)) {
       g_mesh_err = e;
       delete ctx;
-      return DFDG_E_MESH;
+      return rc;
     }
-    if ((int)ctx->H.lv.size() > kMaxLev) {
-      g_mesh_err = "multigrid: too many levels";
-      delete ctx;
-      return DFDG_E_UNSUPPORTED;
-    }
-  }
   ctx->K = prm->k;
   ctx->P = ctx->dim == 3 ? nP3(ctx->K) : nP(ctx->K);
   ctx->NF = ctx->dim == 3 ? nF3(ctx->K) : nF(ctx->K);
@@ -347,13 +370,6 @@ extern "C" int dfdg_ctx_create(const dfdg_mesh* mesh, const dfdg_params* prm, vo
   ctx->E = mesh->m.E;
   ctx->nU = (long)ctx->dim * ctx->P * ctx->T;
   ctx->nL = (long)ctx->NF * ctx->E;
-  // a hierarchy of one level is solved densely as it is
-  if (ctx->H.lv.size() < 2) ctx->el_on = false;
-  if (prm->elimination == DFDG_ELIM_ON && !ctx->el_on) {
-    g_mesh_err = "elimination: not for this mesh or these parameters";
-    delete ctx;
-    return DFDG_E_UNSUPPORTED;
-  }
   *out = ctx;
   return DFDG_OK;
 }
@@ -396,8 +412,6 @@ struct Carver {
   }
 };
 
-static int d3slots(const dfdg_ctx* ctx) { return ctx->dim == 3 ? kSlots3 : kSlots; }
-
 // Whether the FP64 PCG forms its products element by element instead of reading S: as the
 // caller asks, else on tetrahedral meshes from 32768 elements on.  Measured, Jacobi iteration
 // with and without: BDM_2 16^3 (24576 elements) 35 / 36 us, 20^3 41 / 53, 24^3 50 / 133, 32^3
@@ -408,137 +422,22 @@ static bool mf_products(const dfdg_ctx* ctx) {
   return ctx->dim == 3 && ctx->T >= 32768;
 }
 
-static void carve(dfdg_ctx* ctx, char* base) {
-  Carver c{base};
+// The multigrid cycle: what its finest level reads of S, and the hierarchy.
+static void carve_cycle(const dfdg_ctx* ctx, Carver& c, DevBsr& A, MgDev& mg) {
   const HostSetup& h = ctx->hs;
-  const long T = ctx->T, E = ctx->E, NF = ctx->NF, nU = ctx->nU, nL = ctx->nL;
-  const RefTables& tb = h.tabs;
-  DevGeo& g = ctx->g;
-  g.T = (int)T;
-  g.E = (int)E;
-  // one thread per facet row, or two for split rows (facet_split)
-  const int parts = (int)(E * facet_split((int)NF, d3slots(ctx)));
-  g.fgrid = facet_grid_size(parts, ctx->prm.facet_blocks);
-  g.fblk = facet_block_size(parts, ctx->prm.facet_blocks);
-  const long dm = ctx->dim, nfac = dm + 1;
-  g.Jinv = c.take<double>(dm * dm * T);
-  g.detJ = c.take<double>(T);
-  g.isq = c.take<double>(T);
-  g.nbr = c.take<int>(nfac * T);
-  g.code = c.take<int>(nfac * T);
-  g.efacet = c.take<int>(nfac * T);
-  g.nx = c.take<double>(nfac * T);
-  g.ny = c.take<double>(nfac * T);
-  g.nz = dm == 3 ? c.take<double>(nfac * T) : nullptr;
-  g.flen = c.take<double>(nfac * T);
-  g.sig = c.take<double>(nfac * T);
-  g.sF = c.take<double>(nfac * T);
-  g.G = c.take<double>(h.G.size());
-  g.G4 = h.G4.empty() ? nullptr : c.take<double>(h.G4.size());
-  g.qL = c.take<int>(E);
-  g.qR = c.take<int>(E);
-  g.zdef = c.take<double>(E);
-  DevTabs& d = ctx->tb;
-  d.Vv = c.take<double>(tb.Vv.size());
-  d.Gv = c.take<double>(tb.Gv.size());
-  d.Wv = c.take<double>(tb.vw.size());
-  d.Vf = c.take<double>(tb.Vf.size());
-  d.Gf = c.take<double>(tb.Gf.size());
-  d.Wf = c.take<double>(tb.fw.size());
-  d.Vp = c.take<double>(tb.Vp.size());
-  d.Wp = c.take<double>(tb.pw.size());
-  d.Dh = c.take<double>(tb.Dh.size());
-  d.Ch = c.take<double>(tb.Ch.size());
-  d.Zh = tb.Zh.empty() ? nullptr : c.take<double>(tb.Zh.size());
-  d.fpidx = tb.fpidx.empty() ? nullptr : c.take<int>(tb.fpidx.size());
-  d.Qf = tb.Qf.empty() ? nullptr : c.take<double>(tb.Qf.size());
-  d.cond = tb.cond.empty() ? nullptr : c.take<double>(tb.cond.size());
-  d.res = tb.res.empty() ? nullptr : c.take<double>(tb.res.size());
-  DevBsr& A = ctx->A;
-  A.ns = d3slots(ctx);
-  A.cols = c.take<int>(h.cols.size());
-  A.vals = c.take<double>(h.vals.size());
-  A.dinv = c.take<double>(h.dinv.size());
-  A.binv = c.take<double>(h.binv.size());
-  const bool mixed = ctx->prm.precision == DFDG_MIXED;
-  // FP32 copies of S (and of the multigrid data) for the mixed form or an FP32 V-cycle
-  const bool f32 = mixed || (ctx->prm.precond == DFDG_AMG && ctx->prm.mg_fp32);
-  A.vals32 = f32 ? c.take<float>(h.vals.size()) : nullptr;
-  A.dinv32 = f32 ? c.take<float>(h.dinv.size()) : nullptr;
-  A.binv32 = f32 ? c.take<float>(h.binv.size()) : nullptr;
-  const bool f16 = ctx->prm.precond == DFDG_AMG && (mixed || ctx->prm.mg_fp32) && ctx->prm.mg_fine_fp16;
+  const long E = ctx->E, NF = ctx->NF, nL = ctx->nL;
+  // FP32 copies of S and of the multigrid data for the mixed form or an FP32 V-cycle
+  const bool f32 = ctx->prm.precision == DFDG_MIXED || ctx->prm.mg_fp32;
+  const bool f16 = f32 && ctx->prm.mg_fine_fp16;
+  if (f32 && ctx->prm.precision != DFDG_MIXED) {  // (a MIXED context has them anyway)
+    A.vals32 = c.take<float>(h.vals.size());
+    A.dinv32 = c.take<float>(h.dinv.size());
+    A.binv32 = c.take<float>(h.binv.size());
+  }
   A.vals16 = f16 ? c.take<uint32_t>((size_t)nPairs(NF, A.ns) * E) : nullptr;
-  const bool amg = ctx->prm.precond == DFDG_AMG;
-  A.tdef = amg ? c.take<double>(nL) : nullptr;
-  A.tdef32 = amg && f32 ? c.take<float>(nL) : nullptr;
-  // work
-  ctx->Lbuf = c.take<double>(nU);
-  ctx->q = c.take<double>(nfac * NF * T);
-  A.mfq = mf_products(ctx) ? c.take<double>(2 * nL) : nullptr;
-  A.mfcond = d.cond;
-  A.mfQf = d.Qf;
-  A.mfK = ctx->K;
-  ctx->gv = c.take<double>(nL);
-  ctx->lamw = c.take<double>(nL);
-  ctx->lamx = c.take<double>(nL);
-  ctx->r = c.take<double>(nL);
-  ctx->rb = c.take<double>(nL);  // second residual buffer (multigrid PCG alternates)
-  ctx->z = c.take<double>(nL);
-  ctx->p[0] = c.take<double>(nL);
-  ctx->p[1] = c.take<double>(nL);
-  ctx->Sp = c.take<double>(nL);
-  ctx->Ustage = c.take<double>(nU);
-  for (int s = 0; s < kHistSlots; ++s)
-    for (int j = 0; j < kHistDepth; ++j) ctx->hist[s][j] = c.take<double>(nL);
-  for (int s = 0; s < 3; ++s) ctx->gbuf[s] = c.take<double>(nL);
-  ctx->proj_on = ctx->prm.extrapolate == DFDG_EXTRAPOLATE_PROJECT;
-  if (ctx->proj_on) {
-    for (int i = 0; i < kProjMax; ++i) {
-      ctx->pjX[i] = c.take<double>(nL);
-      ctx->pjSX[i] = c.take<double>(nL);
-    }
-    for (int i = 0; i < kProjKeep; ++i) {
-      ctx->pjRawL[i] = c.take<double>(nL);
-      ctx->pjRawG[i] = c.take<double>(nL);
-    }
-    ctx->pjx0 = c.take<double>(nL);
-    ctx->pjnrm = c.take<double>(kProjMax);
-    ctx->pjT = c.take<double>((size_t)kProjMax * kProjMax);
-    ctx->pjcA = c.take<double>(kProjMax);
-    ctx->pjcB = c.take<double>(kProjMax);
-    ctx->pjpart = c.take<double>((size_t)kProjGrid * kProjPart);
-  }
-  ctx->evaltab = c.take<double>((size_t)kMaxEvalPts * ctx->P);
-  const long maxblk = std::max((T + 127) / 128, (E + 255) / 256) + 1;
-  ctx->partials = c.take<double>(4 * maxblk);
-  ctx->diagres = c.take<double>(4);
-  ctx->xpart = c.take<double>(kExtrapParts);
-  const long G = g.fgrid;
-  for (PcgBufs* pb : {&ctx->pb, &ctx->pb32, &ctx->pbt}) {
-    pb->sc = c.take<PcgScalars>(1);
-    pb->gg = c.take<double>(3 * G);
-    pb->rz[0] = c.take<double>(2 * G);
-    pb->rz[1] = c.take<double>(2 * G);
-    pb->pq = c.take<double>(2 * G);
-    for (double*& pj : pb->pj) pj = c.take<double>(6 * kOneLaunchRows / 256);
-  }
-  if (mixed) {
-    ctx->L32 = c.take<float>(nU);
-    ctx->x32 = c.take<float>(nL);
-    ctx->r32 = c.take<float>(nL);
-    ctx->r32b = c.take<float>(nL);
-    ctx->z32 = c.take<float>(nL);
-    ctx->p32[0] = c.take<float>(nL);
-    ctx->p32[1] = c.take<float>(nL);
-    ctx->Sp32 = c.take<float>(nL);
-    ctx->r64 = c.take<double>(nL);
-  }
-  for (int s = 0; s < 3; ++s) ctx->Ustages[s] = c.take<double>(nU);
-  ctx->Ybar = c.take<double>(nU);
-  ctx->Wbuf = c.take<double>(nU);
+  A.tdef = c.take<double>(nL);
+  A.tdef32 = f32 ? c.take<float>(nL) : nullptr;
   // multigrid hierarchy: operators of levels >= 1, transfer operators, level vectors
-  MgDev& mg = ctx->mg;
-  mg = MgDev{};
   const AmgHierarchy& H = ctx->H;
   mg.nlev = (int)H.lv.size();
   // lanes per row: the largest power of two not above the mean row length (<= 64)
@@ -623,6 +522,135 @@ static void carve(dfdg_ctx* ctx, char* base) {
     mg.coarse_inv = c.take<double>(nd);
     mg.coarse_inv32 = f32 ? c.take<float>(nd) : nullptr;
   }
+}
+
+static void carve(dfdg_ctx* ctx, char* base) {
+  Carver c{base};
+  const HostSetup& h = ctx->hs;
+  const long T = ctx->T, E = ctx->E, NF = ctx->NF, nU = ctx->nU, nL = ctx->nL;
+  const RefTables& tb = h.tabs;
+  DevGeo& g = ctx->g;
+  g.T = (int)T;
+  g.E = (int)E;
+  // one thread per facet row, or two for split rows (facet_split)
+  const int parts = (int)(E * facet_split((int)NF, d3slots(ctx)));
+  g.fgrid = facet_grid_size(parts, ctx->prm.facet_blocks);
+  g.fblk = facet_block_size(parts, ctx->prm.facet_blocks);
+  const long dm = ctx->dim, nfac = dm + 1;
+  g.Jinv = c.take<double>(dm * dm * T);
+  g.detJ = c.take<double>(T);
+  g.isq = c.take<double>(T);
+  g.nbr = c.take<int>(nfac * T);
+  g.code = c.take<int>(nfac * T);
+  g.efacet = c.take<int>(nfac * T);
+  g.nx = c.take<double>(nfac * T);
+  g.ny = c.take<double>(nfac * T);
+  g.nz = dm == 3 ? c.take<double>(nfac * T) : nullptr;
+  g.flen = c.take<double>(nfac * T);
+  g.sig = c.take<double>(nfac * T);
+  g.sF = c.take<double>(nfac * T);
+  g.G = c.take<double>(h.G.size());
+  g.G4 = h.G4.empty() ? nullptr : c.take<double>(h.G4.size());
+  g.qL = c.take<int>(E);
+  g.qR = c.take<int>(E);
+  g.zdef = c.take<double>(E);
+  DevTabs& d = ctx->tb;
+  d.Vv = c.take<double>(tb.Vv.size());
+  d.Gv = c.take<double>(tb.Gv.size());
+  d.Wv = c.take<double>(tb.vw.size());
+  d.Vf = c.take<double>(tb.Vf.size());
+  d.Gf = c.take<double>(tb.Gf.size());
+  d.Wf = c.take<double>(tb.fw.size());
+  d.Vp = c.take<double>(tb.Vp.size());
+  d.Wp = c.take<double>(tb.pw.size());
+  d.Dh = c.take<double>(tb.Dh.size());
+  d.Ch = c.take<double>(tb.Ch.size());
+  d.Zh = tb.Zh.empty() ? nullptr : c.take<double>(tb.Zh.size());
+  d.fpidx = tb.fpidx.empty() ? nullptr : c.take<int>(tb.fpidx.size());
+  d.Qf = tb.Qf.empty() ? nullptr : c.take<double>(tb.Qf.size());
+  d.cond = tb.cond.empty() ? nullptr : c.take<double>(tb.cond.size());
+  d.res = tb.res.empty() ? nullptr : c.take<double>(tb.res.size());
+  DevBsr& A = ctx->A;
+  A.ns = d3slots(ctx);
+  A.cols = c.take<int>(h.cols.size());
+  A.vals = c.take<double>(h.vals.size());
+  A.dinv = c.take<double>(h.dinv.size());
+  A.binv = c.take<double>(h.binv.size());
+  const bool mixed = ctx->prm.precision == DFDG_MIXED;
+  // FP32 copies of S for the mixed form
+  A.vals32 = mixed ? c.take<float>(h.vals.size()) : nullptr;
+  A.dinv32 = mixed ? c.take<float>(h.dinv.size()) : nullptr;
+  A.binv32 = mixed ? c.take<float>(h.binv.size()) : nullptr;
+  A.vals16 = nullptr;
+  A.tdef = nullptr;
+  A.tdef32 = nullptr;
+  ctx->mg = MgDev{};
+  if (ctx->prm.precond == DFDG_AMG && !ctx->el_on) carve_cycle(ctx, c, A, ctx->mg);
+  // work
+  ctx->Lbuf = c.take<double>(nU);
+  ctx->q = c.take<double>(nfac * NF * T);
+  A.mfq = mf_products(ctx) ? c.take<double>(2 * nL) : nullptr;
+  A.mfcond = d.cond;
+  A.mfQf = d.Qf;
+  A.mfK = ctx->K;
+  ctx->gv = c.take<double>(nL);
+  ctx->lamw = c.take<double>(nL);
+  ctx->lamx = c.take<double>(nL);
+  ctx->r = c.take<double>(nL);
+  ctx->rb = c.take<double>(nL);  // second residual buffer (multigrid PCG alternates)
+  ctx->z = c.take<double>(nL);
+  ctx->p[0] = c.take<double>(nL);
+  ctx->p[1] = c.take<double>(nL);
+  ctx->Sp = c.take<double>(nL);
+  ctx->Ustage = c.take<double>(nU);
+  for (int s = 0; s < kHistSlots; ++s)
+    for (int j = 0; j < kHistDepth; ++j) ctx->hist[s][j] = c.take<double>(nL);
+  for (int s = 0; s < 3; ++s) ctx->gbuf[s] = c.take<double>(nL);
+  ctx->proj_on = ctx->prm.extrapolate == DFDG_EXTRAPOLATE_PROJECT;
+  if (ctx->proj_on) {
+    for (int i = 0; i < kProjMax; ++i) {
+      ctx->pjX[i] = c.take<double>(nL);
+      ctx->pjSX[i] = c.take<double>(nL);
+    }
+    for (int i = 0; i < kProjKeep; ++i) {
+      ctx->pjRawL[i] = c.take<double>(nL);
+      ctx->pjRawG[i] = c.take<double>(nL);
+    }
+    ctx->pjx0 = c.take<double>(nL);
+    ctx->pjnrm = c.take<double>(kProjMax);
+    ctx->pjT = c.take<double>((size_t)kProjMax * kProjMax);
+    ctx->pjcA = c.take<double>(kProjMax);
+    ctx->pjcB = c.take<double>(kProjMax);
+    ctx->pjpart = c.take<double>((size_t)kProjGrid * kProjPart);
+  }
+  ctx->evaltab = c.take<double>((size_t)kMaxEvalPts * ctx->P);
+  const long maxblk = std::max((T + 127) / 128, (E + 255) / 256) + 1;
+  ctx->partials = c.take<double>(4 * maxblk);
+  ctx->diagres = c.take<double>(4);
+  ctx->xpart = c.take<double>(kExtrapParts);
+  const long G = g.fgrid;
+  for (PcgBufs* pb : {&ctx->pb, &ctx->pb32, &ctx->pbt}) {
+    pb->sc = c.take<PcgScalars>(1);
+    pb->gg = c.take<double>(3 * G);
+    pb->rz[0] = c.take<double>(2 * G);
+    pb->rz[1] = c.take<double>(2 * G);
+    pb->pq = c.take<double>(2 * G);
+    for (double*& pj : pb->pj) pj = c.take<double>(6 * kOneLaunchRows / 256);
+  }
+  if (mixed) {
+    ctx->L32 = c.take<float>(nU);
+    ctx->x32 = c.take<float>(nL);
+    ctx->r32 = c.take<float>(nL);
+    ctx->r32b = c.take<float>(nL);
+    ctx->z32 = c.take<float>(nL);
+    ctx->p32[0] = c.take<float>(nL);
+    ctx->p32[1] = c.take<float>(nL);
+    ctx->Sp32 = c.take<float>(nL);
+    ctx->r64 = c.take<double>(nL);
+  }
+  for (int s = 0; s < 3; ++s) ctx->Ustages[s] = c.take<double>(nU);
+  ctx->Ybar = c.take<double>(nU);
+  ctx->Wbuf = c.take<double>(nU);
   if (ctx->el_on) {
     const ElimHost& h2 = ctx->eh;
     ElimDev& D = ctx->el;
@@ -673,6 +701,136 @@ template <typename T>
 static hipError_t up(T* dst, const std::vector<T>& src, hipStream_t s) {
   if (src.empty()) return hipSuccess;
   return hipMemcpyAsync(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, s);
+}
+
+// The FP32 copies of S and its diagonal blocks.
+static int upload_fp32(dfdg_ctx* ctx, const DevBsr& A) {
+  const HostSetup& h = ctx->hs;
+  hipStream_t s = ctx->stream;
+  std::vector<float> v(h.vals.begin(), h.vals.end()), d(h.dinv.begin(), h.dinv.end()),
+      b(h.binv.begin(), h.binv.end());
+  HIPC(up(const_cast<float*>(A.vals32), v, s));
+  HIPC(up(const_cast<float*>(A.dinv32), d, s));
+  HIPC(up(const_cast<float*>(A.binv32), b, s));
+  HIPC(hipStreamSynchronize(s));
+  return DFDG_OK;
+}
+
+// The arrays of carve_cycle, on the context's stream (done on return).
+static int upload_cycle(dfdg_ctx* ctx, DevBsr& A, MgDev& mg) {
+  const HostSetup& h = ctx->hs;
+  hipStream_t s = ctx->stream;
+  {  // S D^{-1} z, z = zdef on mode 0 (FP64 on the host)
+    const int NS = A.ns;
+    const long E = ctx->E, NF = ctx->NF;
+    std::vector<double> t((size_t)E * NF, 0.0);
+    for (long F = 0; F < E; ++F)
+      for (int sl = 0; sl < NS; ++sl) {
+        const long cc = h.cols[(size_t)sl * E + F];
+        const double w = h.dinv[(size_t)cc * NF] * h.zdef[cc];
+        for (long a = 0; a < NF; ++a) t[(size_t)F * NF + a] += h.vals[(((size_t)sl * NF + a) * NF + 0) * E + F] * w;
+      }
+    std::vector<float> t32(t.begin(), t.end());
+    HIPC(up(const_cast<double*>(A.tdef), t, s));
+    if (A.tdef32) HIPC(up(const_cast<float*>(A.tdef32), t32, s));
+    HIPC(hipStreamSynchronize(s));  // the host copies end with this block
+  }
+  if (A.vals16) {
+    double smax = 0;
+    for (double v : h.vals) smax = std::max(smax, std::fabs(v));
+    if (!(smax > 0)) smax = 1;
+    A.scale16 = (float)smax;
+    HIPC(launch_half_planes((long)A.ns * ctx->NF * ctx->NF, ctx->E, A.vals, 1.0 / smax, const_cast<uint32_t*>(A.vals16),
+                                s));
+  }
+  const bool mixed = A.vals32 != nullptr;  // FP32 copies were carved
+  const AmgHierarchy& H = ctx->H;
+  std::vector<std::vector<float>> keep;  // float staging buffers stay alive until the sync below
+  std::deque<std::vector<double>> keep_d;  // padded copies, likewise
+  std::deque<std::vector<int>> keep_i;
+  auto f32 = [&](const std::vector<double>& v) -> const std::vector<float>& {
+    keep.emplace_back(v.begin(), v.end());
+    return keep.back();
+  };
+  auto up_csr = [&](const Csr& M, DevCsr& D) -> int {
+    // padded row-major copy (see DevCsr)
+    std::vector<int> ce((size_t)M.n * D.w);
+    keep_d.emplace_back((size_t)M.n * D.w, 0.0);
+    std::vector<double>& ve = keep_d.back();
+    for (int i = 0; i < M.n; ++i) {
+      const int b = M.ptr[i], len = M.ptr[i + 1] - b;
+      for (int k = 0; k < D.w; ++k) {
+        ce[(size_t)i * D.w + k] = len ? M.col[b + std::min(k, len - 1)] : 0;
+        if (k < len) ve[(size_t)i * D.w + k] = M.val[b + k];
+      }
+    }
+    keep_i.push_back(std::move(ce));
+    HIPC(up(const_cast<int*>(D.col), keep_i.back(), s));
+    HIPC(up(const_cast<double*>(D.val), ve, s));
+    if (mixed) HIPC(up(const_cast<float*>(D.val32), f32(ve), s));
+    return DFDG_OK;
+  };
+  keep.reserve(8 * kMaxLev + 2);
+  for (int l = 0; l < mg.nlev; ++l) {
+    const AmgLevel& L = H.lv[l];
+    if (l > 0 && l < mg.nlev - 1) {
+      if (int rc = up_csr(L.Rs, mg.Rs[l])) return rc;
+      if (int rc = up_csr(L.Ps, mg.Ps[l])) return rc;
+    }
+  }
+  if (mg.nlev > 1) {
+    const DevXfer& X = mg.X0;
+    const Csr& P = H.lv[0].P;
+    const int NF = (int)ctx->NF, E = X.E;
+    const size_t np = (size_t)X.w * E, nr = (size_t)X.n * X.wr;
+    keep_i.emplace_back(np, 0);
+    std::vector<int>& pc = keep_i.back();
+    keep_i.emplace_back(nr, 0);
+    std::vector<int>& rc = keep_i.back();
+    keep_d.emplace_back(np * NF, 0.0);
+    std::vector<double>& pv = keep_d.back();
+    keep_d.emplace_back(nr * NF, 0.0);
+    std::vector<double>& rv = keep_d.back();
+    std::vector<int> fill(X.n, 0);
+    double vmax = 0;
+    for (int F = 0; F < E; ++F) {
+      const int b = H.p0_ptr[F], len = H.p0_ptr[F + 1] - b;
+      for (int j = 0; j < X.w; ++j) pc[(size_t)j * E + F] = len ? H.p0_col[b + std::min(j, len - 1)] : 0;
+      for (int j = 0; j < len; ++j) rc[(size_t)H.p0_col[b + j] * X.wr + fill[H.p0_col[b + j]]++] = F;
+      for (int a = 0; a < NF; ++a)
+        for (int k = P.ptr[F * NF + a], j = 0; k < P.ptr[F * NF + a + 1]; ++k, ++j) {
+          if (j >= len || H.p0_col[b + j] != P.col[k])  // (rows of a facet mostly list the same columns)
+            j = (int)(std::find(H.p0_col.begin() + b, H.p0_col.begin() + b + len, P.col[k]) - H.p0_col.begin()) - b;
+          pv[((size_t)j * NF + a) * E + F] = P.val[k];
+          rv[((size_t)P.col[k] * X.wr + fill[P.col[k]] - 1) * NF + a] = P.val[k];
+          vmax = std::max(vmax, std::fabs(P.val[k]));
+        }
+    }
+    for (int i = 0; i < X.n; ++i)
+      for (int k = std::max(fill[i], 1); k < X.wr; ++k) rc[(size_t)i * X.wr + k] = rc[(size_t)i * X.wr + std::max(fill[i], 1) - 1];
+    HIPC(up(const_cast<int*>(X.pcol), pc, s));
+    HIPC(up(const_cast<int*>(X.rcol), rc, s));
+    HIPC(up(const_cast<double*>(X.pval), pv, s));
+    HIPC(up(const_cast<double*>(X.rval), rv, s));
+    if (X.pval32) {
+      HIPC(up(const_cast<float*>(X.pval32), f32(pv), s));
+      HIPC(up(const_cast<float*>(X.rval32), f32(rv), s));
+    }
+    if (X.half) {  // the same values in P and R: the same scale and rounding
+      if (!(vmax > 0)) vmax = 1;
+      mg.X0.pscale = (float)vmax;
+      HIPC(launch_half_planes((long)X.w * NF, E, X.pval, 1.0 / vmax, const_cast<uint32_t*>(X.pval16), s));
+      HIPC(launch_col_planes(X.w, E, X.pcol, const_cast<uint32_t*>(X.pcol16), s));
+      HIPC(launch_half_entries(NF, (long)nr, X.rval, 1.0 / vmax, const_cast<uint32_t*>(X.rval16), s));
+    }
+  }
+  if (mg.nlev > 0) {
+    const std::vector<double>& dense = mg.fold ? H.coarse_fold : H.coarse_inv;
+    HIPC(up(const_cast<double*>(mg.coarse_inv), dense, s));
+    if (mixed) HIPC(up(const_cast<float*>(mg.coarse_inv32), f32(dense), s));
+  }
+  HIPC(hipStreamSynchronize(s));
+  return DFDG_OK;
 }
 
 extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
@@ -728,127 +886,10 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
   HIPC(up(const_cast<double*>(ctx->A.vals), h.vals, s));
   HIPC(up(const_cast<double*>(ctx->A.dinv), h.dinv, s));
   HIPC(up(const_cast<double*>(ctx->A.binv), h.binv, s));
-  if (ctx->A.tdef) {  // S D^{-1} z, z = zdef on mode 0 (FP64 on the host)
-    const int NS = ctx->A.ns;
-    const long E = ctx->E, NF = ctx->NF;
-    std::vector<double> t((size_t)E * NF, 0.0);
-    for (long F = 0; F < E; ++F)
-      for (int sl = 0; sl < NS; ++sl) {
-        const long cc = h.cols[(size_t)sl * E + F];
-        const double w = h.dinv[(size_t)cc * NF] * h.zdef[cc];
-        for (long a = 0; a < NF; ++a) t[(size_t)F * NF + a] += h.vals[(((size_t)sl * NF + a) * NF + 0) * E + F] * w;
-      }
-    std::vector<float> t32(t.begin(), t.end());
-    HIPC(up(const_cast<double*>(ctx->A.tdef), t, s));
-    if (ctx->A.tdef32) HIPC(up(const_cast<float*>(ctx->A.tdef32), t32, s));
-    HIPC(hipStreamSynchronize(s));  // the host copies end with this block
-  }
-  if (ctx->A.vals32) {
-    std::vector<float> v(h.vals.begin(), h.vals.end()), d(h.dinv.begin(), h.dinv.end()),
-        b(h.binv.begin(), h.binv.end());
-    HIPC(up(const_cast<float*>(ctx->A.vals32), v, s));
-    HIPC(up(const_cast<float*>(ctx->A.dinv32), d, s));
-    HIPC(up(const_cast<float*>(ctx->A.binv32), b, s));
-    HIPC(hipStreamSynchronize(s));
-  }
-  if (ctx->A.vals16) {
-    double smax = 0;
-    for (double v : h.vals) smax = std::max(smax, std::fabs(v));
-    if (!(smax > 0)) smax = 1;
-    ctx->A.scale16 = (float)smax;
-    HIPC(launch_half_planes((long)ctx->A.ns * ctx->NF * ctx->NF, ctx->E, ctx->A.vals, 1.0 / smax, const_cast<uint32_t*>(ctx->A.vals16),
-                                s));
-  }
-  {
-    const bool mixed = ctx->A.vals32 != nullptr;  // FP32 copies were carved
-    const AmgHierarchy& H = ctx->H;
-    MgDev& mg = ctx->mg;
-    std::vector<std::vector<float>> keep;  // float staging buffers stay alive until the sync below
-    std::deque<std::vector<double>> keep_d;  // padded copies, likewise
-    std::deque<std::vector<int>> keep_i;
-    auto f32 = [&](const std::vector<double>& v) -> const std::vector<float>& {
-      keep.emplace_back(v.begin(), v.end());
-      return keep.back();
-    };
-    auto up_csr = [&](const Csr& M, DevCsr& D) -> int {
-      // padded row-major copy (see DevCsr)
-      std::vector<int> ce((size_t)M.n * D.w);
-      keep_d.emplace_back((size_t)M.n * D.w, 0.0);
-      std::vector<double>& ve = keep_d.back();
-      for (int i = 0; i < M.n; ++i) {
-        const int b = M.ptr[i], len = M.ptr[i + 1] - b;
-        for (int k = 0; k < D.w; ++k) {
-          ce[(size_t)i * D.w + k] = len ? M.col[b + std::min(k, len - 1)] : 0;
-          if (k < len) ve[(size_t)i * D.w + k] = M.val[b + k];
-        }
-      }
-      keep_i.push_back(std::move(ce));
-      HIPC(up(const_cast<int*>(D.col), keep_i.back(), s));
-      HIPC(up(const_cast<double*>(D.val), ve, s));
-      if (mixed) HIPC(up(const_cast<float*>(D.val32), f32(ve), s));
-      return DFDG_OK;
-    };
-    keep.reserve(8 * kMaxLev + 2);
-    for (int l = 0; l < mg.nlev; ++l) {
-      const AmgLevel& L = H.lv[l];
-      if (l > 0 && l < mg.nlev - 1) {
-        if (int rc = up_csr(L.Rs, mg.Rs[l])) return rc;
-        if (int rc = up_csr(L.Ps, mg.Ps[l])) return rc;
-      }
-    }
-    if (mg.nlev > 1) {
-      const DevXfer& X = mg.X0;
-      const Csr& P = H.lv[0].P;
-      const int NF = (int)ctx->NF, E = X.E;
-      const size_t np = (size_t)X.w * E, nr = (size_t)X.n * X.wr;
-      keep_i.emplace_back(np, 0);
-      std::vector<int>& pc = keep_i.back();
-      keep_i.emplace_back(nr, 0);
-      std::vector<int>& rc = keep_i.back();
-      keep_d.emplace_back(np * NF, 0.0);
-      std::vector<double>& pv = keep_d.back();
-      keep_d.emplace_back(nr * NF, 0.0);
-      std::vector<double>& rv = keep_d.back();
-      std::vector<int> fill(X.n, 0);
-      double vmax = 0;
-      for (int F = 0; F < E; ++F) {
-        const int b = H.p0_ptr[F], len = H.p0_ptr[F + 1] - b;
-        for (int j = 0; j < X.w; ++j) pc[(size_t)j * E + F] = len ? H.p0_col[b + std::min(j, len - 1)] : 0;
-        for (int j = 0; j < len; ++j) rc[(size_t)H.p0_col[b + j] * X.wr + fill[H.p0_col[b + j]]++] = F;
-        for (int a = 0; a < NF; ++a)
-          for (int k = P.ptr[F * NF + a], j = 0; k < P.ptr[F * NF + a + 1]; ++k, ++j) {
-            if (j >= len || H.p0_col[b + j] != P.col[k])  // (rows of a facet mostly list the same columns)
-              j = (int)(std::find(H.p0_col.begin() + b, H.p0_col.begin() + b + len, P.col[k]) - H.p0_col.begin()) - b;
-            pv[((size_t)j * NF + a) * E + F] = P.val[k];
-            rv[((size_t)P.col[k] * X.wr + fill[P.col[k]] - 1) * NF + a] = P.val[k];
-            vmax = std::max(vmax, std::fabs(P.val[k]));
-          }
-      }
-      for (int i = 0; i < X.n; ++i)
-        for (int k = std::max(fill[i], 1); k < X.wr; ++k) rc[(size_t)i * X.wr + k] = rc[(size_t)i * X.wr + std::max(fill[i], 1) - 1];
-      HIPC(up(const_cast<int*>(X.pcol), pc, s));
-      HIPC(up(const_cast<int*>(X.rcol), rc, s));
-      HIPC(up(const_cast<double*>(X.pval), pv, s));
-      HIPC(up(const_cast<double*>(X.rval), rv, s));
-      if (X.pval32) {
-        HIPC(up(const_cast<float*>(X.pval32), f32(pv), s));
-        HIPC(up(const_cast<float*>(X.rval32), f32(rv), s));
-      }
-      if (X.half) {  // the same values in P and R: the same scale and rounding
-        if (!(vmax > 0)) vmax = 1;
-        mg.X0.pscale = (float)vmax;
-        HIPC(launch_half_planes((long)X.w * NF, E, X.pval, 1.0 / vmax, const_cast<uint32_t*>(X.pval16), s));
-        HIPC(launch_col_planes(X.w, E, X.pcol, const_cast<uint32_t*>(X.pcol16), s));
-        HIPC(launch_half_entries(NF, (long)nr, X.rval, 1.0 / vmax, const_cast<uint32_t*>(X.rval16), s));
-      }
-    }
-    if (mg.nlev > 0) {
-      const std::vector<double>& dense = mg.fold ? H.coarse_fold : H.coarse_inv;
-      HIPC(up(const_cast<double*>(mg.coarse_inv), dense, s));
-      if (mixed) HIPC(up(const_cast<float*>(mg.coarse_inv32), f32(dense), s));
-    }
-    HIPC(hipStreamSynchronize(s));
-  }
+  if (ctx->A.vals32)
+    if (int rc = upload_fp32(ctx, ctx->A)) return rc;
+  if (ctx->mg.nlev > 0)
+    if (int rc = upload_cycle(ctx, ctx->A, ctx->mg)) return rc;
   if (ctx->el_on) {
     const ElimHost& e = ctx->eh;
     ElimDev& D = ctx->el;
@@ -891,6 +932,34 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
   for (int i = 0; i < 3; ++i) ctx->hist_count[i] = 0;
   invalidate_guesses(ctx);
   return DFDG_OK;
+}
+
+// The cycle of a context for the debug and measurement entry points: its own, or, where the
+// elimination takes its place, one set up for the call in device memory that ends with it.
+struct CycleOf {
+  DevBsr A;
+  MgDev mg;
+  void* mem = nullptr;
+  ~CycleOf() {
+    if (mem) (void)hipFree(mem);
+  }
+};
+static int cycle_of(dfdg_ctx* ctx, CycleOf& c) {
+  c.A = ctx->A;
+  c.mg = ctx->mg;
+  if (!ctx->el_on) return DFDG_OK;
+  std::string e;
+  if (const int rc = need_hierarchy(ctx, e)) return fail(ctx, rc, e);
+  Carver count{nullptr};
+  carve_cycle(ctx, count, c.A, c.mg);
+  HIPC(hipMalloc(&c.mem, count.off));
+  c.A = ctx->A;
+  Carver take{(char*)c.mem};
+  carve_cycle(ctx, take, c.A, c.mg);
+  HIPC(hipMemsetAsync(c.mem, 0, count.off, ctx->stream));
+  if (ctx->prm.precision != DFDG_MIXED && c.A.vals32)
+    if (const int rc = upload_fp32(ctx, c.A)) return rc;
+  return upload_cycle(ctx, c.A, c.mg);
 }
 
 extern "C" const char* dfdg_last_error(const dfdg_ctx* ctx) {
@@ -1007,7 +1076,7 @@ static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGrap
   // the stopping test, so a run of n iterations takes n launches; otherwise the next
   // iteration's first kernel applies it and a run takes n + 1
   // (the elimination likewise; the one-launch Jacobi iteration tests the residual before last)
-  const int extra = (amg && ctx->mg.nlev >= 2) ? 0 : (one_launch_jacobi(ctx) && sc == ctx->pb.sc) ? 2 : 1;
+  const int extra = (amg && (ctx->el_on || ctx->mg.nlev >= 2)) ? 0 : (one_launch_jacobi(ctx) && sc == ctx->pb.sc) ? 2 : 1;
   // the first chunk: the fewest iterations among the last kHintRuns runs.  With start
   // values that vary in quality the count varies from solve to solve; a chunk that falls
   // short costs one host round trip, while each iteration enqueued past the end still runs
@@ -1748,6 +1817,8 @@ extern "C" int dfdg_debug_vcycle(dfdg_ctx* ctx, const double* b, double* z) {
   NEED_BOUND(ctx);
   if (!b || !z) return fail(ctx, DFDG_E_INVALID_ARG, "null pointer");
   if (ctx->prm.precond != DFDG_AMG) return fail(ctx, DFDG_E_INVALID_ARG, "V-cycle needs an AMG context");
+  CycleOf cy;
+  if (const int rc = cycle_of(ctx, cy)) return rc;
   hipStream_t s = ctx->stream;
   const long NF = ctx->NF;
   const PcgBufs& pb = ctx->pbt;
@@ -1757,8 +1828,8 @@ extern "C" int dfdg_debug_vcycle(dfdg_ctx* ctx, const double* b, double* z) {
   const long G = ctx->g.fgrid;
   HIPC(launch_fill(2 * G, 1.0, pb.rz[0], s));
   HIPC(hipMemcpyAsync(ctx->r, b, ctx->nL * sizeof(double), hipMemcpyDeviceToDevice, s));
-  if (ctx->prm.mg_fp32) HIPC((launch_vcycle<float, double>(NF, ctx->g, ctx->A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
-  else HIPC((launch_vcycle<double, double>(NF, ctx->g, ctx->A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
+  if (ctx->prm.mg_fp32) HIPC((launch_vcycle<float, double>(NF, ctx->g, cy.A, cy.mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
+  else HIPC((launch_vcycle<double, double>(NF, ctx->g, cy.A, cy.mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s)));
   HIPC(hipMemcpyAsync(z, ctx->z, ctx->nL * sizeof(double), hipMemcpyDeviceToDevice, s));
   HIPC(hipStreamSynchronize(s));
   return DFDG_OK;
@@ -1770,6 +1841,9 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
   if (which == 3 && ctx->prm.precision != DFDG_MIXED) return fail(ctx, DFDG_E_INVALID_ARG, "FP32 SpMV needs a MIXED context");
   if (which == 4 && ctx->prm.precond != DFDG_AMG) return fail(ctx, DFDG_E_INVALID_ARG, "V-cycle needs an AMG context");
   if (which < 0 || which > 6) return fail(ctx, DFDG_E_INVALID_ARG, "unknown kernel id");
+  CycleOf cy;
+  if (which == 4)
+    if (const int rc = cycle_of(ctx, cy)) return rc;
   hipStream_t s = ctx->stream;
   const long T = ctx->T, E = ctx->E, NF = ctx->NF, P = ctx->P, NS = ctx->A.ns;
   // a running PCG state whose stopping test never fires, and finite partials
@@ -1792,8 +1866,8 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
         return el_recover(ctx, false, ctx->Lbuf, ctx->lamx, ctx->Ustage, 1, 0.5, ctx->Ustage, 0.5, ctx->Ustage, 1e-30,
                           s);
       case 4:
-        if (ctx->prm.mg_fp32) return launch_vcycle<float, double>(NF, ctx->g, ctx->A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s);
-        return launch_vcycle<double, double>(NF, ctx->g, ctx->A, ctx->mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s);
+        if (ctx->prm.mg_fp32) return launch_vcycle<float, double>(NF, ctx->g, cy.A, cy.mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s);
+        return launch_vcycle<double, double>(NF, ctx->g, cy.A, cy.mg, ctx->r, ctx->z, pb.rz[0], pb.sc, s);
       default: return launch_pcg32_spmv(NF, ctx->g, ctx->A, ctx->z32, ctx->p32[0], ctx->p32[1], ctx->Sp32, pb, 2, s);
     }
   };
@@ -1854,7 +1928,7 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
         // 2 bytes where they are stored so), vectors once.  Values and vectors in the cycle's
         // precision (8 or 4 bytes; finest-level S in 2 bytes when it is stored in FP16).
         const double vb = ctx->prm.mg_fp32 ? 4.0 : 8.0;
-        const double sv = ctx->A.vals16 ? 4.0 * nPairs(NF, NS) / (NS * NF * NF) : vb;
+        const double sv = cy.A.vals16 ? 4.0 * nPairs(NF, NS) / (NS * NF * NF) : vb;
         const double sbytes = E * (NS * NF * NF * sv + NS * 4.0);
         b = 4 * sbytes + 17.0 * E * NF * vb;
         const AmgHierarchy& H = ctx->H;
@@ -1862,7 +1936,7 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
           const AmgLevel& L = H.lv[l];
           const double nn = H.lv[l + 1].A.n;
           if (l == 0) {  // transfers of the finest level by facets: a column for NF values each way
-            const DevXfer& X = ctx->mg.X0;
+            const DevXfer& X = cy.mg.X0;
             const double np = (double)H.p0_col.size();
             b += X.half ? np * ((2.0 + NF * 2.0) + (4.0 + (NF + 1) / 2 * 4.0)) : 2.0 * np * (4.0 + NF * vb);
             b += (2.0 * L.A.n + 2.0 * nn) * vb;
@@ -1948,6 +2022,8 @@ extern "C" int dfdg_debug_multigrid_matrix(const dfdg_ctx* ctx, int level, int w
                                            int64_t* n_cols, int64_t* nnz, int64_t* ptr, int32_t* cols,
                                            double* vals) {
   if (!ctx || !n_rows || !n_cols || !nnz) return DFDG_E_INVALID_ARG;
+  std::string e;
+  if (const int rc = need_hierarchy(const_cast<dfdg_ctx*>(ctx), e)) return fail(const_cast<dfdg_ctx*>(ctx), rc, e);
   const int L = (int)ctx->H.lv.size();
   if (level < 0 || level >= L || which < 0 || which > 4) return DFDG_E_INVALID_ARG;
   if (which == 2) {  // dense coarsest pseudo-inverse, as a full CSR
@@ -1984,6 +2060,8 @@ extern "C" int dfdg_debug_multigrid_matrix(const dfdg_ctx* ctx, int level, int w
 extern "C" int dfdg_debug_multigrid(const dfdg_ctx* ctx, int max_levels, int* n_levels, int64_t* rows,
                                     int64_t* nnz, double* rho) {
   if (!ctx || !n_levels || max_levels < 0 || (max_levels > 0 && (!rows || !nnz || !rho))) return DFDG_E_INVALID_ARG;
+  std::string e;
+  if (const int rc = need_hierarchy(const_cast<dfdg_ctx*>(ctx), e)) return fail(const_cast<dfdg_ctx*>(ctx), rc, e);
   const int L = (int)ctx->H.lv.size();
   *n_levels = L;
   for (int l = 0; l < std::min(L, max_levels); ++l) {
