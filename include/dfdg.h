@@ -276,6 +276,14 @@ int dfdg_ctx_workspace_bytes(const dfdg_ctx* ctx, size_t* bytes);
 /* dev_ptr: 256-byte aligned device memory of at least the reported size.  Uploads
  * the setup data (synchronous). */
 int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev_ptr, size_t bytes);
+/* The same in two parts: the workspace proper, and scratch that only the bind works in (the
+ * factorisation of a context that solves by elimination, up to three times its workspace; else
+ * 0 bytes).  scratch_ptr: 256-byte aligned; the caller's again when the bind returns.
+ * dfdg_ctx_workspace_bytes reports the sum, and dfdg_ctx_bind_workspace takes both from one
+ * block, whose end then stays unused. */
+int dfdg_ctx_setup_bytes(const dfdg_ctx* ctx, size_t* workspace_bytes, size_t* scratch_bytes);
+int dfdg_ctx_bind_workspace_scratch(dfdg_ctx* ctx, void* dev_ptr, size_t bytes, void* scratch_ptr,
+                                    size_t scratch_bytes);
 const char* dfdg_last_error(const dfdg_ctx* ctx);
 void dfdg_ctx_destroy(dfdg_ctx* ctx);
 

@@ -35,7 +35,7 @@ struct dfdg_ctx {
   int dim = 2;  // 2: triangles, 3: tetrahedra
   int K = 0, P = 0, NF = 0, T = 0, E = 0;
   long nU = 0, nL = 0;
-  size_t ws_need = 0;
+  size_t ws_need = 0, scratch_need = 0;  // kept; used by the bind only
   char* ws = nullptr;
   bool bound = false;
   DevGeo g{};
@@ -679,22 +679,44 @@ static void carve(dfdg_ctx* ctx, char* base) {
     D.mat = c.take<float>(h2.mvals);
     D.tmat = c.take<float>(n * ld);
     D.contrib = c.take<float>(h2.ngam.size() * NF);
-    D.front = c.take<double>(h2.fvals);
-    D.top = c.take<double>(n * n);
-    const size_t pan = 32 * std::max((size_t)h2.nc * h2.maxV, n);
-    D.panW = c.take<double>(pan);
-    D.panR = c.take<double>(pan);
-    ctx->elST = c.take<double>(h.ST.size());
   }
-  ctx->ws_need = c.off + 256;
+  ctx->ws_need = ((c.off + 255) & ~size_t(255)) + 256;
 }
 
-extern "C" int dfdg_ctx_workspace_bytes(const dfdg_ctx* cctx, size_t* bytes) {
-  if (!cctx || !bytes) return DFDG_E_INVALID_ARG;
+// What the elimination's factorisation works in while the workspace is bound.
+static void carve_scratch(dfdg_ctx* ctx, char* base) {
+  Carver c{base};
+  ElimDev& D = ctx->el;
+  D.front = D.top = D.panW = D.panR = ctx->elST = nullptr;
+  if (ctx->el_on) {
+    const ElimHost& h = ctx->eh;
+    const size_t n = (size_t)h.ng * ctx->NF, pan = 32 * std::max((size_t)h.nc * h.maxV, n);
+    D.front = c.take<double>(h.fvals);
+    D.top = c.take<double>(n * n);
+    D.panW = c.take<double>(pan);
+    D.panR = c.take<double>(pan);
+    ctx->elST = c.take<double>(ctx->hs.ST.size());
+  }
+  ctx->scratch_need = c.off;
+}
+
+extern "C" int dfdg_ctx_setup_bytes(const dfdg_ctx* cctx, size_t* workspace, size_t* scratch) {
+  if (!cctx || !workspace || !scratch) return DFDG_E_INVALID_ARG;
   auto* ctx = const_cast<dfdg_ctx*>(cctx);
-  if (!ctx->bound) carve(ctx, nullptr);
-  *bytes = ctx->ws_need;
+  if (!ctx->bound) {
+    carve(ctx, nullptr);
+    carve_scratch(ctx, nullptr);
+  }
+  *workspace = ctx->ws_need;
+  *scratch = ctx->scratch_need;
   return DFDG_OK;
+}
+extern "C" int dfdg_ctx_workspace_bytes(const dfdg_ctx* ctx, size_t* bytes) {
+  size_t ws = 0, scratch = 0;
+  if (!bytes) return DFDG_E_INVALID_ARG;
+  const int rc = dfdg_ctx_setup_bytes(ctx, &ws, &scratch);
+  if (!rc) *bytes = ws + scratch;
+  return rc;
 }
 
 template <typename T>
@@ -835,17 +857,33 @@ static int upload_cycle(dfdg_ctx* ctx, DevBsr& A, MgDev& mg) {
 
 extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
   if (!ctx || !dev) return DFDG_E_INVALID_ARG;
-  if (((uintptr_t)dev & 255) != 0) return fail(ctx, DFDG_E_WORKSPACE, "workspace must be 256-byte aligned");
   carve(ctx, nullptr);
+  carve_scratch(ctx, nullptr);
+  const size_t ws = ctx->ws_need, scratch = ctx->scratch_need;
+  if (bytes < ws + scratch)
+    return fail(ctx, DFDG_E_WORKSPACE, "workspace too small: need " + std::to_string(ws + scratch) + " bytes");
+  return dfdg_ctx_bind_workspace_scratch(ctx, dev, ws, scratch ? (char*)dev + ws : nullptr, scratch);
+}
+
+extern "C" int dfdg_ctx_bind_workspace_scratch(dfdg_ctx* ctx, void* dev, size_t bytes, void* scratch,
+                                               size_t scratch_bytes) {
+  if (!ctx || !dev) return DFDG_E_INVALID_ARG;
+  if ((((uintptr_t)dev | (uintptr_t)scratch) & 255) != 0)
+    return fail(ctx, DFDG_E_WORKSPACE, "workspace must be 256-byte aligned");
+  carve(ctx, nullptr);
+  carve_scratch(ctx, nullptr);
   const size_t need = ctx->ws_need;
   if (bytes < need)
     return fail(ctx, DFDG_E_WORKSPACE, "workspace too small: need " + std::to_string(need) + " bytes");
+  if (ctx->scratch_need > 0 && (!scratch || scratch_bytes < ctx->scratch_need))
+    return fail(ctx, DFDG_E_WORKSPACE, "scratch too small: need " + std::to_string(ctx->scratch_need) + " bytes");
   ctx->ws = (char*)dev;
   carve(ctx, ctx->ws);
   if (ctx->ws_need != need) {  // both passes must lay out the same arrays
     ctx->ws = nullptr;
     return fail(ctx, DFDG_E_WORKSPACE, "internal error: workspace layout differs between passes");
   }
+  carve_scratch(ctx, (char*)scratch);
   const HostSetup& h = ctx->hs;
   hipStream_t s = ctx->stream;
   HIPC(hipMemsetAsync(ctx->ws, 0, ctx->ws_need - 256, s));
@@ -922,7 +960,8 @@ extern "C" int dfdg_ctx_bind_workspace(dfdg_ctx* ctx, void* dev, size_t bytes) {
     HIPC(up(const_cast<double*>(D.zhat), zhat, s));
     HIPC(up(ctx->elST, h.ST, s));
     HIPC(launch_elim_factor(D, ctx->dim + 1, ctx->elST, shift, s));
-    HIPC(hipStreamSynchronize(s));  // the host lists end with this block
+    HIPC(hipStreamSynchronize(s));  // the host lists end with this block, the scratch with this call
+    D.front = D.top = D.panW = D.panR = ctx->elST = nullptr;
   }
   HIPC(hipStreamSynchronize(s));
   if (!ctx->pinned) HIPC(hipHostMalloc((void**)&ctx->pinned, 4 * sizeof(PcgScalars), hipHostMallocDefault));

@@ -89,6 +89,8 @@ _SIGS = {
     "dfdg_ctx_sizes": (ctypes.c_int, [_P, ctypes.POINTER(Sizes)]),
     "dfdg_ctx_workspace_bytes": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_size_t)]),
     "dfdg_ctx_bind_workspace": (ctypes.c_int, [_P, _P, ctypes.c_size_t]),
+    "dfdg_ctx_setup_bytes": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t)]),
+    "dfdg_ctx_bind_workspace_scratch": (ctypes.c_int, [_P, _P, ctypes.c_size_t, _P, ctypes.c_size_t]),
     "dfdg_last_error": (ctypes.c_char_p, [_P]),
     "dfdg_ctx_destroy": (None, [_P]),
     "dfdg_proj_rule": (ctypes.c_int, [_P, _P, _P]),
@@ -262,12 +264,17 @@ class Solver:
         self.sizes = s
         self.T, self.E, self.k, self.P, self.dim = s.T, s.E, s.k, s.P, s.dim
         self.n_broken, self.n_lambda, self.n_bdm, self.nq_proj = s.n_broken, s.n_lambda, s.n_bdm, s.nq_proj
-        nb = ctypes.c_size_t()
-        self._check(lib.dfdg_ctx_workspace_bytes(h, ctypes.byref(nb)))
+        nb, ns = ctypes.c_size_t(), ctypes.c_size_t()
+        self._check(lib.dfdg_ctx_setup_bytes(h, ctypes.byref(nb), ctypes.byref(ns)))
         self.workspace = torch.empty(nb.value + 256, dtype=torch.uint8, device=self.device)
         base = self.workspace.data_ptr()
         off = (-base) % 256
-        self._check(lib.dfdg_ctx_bind_workspace(h, ctypes.c_void_p(base + off), nb.value))
+        with torch.cuda.stream(self.stream):  # work still queued on the scratch's memory goes first
+            scratch = torch.empty(ns.value + 256, dtype=torch.uint8, device=self.device)
+        soff = (-scratch.data_ptr()) % 256
+        self._check(lib.dfdg_ctx_bind_workspace_scratch(h, ctypes.c_void_p(base + off), nb.value,
+                                                        ctypes.c_void_p(scratch.data_ptr() + soff), ns.value))
+        del scratch  # the bind has waited for its last use
         t3 = time.perf_counter()
         # wall-clock seconds of the set-up calls: mesh (facet matching), context (host set-up:
         # tabulations, geometry, element condensation, facet matrix, multigrid hierarchy),

@@ -92,3 +92,58 @@ def test_debug_entries_of_the_cycle(dim, N, k, kw):
         assert ms > 0 and torch.equal(z, z2) and torch.equal(s.mass_solve(F)[0], U)
         out.append((z, nbytes, s.mg_levels()))
     assert torch.equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
+
+
+def test_workspace_without_the_scratch():
+    """The factorisation's arrays (fronts, interface and panels in FP64, the element matrices) are
+    no part of what a context keeps: that stays below half of the whole."""
+    lib = lib_mod.load_library()
+    mesh = lib_mod.Mesh(*periodic_kuhn_cube(7, "morton"))
+    sizes = {}
+    for elim in (1, 2):
+        rc, h, _ = _create(mesh, k=2, elimination=elim)
+        assert rc == 0
+        ws, scratch, total = (ctypes.c_size_t() for _ in range(3))
+        assert lib.dfdg_ctx_setup_bytes(h, ctypes.byref(ws), ctypes.byref(scratch)) == 0
+        assert lib.dfdg_ctx_workspace_bytes(h, ctypes.byref(total)) == 0
+        assert total.value == ws.value + scratch.value and ws.value % 256 == 0
+        sizes[elim] = (ws.value, scratch.value)
+        lib.dfdg_ctx_destroy(h)
+    assert sizes[1][1] == 0 and sizes[2][0] < sizes[2][1]
+
+
+@pytest.mark.gpu
+def test_scratch_is_given_back():
+    """Solves do not read the scratch after the bind (overwritten here), a bind with too little of
+    it is refused, and one block for both parts gives the same solution."""
+    from gpu_util import make_pair
+    lib = lib_mod.load_library()
+    _, s, _, _ = make_pair(20, 2, oracle=False, precond="amg", elimination=True)
+    F = torch.randn(s.n_broken, generator=torch.Generator().manual_seed(2), dtype=torch.float64).to(s.device)
+    U = s.mass_solve(F)[0]
+    ws, scratch = ctypes.c_size_t(), ctypes.c_size_t()
+    p, mesh = s.params, s.mesh
+    out = []
+    for split in (True, False):
+        c = ctypes.c_void_p()
+        assert lib.dfdg_ctx_create(mesh._h, ctypes.byref(p), ctypes.c_void_p(s.stream.cuda_stream), ctypes.byref(c)) == 0
+        assert lib.dfdg_ctx_setup_bytes(c, ctypes.byref(ws), ctypes.byref(scratch)) == 0
+        mem = torch.empty(ws.value + scratch.value + 512, dtype=torch.uint8, device=s.device)
+        a = mem.data_ptr() + (-mem.data_ptr()) % 256
+        if split:
+            b = a + ws.value
+            short = lib.dfdg_ctx_bind_workspace_scratch(c, ctypes.c_void_p(a), ws.value, ctypes.c_void_p(b), scratch.value - 1)
+            assert short == -3 and lib.dfdg_ctx_bind_workspace_scratch(c, ctypes.c_void_p(a), ws.value, None, 0) == -3
+            assert lib.dfdg_ctx_bind_workspace_scratch(c, ctypes.c_void_p(a), ws.value, ctypes.c_void_p(b), scratch.value) == 0
+            mem[b - mem.data_ptr():].fill_(255)  # NaN
+        else:
+            assert lib.dfdg_ctx_bind_workspace(c, ctypes.c_void_p(a), ws.value + scratch.value - 1) == -3
+            assert lib.dfdg_ctx_bind_workspace(c, ctypes.c_void_p(a), ws.value + scratch.value) == 0
+        V = torch.empty_like(U)
+        info = lib_mod.SolveInfo()
+        assert lib.dfdg_hdiv_mass_solve(c, ctypes.c_void_p(F.data_ptr()), ctypes.c_void_p(V.data_ptr()), None,
+                                        ctypes.byref(info)) == 0
+        torch.cuda.synchronize()
+        out.append(V)
+        lib.dfdg_ctx_destroy(c)
+    assert torch.equal(out[0], U) and torch.equal(out[1], U)
