@@ -454,7 +454,8 @@ int dfdg_debug_multigrid(const dfdg_ctx* ctx, int max_levels, int* n_levels, int
  *   which = 0 the operator A_level (level 0 is S, rows in facet-major order F*n_f + m),
  *   which = 1 the prolongator from level + 1 to level (rows: level's unknowns),
  *   which = 2 the dense pseudo-inverse of the coarsest operator (level = last), all n^2
- *   entries, which = 3 and 4 the products A P and R A = P^T A kept for levels 1 .. last - 1.  *n_rows, *n_cols, *nnz are always written; ptr_host[n_rows + 1],
+ *   entries, which = 3 and 4 the products A P and P^T A of levels 1 .. last - 1 (formed for
+ *   the call).  *n_rows, *n_cols, *nnz are always written; ptr_host[n_rows + 1],
  *   cols_host[nnz] and vals_host[nnz] are filled when all three are non-null (call once
  *   with nulls to size them).  DFDG_E_INVALID_ARG for a level or kind that does not exist. */
 /* dfdg_debug_vcycle: z = one multigrid V-cycle (the context's preconditioner, FP32 or FP64

@@ -236,10 +236,10 @@ static Csr matmul(const Csr& A, const Csr& B) {
   return C;
 }
 
-// One damped-Jacobi step on a prolongator: (I - omega D^{-1} A) P, rows merged in column
-// order (both operands' rows are sorted), exact zeros dropped; row ranges on the host's threads.
-static Csr smooth_prolongator(const Csr& A, const std::vector<double>& dinv, double omega, const Csr& Pin) {
-  const Csr AP = matmul(A, Pin);
+// One damped-Jacobi step on a prolongator, given A P: (I - omega D^{-1} A) P, rows merged in
+// column order (both operands' rows are sorted), exact zeros dropped; row ranges on the host's
+// threads.
+static Csr smooth_prolongator(const Csr& AP, const std::vector<double>& dinv, double omega, const Csr& Pin) {
   Csr P;
   P.n = Pin.n;
   P.m = Pin.m;
@@ -467,58 +467,37 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
     const double omega = 4.0 / (3.0 * L.lmax);
     Csr P = std::move(Pt);
     const int steps = level == 0 ? fine_smooth : 1;
-    for (int st = 0; st < steps; ++st) P = smooth_prolongator(L.A, L.dinv, omega, P);
-    Csr R = transpose(P);
-    Csr AP = matmul(L.A, P);
-    Csr Ac = matmul(R, AP);
+    for (int st = 0; st < steps; ++st) P = smooth_prolongator(matmul(L.A, P), L.dinv, omega, P);
+    const Csr AP = matmul(L.A, P);
+    Csr Ac = matmul(transpose(P), AP);
     if (level > 0) {  // the smoothing steps of the coarse levels within their transfers
       const double ith = 1.0 / amg_coarse_theta(L.lmax);
-      Csr C;  // P - D^{-1} A P / th, on the columns of A P (which has those of P)
-      C.n = n;
-      C.m = P.m;
-      C.ptr.assign(n + 1, 0);
+      const Csr C = smooth_prolongator(AP, L.dinv, ith, P);  // Rs^T
+      L.Rs = transpose(C);
       Csr& W = L.Ps;
       W.n = n;
       W.m = n + P.m;
-      W.ptr.assign(n + 1, 0);
-      for (Csr* M : {&C, &W}) {
-        const size_t nz = AP.nnz() + (M == &W ? L.A.nnz() : 0);
-        M->col.reserve(nz);
-        M->val.reserve(nz);
-      }
-      std::vector<int> pos(P.m, -1);
-      for (int i = 0; i < n; ++i) {
-        const double w = ith * L.dinv[i];
-        for (int k = L.A.ptr[i]; k < L.A.ptr[i + 1]; ++k) {
-          const int c = L.A.col[k];
-          W.col.push_back(c);
-          W.val.push_back((c == i ? 2.0 * w : 0.0) - w * L.A.val[k] * (ith * L.dinv[c]));
-        }
-        const size_t c0 = C.col.size();
-        auto add = [&](int c, double v) {
-          if (pos[c] < 0) {
-            pos[c] = (int)C.col.size();
-            C.col.push_back(c);
-            C.val.push_back(0.0);
+      W.ptr.resize(n + 1);
+      for (int i = 0; i <= n; ++i) W.ptr[i] = L.A.ptr[i] + C.ptr[i];
+      W.col.resize(W.ptr[n]);
+      W.val.resize(W.ptr[n]);
+      parallel_chunks(n, [&](int, int b, int e) {
+        for (int i = b; i < e; ++i) {
+          int o = W.ptr[i];
+          const double w = ith * L.dinv[i];
+          for (int k = L.A.ptr[i]; k < L.A.ptr[i + 1]; ++k, ++o) {
+            const int c = L.A.col[k];
+            W.col[o] = c;
+            W.val[o] = (c == i ? 2.0 * w : 0.0) - w * L.A.val[k] * (ith * L.dinv[c]);
           }
-          C.val[pos[c]] += v;
-        };
-        for (int k = AP.ptr[i]; k < AP.ptr[i + 1]; ++k) add(AP.col[k], -w * AP.val[k]);
-        for (int k = P.ptr[i]; k < P.ptr[i + 1]; ++k) add(P.col[k], P.val[k]);
-        for (size_t k = c0; k < C.col.size(); ++k) {
-          pos[C.col[k]] = -1;
-          W.col.push_back(n + C.col[k]);
-          W.val.push_back(C.val[k]);
+          for (int k = C.ptr[i]; k < C.ptr[i + 1]; ++k, ++o) {
+            W.col[o] = n + C.col[k];
+            W.val[o] = C.val[k];
+          }
         }
-        C.ptr[i + 1] = (int)C.col.size();
-        W.ptr[i + 1] = (int)W.col.size();
-      }
-      L.Rs = transpose(C);
-      L.RA = transpose(AP);
-      L.AP = std::move(AP);
+      });
     }
     L.P = std::move(P);
-    L.R = std::move(R);
     AmgLevel next;
     next.A = std::move(Ac);
     H.lv.push_back(std::move(next));
@@ -592,23 +571,13 @@ int build_amg(int E, int NF, int NS, const std::vector<int>& cols, const std::ve
   }
   H.coarse_inv = std::move(D);
   H.n_coarse = nc;
-  H.coarse_fold.clear();
-  if (H.lv.size() >= 3) {
-    const Csr& Rs = H.lv[H.lv.size() - 2].Rs;
-    if ((long)nc * Rs.m <= kAmgFoldValues) {
-      H.coarse_fold.assign((size_t)nc * Rs.m, 0.0);
-      parallel_chunks(nc, [&](int, int r0, int r1) {
-        for (int i = r0; i < r1; ++i) {
-          double* row = &H.coarse_fold[(size_t)i * Rs.m];
-          for (int j = 0; j < nc; ++j) {
-            const double a = H.coarse_inv[(size_t)i * nc + j];
-            for (int k = Rs.ptr[j]; k < Rs.ptr[j + 1]; ++k) row[Rs.col[k]] += a * Rs.val[k];
-          }
-        }
-      });
-    }
-  }
+  H.fold = H.lv.size() >= 3 && (long)nc * H.lv[H.lv.size() - 2].A.n <= kAmgFoldValues;
   return 0;
+}
+
+void amg_products(const AmgLevel& L, Csr& AP, Csr& RA) {
+  AP = matmul(L.A, L.P);
+  RA = transpose(AP);
 }
 
 }  // namespace dfdg

@@ -20,12 +20,13 @@ struct AmgLevel {
   std::vector<double> dinv;
   double lmax = 0;  // spectral radius estimate of D^{-1} A (Chebyshev upper bound)
   Csr P;            // prolongator from the next coarser level to this one (empty on the coarsest)
-  Csr R;            // restriction = P^T
-  Csr AP, RA;       // A P and R A = (A P)^T, kept on levels >= 1 that have a coarser level
-  // on those levels, with one damped Jacobi step x1 = D^{-1} b / th around the coarse correction e:
-  Csr Rs;           // the restricted residual of x1 from b, R (I - A D^{-1} / th)
+  // on levels >= 1 that have a coarser one, with one damped Jacobi step x1 = D^{-1} b / th around
+  // the coarse correction e:
+  Csr Rs;           // the restricted residual of x1 from b, P^T (I - A D^{-1} / th)
   Csr Ps;           // the result from [b; e]: (2 - D^{-1} A / th) D^{-1} / th, then Rs^T
 };
+// A P and P^T A of a level that has a coarser one (no solve reads them: debugging)
+void amg_products(const AmgLevel& L, Csr& AP, Csr& RA);
 inline double amg_smooth_lmax(double lmax) { return 1.05 * lmax; }
 // th of the coarse levels: the centre of [lmax / 30, lmax]
 inline double amg_coarse_theta(double lmax) { return 0.5 * amg_smooth_lmax(lmax) * (1.0 + 1.0 / 30.0); }
@@ -37,9 +38,9 @@ struct AmgHierarchy {
   // finest prolongator by facets: the columns of facet F's rows, p0_ptr[F] .. p0_ptr[F + 1]
   std::vector<int> p0_ptr, p0_col;
   int p0_w = 0, p0_wr = 0;           // the most columns of a facet, and facets of a column
-  // with three levels or more: coarse_inv Rs of the level above (n_c x its unknowns), if within
-  // kAmgFoldValues
-  std::vector<double> coarse_fold;
+  // the last restriction is multiplied into the dense solve (on the device, from Ps): with three
+  // levels or more, if coarse_inv Rs of the level above the coarsest is within kAmgFoldValues
+  bool fold = false;
 };
 // 32 MB in FP32, read at the rate of the memory-side cache in about the time of the launch saved
 constexpr long kAmgFoldValues = 8l << 20;

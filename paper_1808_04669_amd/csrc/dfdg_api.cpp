@@ -482,7 +482,7 @@ static void carve_cycle(const dfdg_ctx* ctx, Carver& c, DevBsr& A, MgDev& mg) {
     const AmgLevel& L = H.lv[l];
     const long n = L.A.n;
     if (l > 0 && l < mg.nlev - 1) {
-      take_csr(L.Rs, mg.Rs[l]);
+      if (!H.fold || l < mg.nlev - 2) take_csr(L.Rs, mg.Rs[l]);
       take_csr(L.Ps, mg.Ps[l]);
     }
     MgVec<double>& v = mg.v64[l];
@@ -517,8 +517,9 @@ static void carve_cycle(const dfdg_ctx* ctx, Carver& c, DevBsr& A, MgDev& mg) {
   }
   if (mg.nlev > 0) {
     mg.n_coarse = H.n_coarse;
-    mg.fold = !H.coarse_fold.empty();
-    const size_t nd = (mg.fold ? H.coarse_fold : H.coarse_inv).size();
+    mg.fold = H.fold;
+    mg.coarse_src = mg.fold ? c.take<double>(H.coarse_inv.size()) : nullptr;
+    const size_t nd = mg.fold ? (size_t)H.n_coarse * H.lv[mg.nlev - 2].A.n : H.coarse_inv.size();
     mg.coarse_inv = c.take<double>(nd);
     mg.coarse_inv32 = f32 ? c.take<float>(nd) : nullptr;
   }
@@ -796,7 +797,8 @@ static int upload_cycle(dfdg_ctx* ctx, DevBsr& A, MgDev& mg) {
   for (int l = 0; l < mg.nlev; ++l) {
     const AmgLevel& L = H.lv[l];
     if (l > 0 && l < mg.nlev - 1) {
-      if (int rc = up_csr(L.Rs, mg.Rs[l])) return rc;
+      if (!mg.fold || l < mg.nlev - 2)
+        if (int rc = up_csr(L.Rs, mg.Rs[l])) return rc;
       if (int rc = up_csr(L.Ps, mg.Ps[l])) return rc;
     }
   }
@@ -847,9 +849,13 @@ static int upload_cycle(dfdg_ctx* ctx, DevBsr& A, MgDev& mg) {
     }
   }
   if (mg.nlev > 0) {
-    const std::vector<double>& dense = mg.fold ? H.coarse_fold : H.coarse_inv;
-    HIPC(up(const_cast<double*>(mg.coarse_inv), dense, s));
-    if (mixed) HIPC(up(const_cast<float*>(mg.coarse_inv32), f32(dense), s));
+    if (mg.fold) {
+      HIPC(up(const_cast<double*>(mg.coarse_src), H.coarse_inv, s));
+      HIPC(launch_fold(mg, s));
+    } else {
+      HIPC(up(const_cast<double*>(mg.coarse_inv), H.coarse_inv, s));
+      if (mixed) HIPC(up(const_cast<float*>(mg.coarse_inv32), f32(H.coarse_inv), s));
+    }
   }
   HIPC(hipStreamSynchronize(s));
   return DFDG_OK;
@@ -1980,11 +1986,11 @@ extern "C" int dfdg_time_kernel(dfdg_ctx* ctx, int which, int reps, float* ms, d
             b += X.half ? np * ((2.0 + NF * 2.0) + (4.0 + (NF + 1) / 2 * 4.0)) : 2.0 * np * (4.0 + NF * vb);
             b += (2.0 * L.A.n + 2.0 * nn) * vb;
           } else {  // restriction with the smoothing step, prolongation with the post-smoothing
-            const bool fold = l + 2 == H.lv.size() && !H.coarse_fold.empty();
+            const bool fold = l + 2 == H.lv.size() && H.fold;
             b += ((fold ? 0 : L.Rs.nnz()) + L.Ps.nnz()) * (vb + 4.0) + 3.0 * L.A.n * vb + 2.0 * nn * vb;
           }
         }
-        b += (double)std::max(H.coarse_inv.size(), H.coarse_fold.size()) * vb;
+        b += (double)H.n_coarse * (H.fold ? H.lv[H.lv.size() - 2].A.n : H.n_coarse) * vb;
         break;
       }
       case 5:    // F in, face coefficients out; Jinv; the packed local inverse (FE4: and det J,
@@ -2080,9 +2086,11 @@ extern "C" int dfdg_debug_multigrid_matrix(const dfdg_ctx* ctx, int level, int w
     return DFDG_OK;
   }
   const AmgLevel& lv = ctx->H.lv[level];
-  const Csr& M = which == 0 ? lv.A : which == 1 ? lv.P : which == 3 ? lv.AP : lv.RA;
   if (which != 0 && level == L - 1) return DFDG_E_INVALID_ARG;
-  if (which >= 3 && M.n == 0) return DFDG_E_INVALID_ARG;
+  if (which >= 3 && level == 0) return DFDG_E_INVALID_ARG;
+  Csr AP, RA;
+  if (which >= 3) amg_products(lv, AP, RA);
+  const Csr& M = which == 0 ? lv.A : which == 1 ? lv.P : which == 3 ? AP : RA;
   *n_rows = M.n;
   *n_cols = M.m;
   *nnz = M.nnz();

@@ -71,9 +71,10 @@ struct MgDev {
   MgVec<double> v64[kMaxLev];
   MgVec<float> v32[kMaxLev];
   int n_coarse = 0;
-  // the dense solve: from the coarsest level's right-hand side, or (AmgHierarchy::coarse_fold)
-  // from that of the level above
+  // the dense solve: from the coarsest level's right-hand side, or (AmgHierarchy::fold) from that of
+  // the level above; coarse_src: the coarsest inverse that the latter is formed from (launch_fold)
   bool fold = false;
+  const double* coarse_src = nullptr;
   const double* coarse_inv = nullptr;
   const float* coarse_inv32 = nullptr;
 };
@@ -81,6 +82,8 @@ template <typename V>
 inline const MgVec<V>& mg_vec(const MgDev& m, int l) {
   if constexpr (sizeof(V) == 8) return m.v64[l]; else return m.v32[l];
 }
+// coarse_inv and coarse_inv32 (where there is one) from coarse_src and the last level's Ps.
+hipError_t launch_fold(const MgDev& mg, hipStream_t s);
 // z = V-cycle(b) (one smoothed-aggregation multigrid cycle run in type V on PCG vectors
 // of type VB); writes the (b, z) partial of each facet block into rz[2*block].  Every
 // kernel returns at once when sc->done says the PCG has stopped.

@@ -1815,6 +1815,38 @@ __global__ __launch_bounds__(kBlk) void k_dense_mv(int n, int m, const double* _
   if (live && t == 0) x[i] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
+// The last restriction Rs multiplied into the coarsest inverse (set-up): Ps's rows end in those of
+// Rs^T (columns from its n on), so that entry (i, c) of the product is their dot product with row i
+// of the inverse, held in LDS.  A block takes kFoldRows rows i, so that Ps is read from the cache
+// as often as there are blocks: 852 x 7228 values (256^2 BDM_2) in 1.4 ms
+// (on 16 cores of the host, and uploaded, 50).
+constexpr int kFoldRows = 4;
+__global__ __launch_bounds__(kBlk) void k_fold(int nc, int n, DevCsr Ps, const double* __restrict__ inv,
+                                               double* __restrict__ out, float* __restrict__ out32) {
+  extern __shared__ double rows[];  // [kFoldRows][nc]
+  const int i0 = blockIdx.x * kFoldRows, ni = min(kFoldRows, nc - i0);
+  for (int j = threadIdx.x; j < kFoldRows * nc; j += kBlk) rows[j] = j < ni * nc ? inv[(size_t)i0 * nc + j] : 0.0;
+  __syncthreads();
+  for (int c = blockIdx.y * kBlk + threadIdx.x; c < n; c += gridDim.y * kBlk) {
+    double t[kFoldRows] = {};
+    const int* __restrict__ col = Ps.col + (size_t)c * Ps.w;
+    const double* __restrict__ val = Ps.val + (size_t)c * Ps.w;
+    for (int k = 0; k < Ps.w; ++k) {
+      const int j = col[k] - n;
+      if (j < 0) continue;
+      const double v = val[k];
+#pragma unroll
+      for (int i = 0; i < kFoldRows; ++i) t[i] += v * rows[i * nc + j];
+    }
+#pragma unroll
+    for (int i = 0; i < kFoldRows; ++i) {
+      if (i >= ni) break;
+      out[(size_t)(i0 + i) * n + c] = t[i];
+      if (out32) out32[(size_t)(i0 + i) * n + c] = (float)t[i];
+    }
+  }
+}
+
 __global__ void k_add_f32(long n, const float* __restrict__ x, double* __restrict__ y) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] += (double)x[i];
@@ -2584,6 +2616,17 @@ static void xfer(int NF, const DevXfer& X, bool up, const V* in, V* out, const P
     case 4: run(std::integral_constant<int, 4>{}); break;
     default: run(std::integral_constant<int, 6>{}); break;
   }
+}
+
+hipError_t launch_fold(const MgDev& mg, hipStream_t s) {
+  const int nc = mg.n_coarse, n = mg.Ps[mg.nlev - 2].n;
+  const size_t lds = sizeof(double) * kFoldRows * nc;  // nc <= 4096: within the 160 KB of a CU
+  hipError_t e = hipFuncSetAttribute((const void*)k_fold, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_fold, dim3((nc + kFoldRows - 1) / kFoldRows, (n + 4 * kBlk - 1) / (4 * kBlk)), dim3(kBlk), lds, s,
+                     nc, n, mg.Ps[mg.nlev - 2], mg.coarse_src, const_cast<double*>(mg.coarse_inv),
+                     const_cast<float*>(mg.coarse_inv32));
+  return hipGetLastError();
 }
 
 // Everything of a cycle after the first pre-smoothing step (x2 = pre(b) already in v0.x).
