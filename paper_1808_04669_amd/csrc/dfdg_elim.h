@@ -29,12 +29,12 @@ struct ElimHost {
 // cubes 6^3 BDM_1 0.59 / 2.22, 11^3 BDM_1 1.34 / 2.84, 8^3 BDM_2 1.44 / 3.51.
 // The lines are not where the two cost the same.  Triangles: from 64x64 BDM_2 (36864 unknowns)
 // on, the iteration counts of the multigrid solves, their growth with the mesh and what better
-// start values save of them are tested properties of a context.  Tetrahedra: the separators of
-// a cube make the matrices grow much faster than the system; at the line the workspace is
-// 1.6 GB (0.1 GB without) and the set-up 0.08 s longer (0.2 s in all).
+// start values save of them are tested properties of a context, and the elimination stays below.
+// Tetrahedra: the separators of a cube make the matrices grow much faster than the system; at
+// the line (11^3 BDM_1) a context keeps 0.5 GB (0.1 GB with the cycle), its bind works in 1.1 GB
+// more, and it is set up in 0.10 s (0.11 s).
 constexpr long kElimUnknowns2 = 32768, kElimUnknowns3 = 65536;
 constexpr long kElimValues2 = 48L << 20, kElimValues3 = 128L << 20;
-constexpr int kElimMaxVec = 12288;  // unknowns of a front or of the interface, padded (held in LDS)
 
 // The partition with the fewest values in its matrices; false if none is within the limits.
 bool build_elim(const MeshHost& m, int NF, ElimHost& el);

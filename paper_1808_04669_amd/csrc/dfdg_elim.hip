@@ -364,7 +364,7 @@ hipError_t launch_elim_apply(const ElimDev& D, const DevGeo& g, const double* r,
                              PcgScalars* sc, hipStream_t s) {
   const int NF = D.NF, n = D.ng * NF, rows = 32;
   const size_t front = sizeof(float) * ((D.maxV + 3) & ~3), top = sizeof(float) * ((n + 3) & ~3);
-  if (std::max(D.maxV, n) > kElimMaxVec_) return hipErrorInvalidValue;  // the vectors are held in LDS
+  if (std::max(D.maxV, n) > kElimMaxVec) return hipErrorInvalidValue;  // the vectors are held in LDS
   const PcgScalars* csc = sc;
   hipLaunchKernelGGL(k_el_forward, dim3(D.nc, (D.maxN + 63) / 64), dim3(kBlk), front, s, D, r, (const double*)rz,
                      g.fgrid, sc);

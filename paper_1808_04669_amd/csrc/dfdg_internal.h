@@ -54,6 +54,9 @@ __host__ __device__ constexpr int nPairs(int NF, int NS) { return (NS * NF * NF 
 // tetrahedral meshes at k = 2 (each thread takes half the row's outputs), else 1.
 __host__ __device__ constexpr int facet_split(int NF, int NS) { return (NF % 2 == 0 && NS * NF * NF > 128) ? 2 : 1; }
 constexpr int kMaxEvalPts = 1024;
+// Unknowns of a front or of the interface of the block elimination, padded: the solve kernels
+// hold such a vector in LDS.
+constexpr int kElimMaxVec = 12288;
 
 // The modal tables of the tetrahedral residual in one array (offsets in doubles): traces
 // tr [4][P][NF] and reference gradients dg [4][P][NM][3] of the basis in face modes (NM =

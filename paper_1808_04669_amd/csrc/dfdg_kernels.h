@@ -100,7 +100,6 @@ hipError_t launch_pcg_iteration_mg(int NF, const DevGeo& g, const DevBsr& A, con
 
 // Block elimination of the facet system on small meshes (dfdg_elim.hip): index lists as in
 // ElimHost, solve matrices in FP32, fronts and panels of the set-up in FP64.
-constexpr int kElimMaxVec_ = 12288;
 struct ElimDev {
   int nc, ng, NF, maxB, maxN, maxV;
   const int *boff, *bfac, *noff, *ngam, *nfac, *gfac, *gpos, *gcell, *eoff, *elem, *elp;
