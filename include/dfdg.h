@@ -152,8 +152,9 @@ typedef struct {
   int mg_fine_smooth;/* DFDG_AMG: damped-Jacobi steps smoothing the finest level's tentative
                         prolongator, 1..3 (default 2; the coarser levels take one): more steps
                         give a wider interpolation, fewer PCG iterations and costlier
-                        finest-level transfers (rows of up to 16 entries stay packed in FP16
-                        when the next level has fewer than 65536 unknowns) */
+                        finest-level transfers (in FP16 in an FP32 cycle with mg_fine_fp16 where
+                        no facet has more than 16 columns and the next level has fewer than
+                        65536 unknowns) */
   int local_space;   /* element-local unknowns of the condensation (triangle meshes):
                         DFDG_LOCAL_FE3 (default): broken [P^k]^2 velocity with the P^{k-1}
                         pressure w of eq. (FE3), the local projector applied as
@@ -263,8 +264,8 @@ int dfdg_mesh_set_outflow(dfdg_mesh* mesh, const int32_t* open_host);
 /* ---- context --------------------------------------------------------------------
  * dfdg_ctx_create validates the parameters and does the host part of setup
  * (reference tabulations, geometry, condensation matrices, facet matrix).  On
- * tetrahedral meshes it accepts k = 1, 2, DFDG_FP64 and the Jacobi or block-Jacobi
- * preconditioner (other requests return DFDG_E_UNSUPPORTED).
+ * tetrahedral meshes it accepts k = 1, 2 and DFDG_FP64 (other requests return
+ * DFDG_E_UNSUPPORTED).
  * hip_stream is a hipStream_t (NULL = default stream).  The mesh may be destroyed
  * afterwards. */
 void dfdg_params_default(dfdg_params* p);

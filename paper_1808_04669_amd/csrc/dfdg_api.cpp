@@ -1086,22 +1086,22 @@ static int capture_iteration(dfdg_ctx* ctx, int parity, int count, Step step, hi
   return DFDG_OK;
 }
 
-// Run PCG iterations (already initialised on the device) until the device flags an end.
-// The host enqueues chunks of iterations (graph replays or eager launches) and reads the
-// scalars after each chunk.  The first chunk is the length of the previous run (*hint);
-// later chunks follow the mean contraction of (r, r) observed so far, so that few
-// iterations run past the end (those exit at their first instruction).
 // Point Jacobi with the update and the product in one kernel (launch_pcg_jacobi): on S in
 // blocks, while one pass of the grid covers the rows and the caller has not set a smaller grid.
 // An RK3 step, two kernels -> one: 32^2 BDM_2 8.9 -> 4.7 ms, 128^2 BDM_3 35 -> 29, 256^2 BDM_2
-// 128 -> 118, 6^3 7.0 -> 3.6, 16^3 22.5 -> 20.5; beyond, where the values of S count, three products of
-// a row cost more than they save (400^2 BDM_3: 350 -> 380).
+// 128 -> 118, 6^3 7.0 -> 3.6, 16^3 22.5 -> 20.5; beyond, where the values of S count, three
+// products of a row cost more than they save (400^2 BDM_3: 350 -> 380).
 static bool one_launch_jacobi(const dfdg_ctx* ctx) {
   const long parts = (long)ctx->E * facet_split(ctx->NF, ctx->A.ns);
   return ctx->prm.precond == DFDG_JACOBI && !ctx->A.mfq && parts <= kOneLaunchRows &&
          ctx->g.fgrid == facet_grid_size((int)parts, 0);
 }
 
+// Run PCG iterations (already initialised on the device) until the device flags an end.
+// The host enqueues chunks of iterations (graph replays or eager launches) and reads the
+// scalars after each chunk.  The first chunk is the length of the previous run (*hint);
+// later chunks follow the mean contraction of (r, r) observed so far, so that few
+// iterations run past the end (those leave at the stop flag).
 template <typename Step>
 static int pcg_loop(dfdg_ctx* ctx, PcgScalars* sc, int maxit, Step step, hipGraphExec_t (&graph)[6], int* hint,
                     PcgScalars& fin) {

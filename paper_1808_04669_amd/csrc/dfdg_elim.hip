@@ -1,5 +1,5 @@
 // Block elimination of the facet system on small meshes, the PCG's preconditioner there
-// (gfx950): an exact solve in FP32 up to rounding, in three kernels.
+// (gfx950): an exact solve in FP32 up to rounding, in three kernels and one for (r, z).
 //
 // Why.  On a small mesh every kernel of the multigrid cycle costs 2.4 to 8 us of serial memory
 // round trips plus a kernel boundary, whatever its few rows; an iteration of 10 to 12 kernels

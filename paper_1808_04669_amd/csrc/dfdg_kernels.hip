@@ -7,7 +7,7 @@
 // one contiguous 512-byte segment.  Facet vectors are [E][n_f].
 //
 // Reductions (PCG dot products) are deterministic and use neither atomics nor fences: each
-// block reduces its lanes with wavefront shuffles and LDS and writes one partial; the next
+// block reduces its lanes with register moves and LDS and writes one partial; the next
 // kernel's blocks each sum all partials in the same fixed order.  (A per-block device-scope
 // release fence would write back the XCD's whole L2 on every block.)
 #include <climits>
@@ -632,8 +632,8 @@ __global__ __launch_bounds__(kEBlk) void k_recover(DevGeo g, DevTabs tb, const F
 // a5: facet PCG
 // ---------------------------------------------------------------------------------------
 
-// Facet kernels run a grid-stride loop over facet rows on a grid of at most kMaxFacetGrid
-// blocks, so that the partial buffers (and the redundant reductions) stay small.
+// The facet kernels run a grid-stride loop over facet rows on facet_grid_size() blocks, at most
+// kMaxFacetGrid, so that the partial buffers (and the redundant reductions) stay small.
 
 // g_F = q_{L,f_L} + q_{R,f_R}; partials (g,g), (zdef,g) and (q_L,q_L) + (q_R,q_R), the size
 // of the element contributions that the sum cancels.
@@ -2512,8 +2512,8 @@ hipError_t launch_pcg_update(int NF, int pc, const DevGeo& g, const DevBsr& A, c
 hipError_t launch_pcg_jacobi(int NF, const DevGeo& g, const DevBsr& A, const double* r_in, double* r_out,
                              const double* s_in, double* s_out, const double* p_in, double* p_out, double* x,
                              const PcgBufs& pb, int it, hipStream_t s) {
-  // one row part per thread, the smallest blocks that keep the partials few (64^2 BDM_2, 12288 facets: 17.8 ms an RK4 step with blocks of 64, 33.3
-  // with blocks of 256)
+  // one row part per thread, the smallest blocks that keep the partials few (64^2 BDM_2, 12288
+  // facets: 17.8 ms an RK4 step with blocks of 64, 33.3 with blocks of 256)
   const int units = g.E * facet_split(NF, A.ns);
   const int B = units > kPartsPerThread * 128 * 128 ? 256 : units > kPartsPerThread * 64 * 64 ? 128 : 64;
   const int G = (units + B - 1) / B;
