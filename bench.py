@@ -280,14 +280,15 @@ def three_d(args):
                     ("jacobi_assembled", dict(precond="jacobi", matrix_free="assembled")))
 
     def products(solver, assembled, reps):
-        """The facet products: kernel, time, bytes (the entry point's count for element products
-        has z and p_old read by both passes; the second one reads the two sides only)."""
+        """The facet products: kernel, time, bytes with each array counted once (for the element
+        products the entry point counts z and p_old for both sides of a face and again for the
+        second pass, which reads the two sides only)."""
         ms, b = solver.time_kernel(0, reps=reps)
         if assembled or solver.T < 32768:
             name = "k_pcg_spmv<6, 7> (7-slot face BSR SpMV + p update + (p,Sp) partials)"
         else:
             name = "k_mf_apply3<2> + k_mf_sum<6> (element products + p update + (p,Sp) partials)"
-            b -= 16.0 * solver.n_lambda
+            b -= 32.0 * solver.n_lambda
         return name, ms, b
 
     wanted = [v for v in args.three_d_variants.split(",") if v]
